@@ -9,10 +9,13 @@
 //     (Sec. 2.1) is (rh ^ gh) | (rl ^ gl) over 32 bases;
 //   - gathers the window from the resident bit-plane reference with funnel
 //     shifts (v_alignbit) at any base offset;
-//   - never stores a mask: each of the 2e+1 masks is built, amended, refined
-//     and ANDed into one running accumulator of W registers;
-//   - amends with neighbour funnels and 3-input logic (v_bitop3) instead of a
-//     look-up table, and counts with v_bcnt instead of a table.
+//   - never stores a mask: each of the 2e+1 masks is built and folded into one
+//     running accumulator of W registers;
+//   - amends without a look-up table: a 0 that stays lies in a run of three or
+//     more 0s (or a run that touches an end), so each mask only contributes
+//     where three 0s in a row are centred, and widening those centres back
+//     into runs is done once, on what all masks of a direction collected; the
+//     1s are counted with v_bcnt instead of a table.
 //
 // Steps per pair, all from Sec. 2.1 unless noted:
 //   H        = mismatch(read, window)
@@ -76,6 +79,7 @@ __device__ __forceinline__ void planes_from_words(uint32_t p0, uint32_t p1, uint
 // A 0 at position i is amended iff it lies in a 0-run of length 1 or 2 with
 // 1s on both sides: M[i-1]&M[i+1] | M[i-1]&M[i+2] | M[i-2]&M[i+1].
 // Positions outside [0, m) read as 0, so runs touching an end never qualify.
+// Used for shifts of 32 bases and more only.
 template <int W>
 __device__ __forceinline__ void amend_and(const uint32_t (&M)[W], uint32_t (&acc)[W],
                                           const uint32_t (&X)[W])
@@ -103,44 +107,161 @@ __device__ __forceinline__ void mismatch(const uint32_t (&sh)[W], const uint32_t
         M[w] = (sh[w] ^ gh[w]) | (sl[w] ^ gl[w]);
 }
 
-// Fast path: every word but the top one is fully inside the read
-// (32(W-1) < m <= 32W) and k <= 31, so the refined positions of D_k lie in
-// word 0 and those of I_k in words W-2 and W-1.  Read and window planes have
-// no bits at or beyond m.
-template <int W, bool REFINE = true>
-__device__ __forceinline__ uint32_t filter_exact(const uint32_t (&rh)[W], const uint32_t (&rl)[W],
-                                                 const uint32_t (&gh)[W], const uint32_t (&gl)[W],
-                                                 uint32_t m, uint32_t kmax)
+// M[i-1] | M[i] | M[i+1] of word w (0 outside the words): 0 where three 0s in
+// a row are centred.
+template <int W>
+__device__ __forceinline__ uint32_t centres(const uint32_t (&M)[W], int w)
 {
-    const uint32_t vtop = ones_below((int)m - 32 * (W - 1));  // valid bits of the top word
-    uint32_t acc[W], M[W], X[W], sh[W], sl[W];
+    const uint32_t l1 = funnel(M[w], w > 0 ? M[w - 1] : 0u, 31);
+    const uint32_t r1 = funnel(w < W - 1 ? M[w + 1] : 0u, M[w], 1);
+    return M[w] | l1 | r1;
+}
+
+// x shifted up by q bits (towards higher positions); q < 32 unless ANY.
+template <int W, bool ANY>
+__device__ __forceinline__ void shift_up(uint32_t (&x)[W], uint32_t q)
+{
+    if constexpr (ANY) {
+#pragma unroll
+        for (int step = 8; step >= 1; step >>= 1)
+            if (step < W) {
+#pragma unroll
+                for (int w = W - 1; w >= 0; --w)
+                    x[w] = ((q >> 5) & (uint32_t)step) ? (w >= step ? x[w - step] : 0u) : x[w];
+            }
+    }
+    const uint32_t s = q & 31u;
+    if (s != 0u) {
+#pragma unroll
+        for (int w = W - 1; w >= 0; --w)
+            x[w] = w > 0 ? funnel(x[w], x[w - 1], 32u - s) : x[0] << s;
+    }
+}
+
+// x shifted down by q bits.
+template <int W, bool ANY>
+__device__ __forceinline__ void shift_down(uint32_t (&x)[W], uint32_t q)
+{
+    if constexpr (ANY) {
+#pragma unroll
+        for (int step = 8; step >= 1; step >>= 1)
+            if (step < W) {
+#pragma unroll
+                for (int w = 0; w < W; ++w)
+                    x[w] = ((q >> 5) & (uint32_t)step) ? (w + step < W ? x[w + step] : 0u) : x[w];
+            }
+    }
+    const uint32_t s = q & 31u;
+#pragma unroll
+    for (int w = 0; w < W; ++w)
+        x[w] = funnel(w < W - 1 ? x[w + 1] : 0u, x[w], s);
+}
+
+// Widens collected centres: bit i of the result is 0 iff A is 0 at i-1, i or
+// i+1.  below / above: A at position -1 (bit 0 of below) and at position 32W
+// (bit 31 of above).
+template <int W>
+__device__ __forceinline__ void widen(const uint32_t (&A)[W], uint32_t below, uint32_t above,
+                                      uint32_t (&F)[W])
+{
 #pragma unroll
     for (int w = 0; w < W; ++w) {
-        acc[w] = 0xFFFFFFFFu;
-        X[w] = 0u;
+        const uint32_t l1 = w > 0 ? funnel(A[w], A[w - 1], 31) : (A[0] << 1) | (below & 1u);
+        const uint32_t r1 = w < W - 1 ? funnel(A[w + 1], A[w], 1)
+                                      : (A[W - 1] >> 1) | (above & 0x80000000u);
+        F[w] = A[w] & l1 & r1;
     }
-    mismatch<W>(rh, rl, gh, gl, M);            // Hamming mask (never refined)
-    amend_and<W>(M, acc, X);
+}
 
-    // Deletion masks: read[i-k] against window[i]; refined on [0, k).
-    uint32_t lead = 0u;
+// The masks of shifts 0..kmax, kmax <= min(31, m - 1), ANDed into F.  Read and
+// window planes have no bits at or beyond m.  Without ANY every word but the
+// top one is fully inside the read (32(W-1) < m <= 32W); with it m is any
+// length up to 32W.  REFINE: the vacated positions of a shifted mask are 1
+// after amendment (Sec. 3.4).
+//
+// VALU issue bounds the filter from about e = 6 at 100 bases up.  A mask costs
+// 8 instructions per word: 2 to shift the read's planes, 2 to compare, 2 for
+// the neighbours, 2 to collect (or, and bitop3).  Amending each mask by itself
+// took 11 (two more neighbour funnels and one more three-input logic): the
+// plain launch at 250 bases, e = 25, 2^23 pairs went from 1,023 to 734 us, at
+// 150 bases, e = 7, 3 M pairs from 96 to 86 us, and at 100 bases, e = 5, where
+// the window gathers bound it, stayed at 363 us (2^24 pairs).
+//
+// What is collected: a 0 of a mask stays 0 iff it lies in a run of at least
+// three 0s, where positions outside the read count as 0s (runs touching an end
+// stay), i.e. iff a centre of three 0s lies next to it or on it.  Widening
+// centres into runs distributes over AND, so all masks share one pass at the
+// end.  Refinement: in a deletion mask D_k only positions i >= k may stay 0.
+// Centres at k+1 or higher widen into those only and are collected in A;
+// centre k (0s at k-1, k, k+1) gives positions k and k+1, collected in PA, and
+// centre k-1 position k, collected in PB; lower ones give nothing.  An
+// insertion mask I_k is the mirror image at the read's end: for those the
+// planes are shifted up so that the last base is bit 31 of the top word, which
+// keeps the masks of both directions in one word and, with one k per step, in
+// scalar registers.
+template <int W, bool ANY, bool REFINE>
+__device__ __forceinline__ void near_masks(uint32_t (&rh)[W], uint32_t (&rl)[W],
+                                           uint32_t (&gh)[W], uint32_t (&gl)[W], uint32_t m,
+                                           uint32_t kmax, uint32_t (&F)[W])
+{
+    uint32_t A[W], M[W], sh[W], sl[W];
+    mismatch<W>(rh, rl, gh, gl, M);            // Hamming mask (never refined)
+    uint32_t first = M[0], last = M[W - 1];    // mask bits 0 and 32W - 1 (centres -1 and 32W)
+#pragma unroll
+    for (int w = 0; w < W; ++w)
+        A[w] = centres<W>(M, w);
+
+    // Deletion masks: read[i-k] against window[i].
+    uint32_t PA = 0xFFFFFFFFu, PB = 0xFFFFFFFFu;
+    const uint32_t vtop = ones_below((int)m - 32 * (W - 1));
     for (uint32_t k = 1; k <= kmax; ++k) {
-        lead = (lead << 1) | 1u;
 #pragma unroll
         for (int w = 0; w < W; ++w) {
             sh[w] = w > 0 ? funnel(rh[w], rh[w - 1], 32u - k) : (rh[0] << k);
             sl[w] = w > 0 ? funnel(rl[w], rl[w - 1], 32u - k) : (rl[0] << k);
         }
         mismatch<W>(sh, sl, gh, gl, M);
-        M[W - 1] &= vtop;                      // bases moved past the read end
-        uint32_t Xd[W];
+        if constexpr (ANY) {
 #pragma unroll
-        for (int w = 0; w < W; ++w)
-            Xd[w] = (REFINE && w == 0) ? lead : 0u;
-        amend_and<W>(M, acc, Xd);
+            for (int w = 0; w < W; ++w)
+                M[w] &= ones_below((int)m - 32 * w);
+        } else {
+            M[W - 1] &= vtop;                  // bases moved past the read end
+        }
+        last &= M[W - 1];
+        if constexpr (!REFINE)
+            first &= M[0];
+#pragma unroll
+        for (int w = 0; w < W; ++w) {
+            const uint32_t c = centres<W>(M, w);
+            if (REFINE && w == 0) {
+                A[0] &= c | ((2u << k) - 1u);
+                PA &= c | ~(1u << k);
+                PB &= c | ~(1u << (k - 1u));
+            } else {
+                A[w] &= c;
+            }
+        }
+    }
+    widen<W>(A, first, last, F);
+    if constexpr (REFINE) {
+        F[0] &= PA & ((PA << 1) | 1u) & ((PB << 1) | 1u);
+        if constexpr (W >= 2)
+            F[1] &= (PA >> 31) | ~1u;
     }
 
-    // Insertion masks: read[i+k] against window[i]; refined on [m-k, m).
+    // Insertion masks: read[i+k] against window[i], last base in bit 31 of
+    // word W-1, first base in bit q.
+    const uint32_t q = 32u * W - m;
+    shift_up<W, ANY>(rh, q);
+    shift_up<W, ANY>(rl, q);
+    shift_up<W, ANY>(gh, q);
+    shift_up<W, ANY>(gl, q);
+    PA = PB = first = last = 0xFFFFFFFFu;
+#pragma unroll
+    for (int w = 0; w < W; ++w)
+        A[w] = 0xFFFFFFFFu;
+    const uint32_t vlow = 0xFFFFFFFFu << (q & 31u);
     for (uint32_t k = 1; k <= kmax; ++k) {
 #pragma unroll
         for (int w = 0; w < W; ++w) {
@@ -148,25 +269,54 @@ __device__ __forceinline__ uint32_t filter_exact(const uint32_t (&rh)[W], const 
             sl[w] = w < W - 1 ? funnel(rl[w + 1], rl[w], k) : (rl[W - 1] >> k);
         }
         mismatch<W>(sh, sl, gh, gl, M);
-        // With V = valid bits of words (W-2, W-1) = (all ones, vtop), the
-        // positions >= m-k are those where (V >> k) is 0.  Bits at or above m
-        // may be set in Xi: acc is already 0 there.
-        uint32_t Xi[W];
+        if constexpr (ANY) {
 #pragma unroll
-        for (int w = 0; w < W; ++w)
-            Xi[w] = 0u;
-        if (REFINE) {
-            Xi[W - 1] = ~(vtop >> k);
-            if (W >= 2)
-                Xi[W >= 2 ? W - 2 : 0] = ~funnel(vtop, 0xFFFFFFFFu, k);
+            for (int w = 0; w < W; ++w)
+                M[w] &= ~ones_below((int)q - 32 * w);
+        } else {
+            M[0] &= vlow;                      // bases moved past the read start
         }
-        amend_and<W>(M, acc, Xi);
+        first &= M[0];
+        if constexpr (!REFINE)
+            last &= M[W - 1];
+#pragma unroll
+        for (int w = 0; w < W; ++w) {
+            const uint32_t c = centres<W>(M, w);
+            if (REFINE && w == W - 1) {
+                A[W - 1] &= c | (0xFFFFFFFFu << (31u - k));
+                PA &= c | ~(1u << (31u - k));
+                PB &= c | ~(1u << (32u - k));
+            } else {
+                A[w] &= c;
+            }
+        }
     }
+    uint32_t G[W];
+    widen<W>(A, first, last, G);
+    if constexpr (REFINE) {
+        G[W - 1] &= PA & ((PA >> 1) | 0x80000000u) & ((PB >> 1) | 0x80000000u);
+        if constexpr (W >= 2)
+            G[W - 2] &= (PA << 31) | 0x7FFFFFFFu;
+    }
+    shift_down<W, ANY>(G, q);
+#pragma unroll
+    for (int w = 0; w < W; ++w)
+        F[w] &= G[w];
+}
 
+// Fast path: 32(W-1) < m <= 32W and kmax <= 31.
+template <int W, bool REFINE = true>
+__device__ __forceinline__ uint32_t filter_exact(uint32_t (&rh)[W], uint32_t (&rl)[W],
+                                                 uint32_t (&gh)[W], uint32_t (&gl)[W],
+                                                 uint32_t m, uint32_t kmax)
+{
+    uint32_t F[W];
+    near_masks<W, false, REFINE>(rh, rl, gh, gl, m, kmax, F);
+    F[W - 1] &= ones_below((int)m - 32 * (W - 1));
     uint32_t est = 0;
 #pragma unroll
     for (int w = 0; w < W; ++w)
-        est += __builtin_popcount(acc[w]);
+        est += __builtin_popcount(F[w]);
     return est;
 }
 
@@ -186,91 +336,96 @@ __device__ __forceinline__ void load_read(const FilterArgs &a, uint32_t r, uint3
     }
 }
 
-// General path: any m <= 32W and any k <= m-1 <= 511.  Shifts of 32 bases or
-// more move whole words: the read planes are shifted in place by one word each
-// time k passes a multiple of 32, and rebuilt between the deletion and the
+// General path: any m <= 32W and any k <= m-1 <= 511.  Shifts below 32 as
+// near_masks; from 32 bases on whole words move: the read planes are shifted
+// in place by one word each time k passes a multiple of 32, each mask is
+// amended by itself, and the planes are rebuilt between the deletion and the
 // insertion loop: reloaded from the read rows in memory, or, with KEPT (reads
 // that exist only in registers), taken again from the pair's words.
 template <int W, int L, bool REFINE = true, bool KEPT = false>
 __device__ __forceinline__ uint32_t filter_general(const FilterArgs &a, uint32_t r,
                                                    const uint32_t (&words)[2 * W],
                                                    uint32_t (&rh)[W], uint32_t (&rl)[W],
-                                                   const uint32_t (&gh)[W],
-                                                   const uint32_t (&gl)[W], uint32_t m,
-                                                   uint32_t kmax)
+                                                   uint32_t (&gh)[W], uint32_t (&gl)[W],
+                                                   uint32_t m, uint32_t kmax)
 {
-    uint32_t V[W], acc[W], M[W], X[W], sh[W], sl[W];
+    uint32_t V[W], acc[W];
 #pragma unroll
     for (int w = 0; w < W; ++w) {
         V[w] = ones_below((int)m - 32 * w);
         rh[w] &= V[w];
         rl[w] &= V[w];
-        acc[w] = 0xFFFFFFFFu;
-        X[w] = 0u;
     }
-    mismatch<W>(rh, rl, gh, gl, M);
-    amend_and<W>(M, acc, X);
+    near_masks<W, true, REFINE>(rh, rl, gh, gl, m, kmax < 31u ? kmax : 31u, acc);
 
-    for (uint32_t k = 1; k <= kmax; ++k) {
-        if (k > 1 && ((k - 1) & 31u) == 0u) {  // read moves up one more word
+    if (W > 1 && kmax > 31u) {
+        const uint32_t q = 32u * W - m;
+        shift_down<W, true>(rh, q);
+        shift_down<W, true>(rl, q);
+        shift_down<W, true>(gh, q);
+        shift_down<W, true>(gl, q);
+        uint32_t M[W], X[W], sh[W], sl[W];
+        for (uint32_t k = 32; k <= kmax; ++k) {
+            if (((k - 1) & 31u) == 0u) {           // read moves up one more word
 #pragma unroll
-            for (int w = W - 1; w >= 0; --w) {
-                rh[w] = w > 0 ? rh[w - 1] : 0u;
-                rl[w] = w > 0 ? rl[w - 1] : 0u;
+                for (int w = W - 1; w >= 0; --w) {
+                    rh[w] = w > 0 ? rh[w - 1] : 0u;
+                    rl[w] = w > 0 ? rl[w - 1] : 0u;
+                }
             }
-        }
-        const uint32_t s = 32u - (k - ((k - 1) & ~31u));  // in [0, 31]
-#pragma unroll
-        for (int w = 0; w < W; ++w) {
-            sh[w] = funnel(rh[w], w > 0 ? rh[w - 1] : 0u, s);
-            sl[w] = funnel(rl[w], w > 0 ? rl[w - 1] : 0u, s);
-        }
-        mismatch<W>(sh, sl, gh, gl, M);
-#pragma unroll
-        for (int w = 0; w < W; ++w) {
-            M[w] &= V[w];
-            X[w] = REFINE ? ones_below((int)k - 32 * w) : 0u;
-        }
-        amend_and<W>(M, acc, X);
-    }
-
-    if constexpr (KEPT) {
-#pragma unroll
-        for (int w = 0; w < W; ++w)
-            planes_from_words<L>(words[2 * w], words[2 * w + 1], rh[w], rl[w]);
-    } else {
-        load_read<W, L>(a, r, m, rh, rl);
-    }
-#pragma unroll
-    for (int w = 0; w < W; ++w) {
-        rh[w] &= V[w];
-        rl[w] &= V[w];
-    }
-    for (uint32_t k = 1; k <= kmax; ++k) {
-        if ((k & 31u) == 0u) {                 // read moves down one more word
+            const uint32_t s = 32u - (k - ((k - 1) & ~31u));  // in [0, 31]
 #pragma unroll
             for (int w = 0; w < W; ++w) {
-                rh[w] = w < W - 1 ? rh[w + 1] : 0u;
-                rl[w] = w < W - 1 ? rl[w + 1] : 0u;
+                sh[w] = funnel(rh[w], w > 0 ? rh[w - 1] : 0u, s);
+                sl[w] = funnel(rl[w], w > 0 ? rl[w - 1] : 0u, s);
             }
+            mismatch<W>(sh, sl, gh, gl, M);
+#pragma unroll
+            for (int w = 0; w < W; ++w) {
+                M[w] &= V[w];
+                X[w] = REFINE ? ones_below((int)k - 32 * w) : 0u;
+            }
+            amend_and<W>(M, acc, X);
         }
-        const uint32_t s = k & 31u;
+
+        if constexpr (KEPT) {
+#pragma unroll
+            for (int w = 0; w < W; ++w)
+                planes_from_words<L>(words[2 * w], words[2 * w + 1], rh[w], rl[w]);
+        } else {
+            load_read<W, L>(a, r, m, rh, rl);
+        }
 #pragma unroll
         for (int w = 0; w < W; ++w) {
-            sh[w] = funnel(w < W - 1 ? rh[w + 1] : 0u, rh[w], s);
-            sl[w] = funnel(w < W - 1 ? rl[w + 1] : 0u, rl[w], s);
+            rh[w] &= V[w];
+            rl[w] &= V[w];
         }
-        mismatch<W>(sh, sl, gh, gl, M);
+        for (uint32_t k = 32; k <= kmax; ++k) {
+            if ((k & 31u) == 0u) {                 // read moves down one more word
 #pragma unroll
-        for (int w = 0; w < W; ++w)
-            X[w] = REFINE ? V[w] & ~ones_below((int)m - (int)k - 32 * w) : 0u;
-        amend_and<W>(M, acc, X);
+                for (int w = 0; w < W; ++w) {
+                    rh[w] = w < W - 1 ? rh[w + 1] : 0u;
+                    rl[w] = w < W - 1 ? rl[w + 1] : 0u;
+                }
+            }
+            const uint32_t s = k & 31u;
+#pragma unroll
+            for (int w = 0; w < W; ++w) {
+                sh[w] = funnel(w < W - 1 ? rh[w + 1] : 0u, rh[w], s);
+                sl[w] = funnel(w < W - 1 ? rl[w + 1] : 0u, rl[w], s);
+            }
+            mismatch<W>(sh, sl, gh, gl, M);
+#pragma unroll
+            for (int w = 0; w < W; ++w)
+                X[w] = REFINE ? V[w] & ~ones_below((int)m - (int)k - 32 * w) : 0u;
+            amend_and<W>(M, acc, X);
+        }
     }
 
     uint32_t est = 0;
 #pragma unroll
     for (int w = 0; w < W; ++w)
-        est += __builtin_popcount(acc[w]);
+        est += __builtin_popcount(acc[w] & V[w]);
     return est;
 }
 
