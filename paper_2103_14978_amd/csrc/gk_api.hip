@@ -619,7 +619,14 @@ int prepare_batch(gk_ctx *ctx, const gk_batch *b, const char *who, gkd::FilterAr
     a.accept = b->accept;
     a.est = b->est;
     a.accept_bits = reinterpret_cast<unsigned long long *>(b->accept_bits);
-    a.stream_reads = b->pair_read == nullptr;
+    if (b->n_reads == 0) {
+        // Every pair is GK_INVALID; the kernels' speculative loads of read 0
+        // go to the reference planes.
+        a.pitch = 0;
+        a.reads = reinterpret_cast<const uint32_t *>(ctx->ref_planes);
+        a.read_len = reinterpret_cast<const uint16_t *>(ctx->ref_planes);
+        a.read_has_n = nullptr;
+    }
     return GK_OK;
 }
 
@@ -857,7 +864,6 @@ int gk_filter_mixed(gk_ctx *ctx, const gk_batch *b, void *stream)
         return fail(ctx, GK_EDEVICE, "gk_filter_mixed: hipSetDevice failed");
     if ((st = ensure_mixed_scratch(ctx, b->n_pairs)) != GK_OK)
         return st;
-    a.stream_reads = 0;     // the mixed kernel reads each pair entry twice
     const uint32_t wmax = (b->max_read_len + 31) / 32;
     gkd::MixedArgs x{};
     if ((st = mixed_args(ctx, ctx->mixed, wmax, b->read_layout, x)) != GK_OK)
@@ -955,7 +961,6 @@ int gk_filter_mixed_noalloc(gk_ctx *ctx, const gk_batch *b, void *stream)
     DeviceGuard g(ctx->device);
     if (!g.ok)
         return fail(ctx, GK_EDEVICE, "gk_filter_mixed_noalloc: hipSetDevice failed");
-    a.stream_reads = 0;     // the mixed kernel reads each pair entry twice
     const uint32_t wmax = (b->max_read_len + 31) / 32;
     gkd::MixedArgs x{};
     if ((st = mixed_args(ctx, ctx->mixed, wmax, b->read_layout, x)) != GK_OK)
@@ -1094,7 +1099,6 @@ int gk_tune_mixed(gk_ctx *ctx, const gk_batch *b, void *stream, uint64_t sample_
         return fail(ctx, GK_EDEVICE, "gk_tune_mixed: hipSetDevice failed");
     if ((st = ensure_mixed_scratch(ctx, b->n_pairs)) != GK_OK)
         return st;
-    a.stream_reads = 0;
     const uint32_t wmax = (b->max_read_len + 31) / 32;
     const uint64_t n_full = b->n_pairs;
     if (sample_pairs && sample_pairs < a.n_pairs)

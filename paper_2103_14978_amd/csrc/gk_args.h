@@ -33,7 +33,7 @@ constexpr uint32_t REF_SHIFT_WORDS = 8;
 
 struct FilterArgs {
     const uint2 *ref_planes;
-    const uint2 *ref_planes_b;  // ref_planes shifted by REF_SHIFT_WORDS, or NULL
+    const uint2 *ref_planes_b;  // ref_planes shifted by REF_SHIFT_WORDS
     const uint32_t *ref_unk;
     const unsigned long long *ref_unk_lines;  // bit L: bases [512 L, 512 L + 512)
                                               // hold an unknown base
@@ -46,9 +46,6 @@ struct FilterArgs {
                                 // read rows hold ceil(max_read_len/16) words
     uint32_t rows;              // ceil(max_read_len / 16)
     uint32_t flags;             // GK_FLAG_* variant semantics (0: the paper's)
-    uint32_t stream_reads;      // 1: every read and pair entry is used once
-                                // (load them non-temporally), 0: reads are
-                                // shared by several pairs (keep them cached)
     const uint32_t *reads;
     const uint16_t *read_len;
     const uint8_t *read_has_n;

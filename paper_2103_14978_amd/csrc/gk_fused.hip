@@ -91,10 +91,12 @@ void k_filter_ascii(FilterArgs a, const uint8_t *ascii,
     if (i < n) {
         PairIdx p;
         p.r = i;
-        p.pos = ld_once(a, a.cand_pos + i);
-        p.e = a.e_pair ? (uint32_t)ld_once(a, a.e_pair + i) : a.e_uniform;
+        p.pos = a.cand_pos[i];
+        p.e = a.e_pair ? (uint32_t)a.e_pair[i] : a.e_uniform;
         PairData<W> d;
         load_window<W>(a, p.pos, d);
+        load_unknown_lines<W>(a, p.pos, d);
+        d.has_n = 0u;                 // the text's unknown bases are found below
         const uint64_t off = read_off[i];
         // offsets that decrease give an empty read, as in the read encoder
         const uint64_t len = read_off[i + 1] >= off ? read_off[i + 1] - off : 0u;

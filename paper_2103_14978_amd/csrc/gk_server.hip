@@ -257,10 +257,12 @@ gkd::FilterArgs args_for(const gk_server *s, const Req *q, uint64_t first, uint6
     a.read_has_n = q->d_hasn;
     a.pair_read = q->d_pr ? q->d_pr + first : nullptr;
     if (!q->d_pr && first > 0) {
+        // (with no read left the kernels' speculative loads take read 0)
         a.n_reads = first < q->r.n_reads ? (uint32_t)(q->r.n_reads - first) : 0u;
-        a.reads = q->d_packed + first;
-        a.read_len = q->d_len + first;
-        a.read_has_n = q->d_hasn + first;
+        const uint64_t skip = a.n_reads ? first : 0u;
+        a.reads = q->d_packed + skip;
+        a.read_len = q->d_len + skip;
+        a.read_has_n = q->d_hasn + skip;
     }
     a.cand_pos = q->d_pos + first;
     a.e_pair = nullptr;
@@ -268,7 +270,6 @@ gkd::FilterArgs args_for(const gk_server *s, const Req *q, uint64_t first, uint6
     a.accept = q->d_acc + first;
     a.est = q->d_est + first;
     a.accept_bits = nullptr;
-    a.stream_reads = 0;
     return a;
 }
 

@@ -245,30 +245,22 @@ __device__ __forceinline__ void load_data_rm(const FilterArgs &a, const PairIdx 
                                              uint32_t rm_stride)
 {
     const uint32_t r = p.r < a.n_reads ? p.r : 0u;
-    const uint32_t pos = p.pos < a.ref_len ? p.pos : 0u;
-    d.m = a.n_reads ? (uint32_t)a.read_len[r] : 0u;
     const uint4 *q = reinterpret_cast<const uint4 *>(rm + (size_t)r * rm_stride);
 #pragma unroll
-    for (int j = 0; j < 2 * W; j += 4) {
-        uint4 v = make_uint4(0u, 0u, 0u, 0u);
-        if (a.n_reads && (uint32_t)j < a.rows)
-            v = q[j / 4];
+    for (int j = 0; j < 2 * W; j += 4) {           // rows > 2W - 2 >= j
+        const uint4 v = q[j / 4];
         const uint32_t w4[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
         for (int k = 0; k < 4; ++k)
             if (j + k < 2 * W)
                 d.words[j + k] = w4[k];
     }
-    // the window, as load_data takes it
-    const uint32_t w0 = pos >> 5;
-    const uint32_t span = (pos & 31u) + a.max_read_len;
-    const uint32_t nw = (span + 31u) >> 5;
-    const bool use_b = a.ref_planes_b != nullptr && w0 >= REF_SHIFT_WORDS &&
-                       (w0 & (LINE_WORDS - 1u)) + nw > LINE_WORDS;
-    const uint2 *src = use_b ? a.ref_planes_b + (w0 - REF_SHIFT_WORDS) : a.ref_planes + w0;
-#pragma unroll
-    for (int w = 0; w <= W; ++w)
-        d.win[w] = 32u * w < span ? src[w] : make_uint2(0u, 0u);
+    const uint8_t *flag = a.read_has_n ? a.read_has_n
+                                       : reinterpret_cast<const uint8_t *>(a.read_len);
+    d.m = (uint32_t)a.read_len[r];
+    d.has_n = (uint32_t)flag[r];
+    load_window<W>(a, p.pos, d);
+    load_unknown_lines<W>(a, p.pos, d);
 }
 
 // Transposed read rows (word j of read r at reads[j * pitch + r]) to the
