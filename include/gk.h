@@ -201,6 +201,8 @@ typedef struct gk_batch {
  * Plain filter: one kernel launch over all pairs of the batch (one launch per
  * 2^30 pairs), one GPU lane per pair at a time (Sec. 3.2: one thread per
  * filtration), the read and window held as 32-base bit-planes in registers.
+ * A large batch with a threshold per pair (2^18 pairs or more, max_read_len
+ * above 128) is sorted by threshold within workgroups, as gk_filter_mixed does.
  * Asynchronous on stream.
  * Errors (nothing launched): GK_EINVAL for NULL required pointers, pitch <
  * n_reads, n_reads or pitch >= 2^30, max_read_len outside 1..512, e_uniform
@@ -328,18 +330,24 @@ int gk_verify(gk_ctx *ctx, const gk_batch *batch, const uint8_t *accept, uint16_
                                      flight; 65536 = one residency of the
                                      device.  Range 0..65536.                */
 
-#define GK_OPT_MIXED_TILE           2  /* gk_filter_mixed: pairs per tile,
-                                            2048, 4096 (default) or 8192    */
+#define GK_OPT_MIXED_TILE           2  /* gk_filter_mixed: four times the
+                                            pairs a workgroup sorts at a time,
+                                            2048, 4096 (default) or 8192.
+                                            While no GK_OPT_MIXED_* differs
+                                            from its default, the batch size
+                                            picks 512, 1024 or 2048 pairs.  */
 #define GK_OPT_MIXED_PAIRS_PER_LANE 3  /* gk_filter_mixed: 1 (default) or 2
                                             pairs per lane per chunk        */
 #define GK_OPT_MIXED_SORT_E         4  /* gk_filter_mixed: 1 (default) sorts
                                             a tile by (W, min(e, m-1)), 0 by
                                             W only                          */
 #define GK_OPT_MIXED_BLOCKS_PER_CU  5  /* gk_filter_mixed: persistent
-                                            workgroups per CU, 0 (default) =
-                                            as many as fit, else 1..64      */
+                                            workgroups per CU of the captured
+                                            form, 0 (default) = as many as
+                                            fit, else 1..64                 */
 #define GK_OPT_MIXED_GRAPH          6  /* gk_filter_mixed: 1 (default)
-                                            replays a captured hipGraph, 0
+                                            replays a captured hipGraph where
+                                            that form is used, 0 always
                                             launches directly               */
 #define GK_OPT_HOST_ENCODE_THREADS  7  /* gk_filter_host with ASCII reads:
                                             0 (default) copies the text and
@@ -381,25 +389,26 @@ int gk_get_option(const gk_ctx *ctx, int option, int64_t *value);
  * pairs differ in read length and threshold (the paper compiles both in,
  * Sec. 3.1, and would launch once per (length, e) group).
  *
- * One persistent launch covers the batch: workgroups claim tiles of
- * consecutive pairs from a device counter, counting-sort each tile in LDS by
- * (words per mask, min(e, m-1)) and run each 64-lane chunk through the fast
- * path for its read length; pairs with more than 31 shifts are finished by a
- * general-path pass; accept bits (if requested) by a pass over the accept
- * codes.  The launch sequence is captured in a hipGraph the first time a
- * given shape (words per mask, read layout) and tuning are seen and replayed
- * after that (GK_OPT_MIXED_GRAPH): the batch's arguments reach the graph
+ * One launch covers the batch: a workgroup takes a tile of consecutive
+ * pairs, counting-sorts it in LDS by (words per mask, min(e, m-1)) and runs
+ * each 64-lane chunk through the fast path for its read length, pairs with
+ * more than 31 shifts through the general path.  That launch is direct, one
+ * workgroup per tile, unless a tuning was set (GK_OPT_MIXED_*, gk_tune_mixed)
+ * and the batch has fewer tiles than the device has compute units: then
+ * resident workgroups claim the tiles, in a hipGraph captured the first time
+ * a given shape (words per mask, read layout) and tuning are seen and replayed
+ * after that (GK_OPT_MIXED_GRAPH); the batch's arguments reach the graph
  * through a device table that a copy on the stream fills before each replay,
  * so every batch of that shape replays the same graph.  Batches of more than
- * 2^30 pairs, and batches with variant flags, are launched directly.
+ * 2^30 pairs, and batches with variant flags, are always launched directly.
  * Results are identical to gk_filter's.
  *
  * Same batch rules and errors as gk_filter.  The context keeps scratch for
- * it: two counters, a residual list of min(n_pairs, 2^30) entries (grown on
- * demand), the device argument table and four pinned host copies of it (a
- * call waits until the replay four calls earlier has read its copy), all
- * kept until gk_destroy.  Calls that overlap on one context race on that
- * scratch: one gk_filter_mixed at a time per context, on one stream.
+ * the captured form: a counter, the device argument table and four pinned
+ * host copies of it (a call waits until the replay four calls earlier has
+ * read its copy), all allocated by the first call and kept until gk_destroy.
+ * Calls that overlap on one context race on that scratch: one
+ * gk_filter_mixed at a time per context, on one stream.
  * Asynchronous on stream.
  */
 int gk_filter_mixed(gk_ctx *ctx, const gk_batch *batch, void *stream);
@@ -407,22 +416,11 @@ int gk_filter_mixed(gk_ctx *ctx, const gk_batch *batch, void *stream);
 /*
  * gk_filter_mixed for callers that cannot allocate device memory: code under
  * HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.
- * Same batch rules, tuning (GK_OPT_MIXED_*), launch sequence and results as
- * gk_filter_mixed, launched directly on stream (no hipGraph; the graph
- * option is ignored).  It calls no hipMalloc or hipFree and allocates no
- * stream, event or graph.
- *
- * Scratch: the tile counter, the residual count and a residual list of up
- * to GK_NOALLOC_MAX_PAIRS entries live in one fixed device array of the
- * library (16 MiB + 256 B), of which every GPU holds its own copy from the
- * library's load until the process ends; gk_create takes its address on the
- * context's device.  n_pairs above GK_NOALLOC_MAX_PAIRS returns GK_ERANGE
- * with nothing launched; n_pairs == 0 returns GK_OK with nothing launched.
- * Every call on one GPU, from any context and on any stream, uses that GPU's
- * one array, and the array keeps the last call's contents (the launch
- * sequence zeroes the counters first): calls that overlap on one GPU race
- * and give undefined results.  Order them on one stream, or wait for one
- * before starting the next.  Asynchronous on stream.
+ * Same batch rules, tuning (GK_OPT_MIXED_*) and results as gk_filter_mixed,
+ * always in its direct form on stream.  It calls no hipMalloc or hipFree,
+ * allocates no stream, event or graph, and uses no scratch memory.
+ * n_pairs above GK_NOALLOC_MAX_PAIRS returns GK_ERANGE with nothing launched;
+ * n_pairs == 0 returns GK_OK with nothing launched.  Asynchronous on stream.
  */
 int gk_filter_mixed_noalloc(gk_ctx *ctx, const gk_batch *batch, void *stream);
 

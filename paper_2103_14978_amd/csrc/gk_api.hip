@@ -77,44 +77,6 @@ hipError_t finish_reference(gk_ctx *ctx, uint64_t words, uint64_t alloc_words,
     return e;
 }
 
-// Scratch of gk_filter_mixed_noalloc: the tile counter and the residual
-// count (words 0 and 1), then, from word NOALLOC_LIST_WORD, the residual
-// list of up to GK_NOALLOC_MAX_PAIRS pair indices.  A file-scope device
-// array, so the entry point allocates nothing; every device holds its own
-// copy until the process ends.  Host code never uses the name itself: its
-// device address is taken once per device (scratch_setup, from gk_create)
-// and kept in g_scratch.
-}  // namespace
-
-namespace gkd {
-constexpr uint32_t NOALLOC_LIST_WORD = 64;
-__device__ __align__(256) uint32_t scratch[NOALLOC_LIST_WORD + GK_NOALLOC_MAX_PAIRS];
-}  // namespace gkd
-
-namespace {
-
-constexpr int MAX_DEVICES = 256;
-std::mutex g_scratch_mu;
-uint32_t *g_scratch[MAX_DEVICES] = {};
-
-// With `device` current: its address of the scratch array, once per device.
-hipError_t scratch_setup(int device)
-{
-    if (device < 0 || device >= MAX_DEVICES)
-        return hipErrorInvalidDevice;
-    std::lock_guard<std::mutex> lock(g_scratch_mu);
-    if (g_scratch[device])
-        return hipSuccess;
-    void *p = nullptr;
-    const hipError_t e = hipGetSymbolAddress(&p, HIP_SYMBOL(gkd::scratch));
-    if (e != hipSuccess)
-        return e;
-    if (!p)
-        return hipErrorInvalidSymbol;
-    g_scratch[device] = static_cast<uint32_t *>(p);
-    return hipSuccess;
-}
-
 std::atomic<uint64_t> g_fail_alloc_at{0};   // 0: allocations are never failed
 
 // Whether this allocation is the one gk_detail_fail_alloc asked to fail.
@@ -125,14 +87,6 @@ bool take_injected_failure()
         if (g_fail_alloc_at.compare_exchange_weak(left, left - 1))
             return left == 1;
     return false;
-}
-
-uint32_t *scratch_of(int device)
-{
-    if (device < 0 || device >= MAX_DEVICES)
-        return nullptr;
-    std::lock_guard<std::mutex> lock(g_scratch_mu);
-    return g_scratch[device];
 }
 
 }  // namespace
@@ -311,14 +265,6 @@ int gk_create(int device, gk_ctx **out)
         g_create_error = std::string("gk_create: hipMalloc: ") + hipGetErrorName(e);
         return e == hipErrorOutOfMemory ? GK_ENOMEM : GK_EDEVICE;
     }
-    e = scratch_setup(device);
-    if (e != hipSuccess) {
-        (void)hipFree(ctx->d_counter);
-        delete ctx;
-        g_create_error = std::string("gk_create: device scratch address: ") +
-                         hipGetErrorName(e);
-        return GK_EDEVICE;
-    }
     int st = apply_env_options(ctx);
     if (st == GK_OK)
         st = apply_env_flags(ctx);
@@ -343,10 +289,8 @@ void gk_destroy(gk_ctx *ctx)
             (void)hipFree(ctx->d_counter);
         if (ctx->graph_exec)
             (void)hipGraphExecDestroy(ctx->graph_exec);
-        if (ctx->d_mixed_counters)
-            (void)hipFree(ctx->d_mixed_counters);
-        if (ctx->d_resid)
-            (void)hipFree(ctx->d_resid);
+        if (ctx->d_tile_counter)
+            (void)hipFree(ctx->d_tile_counter);
         if (ctx->capture_stream)
             (void)hipStreamDestroy(ctx->capture_stream);
         if (ctx->d_table)
@@ -638,27 +582,14 @@ void drop_graph(gk_ctx *ctx)
     ctx->graph_key.clear();
 }
 
-// Scratch for the mixed launch: counters and a residual list able to hold
-// every pair of one launch (at most 2^30).
-int ensure_mixed_scratch(gk_ctx *ctx, uint64_t n_pairs)
+// Scratch for the table form of the mixed launch.
+int ensure_mixed_scratch(gk_ctx *ctx)
 {
     hipError_t e;
-    if (!ctx->d_mixed_counters) {
-        e = gk_dmalloc(&ctx->d_mixed_counters, 2 * sizeof(uint32_t));
+    if (!ctx->d_tile_counter) {
+        e = gk_dmalloc(&ctx->d_tile_counter, sizeof(uint32_t));
         if (e != hipSuccess)
-            return hip_fail(ctx, e, "gk_filter_mixed: hipMalloc counters");
-    }
-    const uint64_t need = n_pairs < (1ull << 30) ? n_pairs : (1ull << 30);
-    if (ctx->resid_cap < need) {
-        drop_graph(ctx);
-        if (ctx->d_resid)
-            (void)hipFree(ctx->d_resid);
-        ctx->d_resid = nullptr;
-        ctx->resid_cap = 0;
-        e = gk_dmalloc(&ctx->d_resid, need * sizeof(uint32_t));
-        if (e != hipSuccess)
-            return hip_fail(ctx, e, "gk_filter_mixed: hipMalloc residual list");
-        ctx->resid_cap = need;
+            return hip_fail(ctx, e, "gk_filter_mixed: hipMalloc counter");
     }
     if (!ctx->capture_stream) {
         e = hipStreamCreateWithFlags(&ctx->capture_stream, hipStreamNonBlocking);
@@ -685,27 +616,47 @@ int ensure_mixed_scratch(gk_ctx *ctx, uint64_t n_pairs)
     return GK_OK;
 }
 
+// One batch as the device table's contents, through a pinned slot.
+hipError_t copy_table(gk_ctx *ctx, int slot, const gkd::FilterArgs &a, uint32_t tile,
+                      hipStream_t s)
+{
+    gkd::BatchTable *h = ctx->h_table[slot];
+    h->n_batches = 1;
+    h->prefix[0] = 0;
+    h->prefix[1] = (uint32_t)((a.n_pairs + tile - 1) / tile);
+    h->args[0] = a;
+    const size_t bytes = offsetof(gkd::BatchTable, args) + sizeof(gkd::FilterArgs);
+    return hipMemcpyAsync(ctx->d_table, h, bytes, hipMemcpyHostToDevice, s);
+}
+
+gkd::MixedArgs direct_args(const gk_ctx *ctx, uint64_t n_pairs, uint32_t wmax)
+{
+    const MixedConfig &c = ctx->mixed;
+    gkd::MixedArgs x{};
+    x.tile = c.untouched() ? gkd::mixed_auto_tile(n_pairs, wmax) : gkd::mixed_tile(c.tile);
+    x.ppl = c.ppl;
+    x.sort_e = c.sort_e;
+    return x;
+}
+
 int mixed_args(gk_ctx *ctx, const MixedConfig &c, uint32_t wmax, uint32_t layout,
                gkd::MixedArgs &x)
 {
+    const uint32_t tile = gkd::mixed_tile(c.tile);
     int per_cu = 0;
-    hipError_t e = gkd::mixed_blocks_per_cu(wmax, layout, c.tile, c.ppl, &per_cu);
+    hipError_t e = gkd::mixed_blocks_per_cu(wmax, layout, tile, c.ppl, &per_cu);
     if (e != hipSuccess)
         return hip_fail(ctx, e, "gk_filter_mixed: occupancy");
     if (per_cu < 1)
         per_cu = 1;
     const uint32_t bpc = c.blocks_per_cu && (int)c.blocks_per_cu < per_cu ? c.blocks_per_cu
                                                                           : (uint32_t)per_cu;
-    x.table = nullptr;
-    x.tile_counter = ctx->d_mixed_counters;
-    x.resid_count = ctx->d_mixed_counters + 1;
-    x.resid_list = ctx->d_resid;
-    x.n_tiles = 0;
-    x.tile = c.tile;
+    x.table = ctx->d_table;
+    x.tile_counter = ctx->d_tile_counter;
+    x.tile = tile;
     x.ppl = c.ppl;
     x.sort_e = c.sort_e;
     x.blocks = bpc * (uint32_t)ctx->cu_count;
-    x.resid_blocks = 2u * (uint32_t)ctx->cu_count;
     return GK_OK;
 }
 
@@ -730,8 +681,18 @@ int gk_filter(gk_ctx *ctx, const gk_batch *b, void *stream)
                   "pairs per lane %u (0: automatic), flags %u",
                   (unsigned long long)b->n_pairs, b->n_reads, words, b->read_layout,
                   b->e ? "per pair" : "uniform", ctx->pairs_per_lane, b->flags);
-    hipError_t e = gkd::launch_filter(a, words, b->read_layout, ctx->pairs_per_lane,
-                                      (hipStream_t)stream);
+    hipError_t e;
+    if (a.flags == 0u && ctx->pairs_per_lane == 0 &&
+        gkd::filter_sorts(b->e != nullptr, b->n_pairs, words)) {
+        gkd::MixedArgs x{};
+        x.tile = 1024;
+        x.ppl = 1;
+        x.sort_e = 1;
+        e = gkd::launch_mixed(a, x, words, b->read_layout, (hipStream_t)stream);
+    } else {
+        e = gkd::launch_filter(a, words, b->read_layout, ctx->pairs_per_lane,
+                               (hipStream_t)stream);
+    }
     if (e != hipSuccess)
         return hip_fail(ctx, e, "gk_filter: launch");
     return GK_OK;
@@ -862,33 +823,35 @@ int gk_filter_mixed(gk_ctx *ctx, const gk_batch *b, void *stream)
     DeviceGuard g(ctx->device);
     if (!g.ok)
         return fail(ctx, GK_EDEVICE, "gk_filter_mixed: hipSetDevice failed");
-    if ((st = ensure_mixed_scratch(ctx, b->n_pairs)) != GK_OK)
+    if ((st = ensure_mixed_scratch(ctx)) != GK_OK)
         return st;
     const uint32_t wmax = (b->max_read_len + 31) / 32;
-    gkd::MixedArgs x{};
-    if ((st = mixed_args(ctx, ctx->mixed, wmax, b->read_layout, x)) != GK_OK)
-        return st;
+    gkd::MixedArgs x = direct_args(ctx, b->n_pairs, wmax);
     hipError_t e;
     const hipStream_t hs = (hipStream_t)stream;
-    // Direct launches: graphs off, variant semantics (their own kernels), or
-    // a batch of more than one launch chunk (2^30 pairs).
-    if (!ctx->use_graph || a.flags != 0u || b->n_pairs > (1ull << 30)) {
+    // Direct form unless a tuning was set and the batch leaves compute units
+    // without a tile: one launch without the argument copy, the graph's launch
+    // and the counter reset before it (60,001 pairs: 21 against about 55 us;
+    // 2^24 pairs: 805 against 850).  Always for variant semantics (their own
+    // kernels) and batches of more than one launch chunk (2^30 pairs).
+    const uint64_t n_tiles = (b->n_pairs + x.tile - 1) / x.tile;
+    if (!ctx->use_graph || a.flags != 0u || b->n_pairs > (1ull << 30) ||
+        ctx->mixed.untouched() || n_tiles >= (uint64_t)ctx->cu_count) {
         gk_detail_log(ctx, "gk_filter_mixed: %llu pairs, direct launch (tile %u, %u per lane, "
-                      "sort by e %u, %u workgroups)", (unsigned long long)b->n_pairs, x.tile,
-                      x.ppl, x.sort_e, x.blocks);
+                      "sort by e %u)", (unsigned long long)b->n_pairs, x.tile, x.ppl, x.sort_e);
         e = gkd::launch_mixed(a, x, wmax, b->read_layout, hs);
         if (e != hipSuccess)
             return hip_fail(ctx, e, "gk_filter_mixed: launch");
         return GK_OK;
     }
-    // Graph: the captured sequence (reset, persistent kernel, residual pass)
-    // reads the batch from the context's device table, which a copy on the
-    // stream fills before each replay; so one graph serves every batch of a
-    // given shape (words per mask, layout) and tuning, captured the first
-    // time that pair is seen.
-    x.table = ctx->d_table;
+    if ((st = mixed_args(ctx, ctx->mixed, wmax, b->read_layout, x)) != GK_OK)
+        return st;
+    // Graph: the captured sequence (reset, persistent kernel) reads the batch
+    // from the context's device table, which a copy on the stream fills before
+    // each replay; so one graph serves every batch of a given shape (words per
+    // mask, layout) and tuning, captured the first time that pair is seen.
     const uint32_t shape[8] = {wmax <= 4 ? 4u : (wmax <= 10 ? 10u : 16u), b->read_layout, x.tile,
-                               x.ppl, x.sort_e, x.blocks, x.resid_blocks, 0u};
+                               x.ppl, x.sort_e, x.blocks, 0u, 0u};
     std::vector<uint8_t> key(sizeof shape);
     std::memcpy(key.data(), shape, sizeof shape);
     const bool capture = !ctx->graph_exec || key != ctx->graph_key;
@@ -920,14 +883,7 @@ int gk_filter_mixed(gk_ctx *ctx, const gk_batch *b, void *stream)
     const int slot = (int)(ctx->table_next++ % gk_ctx::TABLE_RING);
     if (ctx->table_used[slot] && (e = hipEventSynchronize(ctx->table_ev[slot])) != hipSuccess)
         return hip_fail(ctx, e, "gk_filter_mixed: table slot");
-    gkd::BatchTable *h = ctx->h_table[slot];
-    h->n_batches = 1;
-    h->prefix[0] = 0;
-    h->prefix[1] = (uint32_t)((b->n_pairs + x.tile - 1) / x.tile);
-    h->args[0] = a;
-    h->args[0].accept_bits = nullptr;
-    const size_t bytes = offsetof(gkd::BatchTable, args) + sizeof(gkd::FilterArgs);
-    e = hipMemcpyAsync(ctx->d_table, h, bytes, hipMemcpyHostToDevice, hs);
+    e = copy_table(ctx, slot, a, x.tile, hs);
     if (e == hipSuccess)
         e = hipGraphLaunch(ctx->graph_exec, hs);
     if (e == hipSuccess)
@@ -935,11 +891,6 @@ int gk_filter_mixed(gk_ctx *ctx, const gk_batch *b, void *stream)
     if (e != hipSuccess)
         return hip_fail(ctx, e, "gk_filter_mixed: graph launch");
     ctx->table_used[slot] = true;
-    if (a.accept_bits) {
-        e = gkd::launch_accept_bits(a.accept, b->n_pairs, a.accept_bits, hs);
-        if (e != hipSuccess)
-            return hip_fail(ctx, e, "gk_filter_mixed: accept bits");
-    }
     return GK_OK;
 }
 
@@ -955,21 +906,11 @@ int gk_filter_mixed_noalloc(gk_ctx *ctx, const gk_batch *b, void *stream)
     if (b->n_pairs > GK_NOALLOC_MAX_PAIRS)
         return fail(ctx, GK_ERANGE,
                     "gk_filter_mixed_noalloc: n_pairs above GK_NOALLOC_MAX_PAIRS (4194304)");
-    uint32_t *scr = scratch_of(ctx->device);
-    if (!scr)
-        return fail(ctx, GK_EDEVICE, "gk_filter_mixed_noalloc: no scratch address for the device");
     DeviceGuard g(ctx->device);
     if (!g.ok)
         return fail(ctx, GK_EDEVICE, "gk_filter_mixed_noalloc: hipSetDevice failed");
     const uint32_t wmax = (b->max_read_len + 31) / 32;
-    gkd::MixedArgs x{};
-    if ((st = mixed_args(ctx, ctx->mixed, wmax, b->read_layout, x)) != GK_OK)
-        return st;
-    // The same launch sequence as gk_filter_mixed (its first kernel zeroes
-    // the two counters), on the library's scratch array and without a graph.
-    x.tile_counter = scr;
-    x.resid_count = scr + 1;
-    x.resid_list = scr + gkd::NOALLOC_LIST_WORD;
+    const gkd::MixedArgs x = direct_args(ctx, b->n_pairs, wmax);
     const hipError_t e = gkd::launch_mixed(a, x, wmax, b->read_layout, (hipStream_t)stream);
     if (e != hipSuccess)
         return hip_fail(ctx, e, "gk_filter_mixed_noalloc: launch");
@@ -1097,12 +1038,13 @@ int gk_tune_mixed(gk_ctx *ctx, const gk_batch *b, void *stream, uint64_t sample_
     DeviceGuard g(ctx->device);
     if (!g.ok)
         return fail(ctx, GK_EDEVICE, "gk_tune_mixed: hipSetDevice failed");
-    if ((st = ensure_mixed_scratch(ctx, b->n_pairs)) != GK_OK)
+    if ((st = ensure_mixed_scratch(ctx)) != GK_OK)
         return st;
     const uint32_t wmax = (b->max_read_len + 31) / 32;
     const uint64_t n_full = b->n_pairs;
     if (sample_pairs && sample_pairs < a.n_pairs)
         a.n_pairs = sample_pairs;
+    a.n_pairs = std::min<uint64_t>(a.n_pairs, 1ull << 30);
     a.accept_bits = nullptr;
 
     // Key: device, CU count, words per mask, layout, threshold mode, batch
@@ -1181,7 +1123,8 @@ int gk_tune_mixed(gk_ctx *ctx, const gk_batch *b, void *stream, uint64_t sample_
         for (uint32_t ppl : {1u, 2u}) {
             if (ppl == 2 && wmax > 10)
                 continue;                      // two pairs per lane only up to 10 words
-            if ((err = gkd::mixed_blocks_per_cu(wmax, b->read_layout, tile, ppl, &full_bpc)) !=
+            if ((err = gkd::mixed_blocks_per_cu(wmax, b->read_layout, gkd::mixed_tile(tile), ppl,
+                                                &full_bpc)) !=
                 hipSuccess)
                 break;
             for (uint32_t sort_e : {0u, 1u})
@@ -1193,11 +1136,14 @@ int gk_tune_mixed(gk_ctx *ctx, const gk_batch *b, void *stream, uint64_t sample_
                         (void)hipEventDestroy(e1);
                         return st;
                     }
+                    // (slot 0: no earlier replay reads it once this ends)
+                    if ((err = hipDeviceSynchronize()) == hipSuccess)
+                        err = copy_table(ctx, 0, a, x.tile, s);
                     float times[5];
                     for (int rep_i = -1; rep_i < 5 && err == hipSuccess; ++rep_i) {
                         err = hipEventRecord(e0, s);
                         if (err == hipSuccess)
-                            err = gkd::launch_mixed(a, x, wmax, b->read_layout, s);
+                            err = gkd::launch_mixed_table(x, wmax, b->read_layout, s);
                         if (err == hipSuccess)
                             err = hipEventRecord(e1, s);
                         if (err == hipSuccess)

@@ -68,17 +68,39 @@ struct BatchTable {
     FilterArgs args[MAX_TABLE_BATCHES];
 };
 
+// Pairs per tile of the mixed launch for a value of GK_OPT_MIXED_TILE.
+inline uint32_t mixed_tile(uint32_t option) { return option / 4; }
+
+// Pairs per tile where no tuning was set.  A small batch needs tiles enough
+// for every compute unit (60,001 mixed pairs over 3.1 Gbp: 21 us with 512, 30
+// with 1024, 47 with 2048 pairs); a large one gains from fuller chunks (2^24
+// pairs: 1,092, 837 and 805 us; 2^20: 81, 66 and 68).  Up to 4 words per mask
+// eight waves per SIMD fit the registers, and only 512-pair tiles leave the LDS
+// for them (2^24 pairs of 100 bases: 475, 563 and 774 us).
+inline uint32_t mixed_auto_tile(uint64_t n_pairs, uint32_t wmax)
+{
+    return wmax <= 4 || n_pairs < (1u << 19) ? 512u : n_pairs < (1u << 22) ? 1024u : 2048u;
+}
+
+// Whether the plain call sorts its pairs first (the direct form of the mixed
+// launch): a threshold per pair makes a wave of neighbours run the largest of
+// its thresholds.  4 M pairs, e per pair up to a tenth of the length: 250 bases
+// 384 us as they come, 252 sorted; 150 bases 161 and 135; mixed lengths up to
+// 300 944 and 206.  At 4 words per mask and fewer the sort costs more than it
+// saves where the lengths are equal (128 bases: 115 and 143 us), and under 2^18
+// pairs one wave per SIMD runs either way, without the sort's steps before it.
+inline bool filter_sorts(bool e_per_pair, uint64_t n_pairs, uint32_t wmax)
+{
+    return e_per_pair && wmax >= 5 && n_pairs >= (1u << 18);
+}
+
 struct MixedArgs {
-    const BatchTable *table;     // device table, or nullptr for the single batch
-    uint32_t *tile_counter;      // zeroed by the launch sequence
-    uint32_t *resid_count;       // zeroed by the launch sequence
-    uint32_t *resid_list;        // capacity >= pairs per launch
-    uint32_t n_tiles;            // set per launch
-    uint32_t tile;               // pairs per tile (multiple of 256, <= 8192)
+    const BatchTable *table;     // table form: the device table
+    uint32_t *tile_counter;      // table form: zeroed by the launch sequence
+    uint32_t tile;               // pairs per tile (multiple of 256, <= 2048)
     uint32_t ppl;                // 1 or 2
     uint32_t sort_e;             // 0 or 1
-    uint32_t blocks;             // persistent workgroups
-    uint32_t resid_blocks;       // grid of the residual pass
+    uint32_t blocks;             // table form: persistent workgroups
 };
 
 }  // namespace gkd

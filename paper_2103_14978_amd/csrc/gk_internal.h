@@ -14,10 +14,17 @@
 
 // Tuning of the mixed-batch launch (never changes results).
 struct MixedConfig {
-    uint32_t tile = 4096;         // pairs per tile: 2048, 4096 or 8192
+    uint32_t tile = 4096;         // four times the pairs per tile: 2048, 4096 or 8192
     uint32_t ppl = 1;             // pairs per lane per chunk: 1 or 2
     uint32_t sort_e = 1;          // sort a tile by (W, k_max) (1) or by W only (0)
     uint32_t blocks_per_cu = 0;   // persistent grid: 0 = as many as fit
+
+    bool untouched() const
+    {
+        const MixedConfig d;
+        return tile == d.tile && ppl == d.ppl && sort_e == d.sort_e &&
+               blocks_per_cu == d.blocks_per_cu;
+    }
 };
 
 // A device buffer of gk_filter_host and its capacity in elements.
@@ -88,9 +95,7 @@ struct gk_ctx {
     uint64_t server_part_pairs = 1u << 17;    // GK_OPT_SERVER_PART_PAIRS
     uint64_t server_tick_pairs = 1u << 20;    // GK_OPT_SERVER_TICK_PAIRS
     uint32_t server_copy_streams = 4;         // GK_OPT_SERVER_COPY_STREAMS
-    uint32_t *d_mixed_counters = nullptr;     // [tile counter, residual count]
-    uint32_t *d_resid = nullptr;              // residual pair list
-    uint64_t resid_cap = 0;
+    uint32_t *d_tile_counter = nullptr;
     hipStream_t capture_stream = nullptr;
     hipGraphExec_t graph_exec = nullptr;
     std::vector<uint8_t> graph_key;           // shape and tuning of graph_exec
@@ -178,21 +183,16 @@ inline int gk_detail_fail(gk_ctx *ctx, int code, const std::string &msg)
 
 namespace gkd {
 
-// Mixed-batch launch sequence: reset, persistent kernel, residual pass and
-// (if a.accept_bits) the accept-bit pass, one set per 2^30 pairs.
+// Mixed-batch filter of one batch, direct form: one launch per 2^30 pairs.
 hipError_t launch_mixed(const FilterArgs &a, const MixedArgs &x, uint32_t wmax, uint32_t layout,
                         hipStream_t s);
+// Workgroups of the table form that fit one compute unit.
 hipError_t mixed_blocks_per_cu(uint32_t wmax, uint32_t layout, uint32_t tile, uint32_t ppl,
                                int *out);
-// Table launch sequence (reset, persistent kernel, residual pass) for the
-// table at x.table; the tile count is read from the table on the device, so
-// the sequence can be captured once and replayed with new table contents.
+// Table form (reset, persistent kernel) for the table at x.table; the tile
+// count is read from the table on the device, so the sequence can be captured
+// once and replayed with new table contents.
 hipError_t launch_mixed_table(const MixedArgs &x, uint32_t wmax, uint32_t layout, hipStream_t s);
-// Accept bits of n accept codes (bit j of word t: pair 64t + j is ACCEPT or
-// UNDEFINED).
-hipError_t launch_accept_bits(const uint8_t *accept, uint64_t n, unsigned long long *bits,
-                              hipStream_t s);
-size_t mixed_lds_size(uint32_t tile);
 
 // Launch the filter that encodes its own reads (pair i uses read i, read i
 // is ascii[read_off[i], read_off[i+1])), `words` 32-base words per mask.

@@ -1,23 +1,27 @@
-// Mixed-batch GateKeeper-GPU filter for gfx950: one persistent launch over a
-// batch whose pairs differ in read length and threshold.
+// Mixed-batch GateKeeper-GPU filter for gfx950: one launch over a batch whose
+// pairs differ in read length and threshold.
 //
 // The paper fixes the read length and e at compile time (Sec. 3.1, 3.2) and
-// so runs one kernel per (length, e) group.  Here one persistent grid takes
-// the whole batch:
-//   - each workgroup repeatedly claims a tile of T consecutive pairs from a
-//     device counter;
-//   - it classifies the tile's pairs (invalid and undefined pairs are written
-//     at once, pairs with more than 31 shifts go to a residual list) and
+// so runs one kernel per (length, e) group.  Here workgroups take the batch in
+// tiles of T consecutive pairs:
+//   - a workgroup classifies the tile's pairs (invalid and undefined pairs are
+//     done at once, pairs with more than 31 shifts are set apart) and
 //     counting-sorts the rest in LDS by (words per mask W, k_max), so that a
 //     64-lane chunk holds one W and nearly equal e;
 //   - its waves take chunks from an LDS counter and run the register-only
 //     fast path of gk_pair.h for the chunk's W (a wave-uniform switch), one
 //     or two pairs per lane (two: both pairs' loads in flight before either
 //     is computed; only for up to 10 words per mask, where the registers for
-//     it fit); results go back to the pairs' own slots.
-// Residual pairs are filtered afterwards by the general path, and the accept
-// bits (if wanted) by a pass over the accept codes.  The host captures the
-// four launches in one hipGraph.
+//     it fit); a pair's entry (read, position, length, e) stays in LDS from
+//     the classification on, and its result takes the entry's place until the
+//     tile is written back in slot order (results land in sorted order, so
+//     writing them directly would scatter partial-line writes).
+// Pairs with more than 31 shifts are a tile's last chunks, on the general path.
+// Two forms:
+//   direct      one batch, one workgroup per tile, accept bits with the
+//               results: one launch, no scratch;
+//   table       resident workgroups claim tiles of a table of batches from a
+//               device counter, so that one captured graph serves any batches.
 #include "gk_pair.h"
 
 namespace gkd {
@@ -25,80 +29,97 @@ namespace gkd {
 namespace {
 
 constexpr uint32_t NBINS = 16 * 32;       // W in 1..16, k_max in 0..31
-constexpr uint32_t KEY_DONE = 0xFFFFu;
+constexpr uint32_t FAR = 16;              // chunk class of the pairs with more shifts
 
 struct MixedLds {
-    uint32_t hist[NBINS];
-    uint32_t wstart[17];
+    uint32_t hist[NBINS + 1];             // bin NBINS: class FAR
+    uint32_t wstart[18];
     uint32_t tile;
     uint32_t n_chunks;
     uint32_t next_chunk;
+    uint32_t pad_[2];
 };
 
-// Dynamic LDS after MixedLds: keys[T] u16, sorted[T] u16, chunk_start[C] u32,
-// chunk_info[C] u32 with C = T/64 + 16, then the tile's results out_est[T] u16
-// and out_acc[T] u8, written back to HBM in slot order once the tile is done
-// (results land in sorted order, so writing them directly would scatter
-// partial-line writes).
-__host__ __device__ inline uint32_t mixed_chunk_cap(uint32_t tile) { return tile / 64 + 16; }
+// Dynamic LDS after MixedLds: the tile's pair entries pos[T], read[T],
+// entry[T] u32, chunk_start[C] u32, chunk_info[C] u32 with C = T/64 + 17,
+// sorted[T] u16 (first the pairs' sort keys, then the slots in sorted order).
+__host__ __device__ inline uint32_t mixed_chunk_cap(uint32_t tile) { return tile / 64 + 17; }
 
 __host__ inline size_t mixed_lds_bytes(uint32_t tile)
 {
-    return sizeof(MixedLds) + 2u * tile * sizeof(uint16_t) + 2u * mixed_chunk_cap(tile) * 4u +
-           3u * tile;
+    return sizeof(MixedLds) + 12u * tile + 8u * mixed_chunk_cap(tile) + 2u * tile;
 }
 
-struct TileOut {
-    uint8_t *acc;
-    uint16_t *est;
+// The tile's pairs: entry[slot] is e | length << 8 until the pair is done, then
+// its result code | estimate << 16.
+struct TilePairs {
+    uint32_t *pos, *read, *entry;
 };
 
-template <int W, int L, bool VAR>
-__device__ __forceinline__ void run_chunk_pair(const FilterArgs &a, const TileOut &o,
-                                               uint32_t base, uint32_t slot)
+__device__ __forceinline__ void tile_done(const TilePairs &t, uint32_t slot, uint32_t res,
+                                          uint32_t est)
 {
-    const PairIdx p = load_idx(a, base + slot);
+    t.entry[slot] = res | (est << 16);
+}
+
+// Loads of a classified pair (its length is known, its read holds no unknown
+// base).
+template <int W>
+__device__ __forceinline__ PairIdx load_slot(const FilterArgs &a, const TilePairs &t,
+                                             uint32_t slot, PairData<W> &d)
+{
+    PairIdx p;
+    const uint32_t en = t.entry[slot];
+    p.r = t.read[slot];
+    p.pos = t.pos[slot];
+    p.e = en & 0xFFu;
+    load_words<W>(a, p.r, d);
+    load_window<W>(a, p.pos, d);
+    load_unknown_lines<W>(a, p.pos, d);
+    d.m = en >> 8;
+    d.has_n = 0u;
+    return p;
+}
+
+template <int W, int L, bool GENERAL, bool VAR>
+__device__ __forceinline__ void run_chunk_pair(const FilterArgs &a, const TilePairs &t,
+                                               uint32_t slot)
+{
     PairData<W> d;
-    load_data<W>(a, p, d);
+    const PairIdx p = load_slot<W>(a, t, slot, d);
     uint32_t est;
-    const uint32_t res = compute_pair<W, L, false, VAR>(a, p, d, est);
-    o.acc[slot] = (uint8_t)res;
-    o.est[slot] = (uint16_t)est;
+    const uint32_t res = compute_pair<W, L, GENERAL, VAR>(a, p, d, est);
+    tile_done(t, slot, res, est);
 }
 
 template <int W, int L, bool VAR>
-__device__ __forceinline__ void run_chunk_pair2(const FilterArgs &a, const TileOut &o,
-                                                uint32_t base, uint32_t s0, bool has1,
-                                                uint32_t s1)
+__device__ __forceinline__ void run_chunk_pair2(const FilterArgs &a, const TilePairs &t,
+                                                uint32_t s0, bool has1, uint32_t s1)
 {
     // both pairs' loads in flight before either is computed
-    const PairIdx p0 = load_idx(a, base + s0);
-    const PairIdx p1 = load_idx(a, base + (has1 ? s1 : s0));
     PairData<W> d0, d1;
-    load_data<W>(a, p0, d0);
-    load_data<W>(a, p1, d1);
+    const PairIdx p0 = load_slot<W>(a, t, s0, d0);
+    const PairIdx p1 = load_slot<W>(a, t, has1 ? s1 : s0, d1);
     uint32_t est;
     uint32_t res = compute_pair<W, L, false, VAR>(a, p0, d0, est);
-    o.acc[s0] = (uint8_t)res;
-    o.est[s0] = (uint16_t)est;
+    tile_done(t, s0, res, est);
     if (has1) {
         res = compute_pair<W, L, false, VAR>(a, p1, d1, est);
-        o.acc[s1] = (uint8_t)res;
-        o.est[s1] = (uint16_t)est;
+        tile_done(t, s1, res, est);
     }
 }
 
 template <int WMAX, int L, int PPL, bool VAR>
-__device__ __forceinline__ void run_chunk(const FilterArgs &a, const TileOut &o, uint32_t base,
-                                          uint32_t w, uint32_t s0, bool has1, uint32_t s1)
+__device__ __forceinline__ void run_chunk(const FilterArgs &a, const TilePairs &t, uint32_t w,
+                                          uint32_t s0, bool has1, uint32_t s1)
 {
 #define GK_CASE(N)                                                                 \
     case N:                                                                        \
         if (N <= WMAX) {                                                           \
             if (PPL == 2)                                                          \
-                run_chunk_pair2<(N <= WMAX ? N : 1), L, VAR>(a, o, base, s0, has1, s1); \
+                run_chunk_pair2<(N <= WMAX ? N : 1), L, VAR>(a, t, s0, has1, s1);  \
             else                                                                   \
-                run_chunk_pair<(N <= WMAX ? N : 1), L, VAR>(a, o, base, s0);       \
+                run_chunk_pair<(N <= WMAX ? N : 1), L, false, VAR>(a, t, s0);      \
         }                                                                          \
         break;
     switch (w) {
@@ -127,69 +148,102 @@ __device__ __forceinline__ uint32_t table_batch(const BatchTable *t, uint32_t ti
     return lo;
 }
 
-template <int WMAX, int L, int PPL, bool VAR = false>
-__global__ __launch_bounds__(256) void k_mixed(FilterArgs a0, MixedArgs x)
+// Arguments of batch b (uniform), by scalar loads: nothing writes the table
+// while a launch reads it.
+__device__ __forceinline__ FilterArgs table_args(const BatchTable *t, uint32_t b)
+{
+    typedef const __attribute__((address_space(4))) uint32_t *constant_words;
+    static_assert(sizeof(FilterArgs) % 4 == 0, "copied as words");
+    const constant_words src = (constant_words)(uintptr_t)&t->args[b];
+    uint32_t w[sizeof(FilterArgs) / 4];
+#pragma unroll
+    for (uint32_t k = 0; k < sizeof(FilterArgs) / 4; ++k)
+        w[k] = src[k];
+    FilterArgs a;
+    __builtin_memcpy(&a, w, sizeof a);
+    return a;
+}
+
+template <int WMAX, int L, int PPL, bool VAR = false, bool DIRECT = false>
+__global__ __launch_bounds__(256)
+__attribute__((amdgpu_waves_per_eu(WMAX <= 10 && PPL == 1 && !VAR ? 4 : 1)))
+void k_mixed(FilterArgs a0, MixedArgs x)
 {
     extern __shared__ uint32_t lds_raw[];
     MixedLds &s = *reinterpret_cast<MixedLds *>(lds_raw);
-    uint16_t *keys = reinterpret_cast<uint16_t *>(lds_raw + sizeof(MixedLds) / 4);
-    uint16_t *sorted = keys + x.tile;
-    uint32_t *chunk_start = reinterpret_cast<uint32_t *>(sorted + x.tile);
+    TilePairs t;
+    t.pos = lds_raw + sizeof(MixedLds) / 4;
+    t.read = t.pos + x.tile;
+    t.entry = t.read + x.tile;
+    uint32_t *chunk_start = t.entry + x.tile;
     uint32_t *chunk_info = chunk_start + mixed_chunk_cap(x.tile);
-    TileOut out;
-    out.est = reinterpret_cast<uint16_t *>(chunk_info + mixed_chunk_cap(x.tile));
-    out.acc = reinterpret_cast<uint8_t *>(out.est + x.tile);
-
-    const uint32_t tid = threadIdx.x;
-    const uint32_t lane = tid & 63u;
-    const uint32_t n_tiles = x.table ? x.table->prefix[x.table->n_batches] : x.n_tiles;
+    uint16_t *sorted = reinterpret_cast<uint16_t *>(chunk_info + mixed_chunk_cap(x.tile));
 
     while (true) {
-        if (tid == 0)
+        // (not known to be the same in the next tile's round, so that nothing
+        // derived from it is held in registers across the chunks)
+        uint32_t tid = threadIdx.x;
+        if (!DIRECT)
+            asm volatile("" : "+v"(tid));
+        const uint32_t lane = tid & 63u;
+        if (!DIRECT && tid == 0)
             s.tile = atomicAdd(x.tile_counter, 1u);
-        for (uint32_t b = tid; b < NBINS; b += 256)
+        for (uint32_t b = tid; b <= NBINS; b += 256)
             s.hist[b] = 0;
         __syncthreads();
-        const uint32_t tile = s.tile;
-        if (tile >= n_tiles)
-            break;
-        // Residual entries are launch-wide ids tile * T + slot.
-        const uint32_t gbase = tile * x.tile;
         FilterArgs a = a0;
-        uint32_t base = gbase;
-        if (x.table) {
-            const uint32_t b = table_batch(x.table, tile);
-            a = x.table->args[b];
-            base = (tile - x.table->prefix[b]) * x.tile;
+        uint32_t base = blockIdx.x * x.tile, batch = 0;
+        if constexpr (!DIRECT) {
+            // uniform, so that the batch's arguments come into scalar registers
+            const uint32_t tile = __builtin_amdgcn_readfirstlane(s.tile);
+            if (tile >= x.table->prefix[x.table->n_batches])
+                break;
+            batch = __builtin_amdgcn_readfirstlane(table_batch(x.table, tile));
+            a = table_args(x.table, batch);
+            base = (tile - x.table->prefix[batch]) * x.tile;
         }
         const uint32_t n = (uint32_t)a.n_pairs;
 
-        // 1. classify
-        for (uint32_t j = tid; j < x.tile; j += 256) {
-            const uint32_t i = base + j;
-            uint32_t key = KEY_DONE;
-            if (i < n) {
-                const PairIdx p = load_idx(a, i);
-                const uint32_t m = p.r < a.n_reads ? (uint32_t)a.read_len[p.r] : 0u;
-                if (m == 0u || m > a.max_read_len) {
-                    out.acc[j] = GK_INVALID;
-                    out.est[j] = GK_EST_NONE;
-                } else if ((uint64_t)p.pos + m > a.ref_len ||
-                           (a.read_has_n && a.read_has_n[p.r])) {
-                    out.acc[j] = GK_UNDEFINED;
-                    out.est[j] = GK_EST_NONE;
-                } else {
-                    const uint32_t kmax = p.e < m - 1u ? p.e : m - 1u;
-                    const uint32_t w = (m + 31u) / 32u;
-                    if (kmax > 31u || w > (uint32_t)WMAX) {
-                        x.resid_list[atomicAdd(x.resid_count, 1u)] = gbase + j;
-                    } else {
-                        key = (w - 1u) * 32u + (x.sort_e ? kmax : 0u);
-                        atomicAdd(&s.hist[key], 1u);
-                    }
-                }
+        // 1. classify, four pairs' loads in flight per lane
+        for (uint32_t j0 = tid; j0 < x.tile; j0 += 1024) {
+            PairIdx p[4];
+            uint32_t m[4], un[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const uint32_t i = base + j0 + 256u * q;
+                p[q] = load_idx(a, i < n ? i : n - 1u);
             }
-            keys[j] = (uint16_t)key;
+            const uint8_t *flag = a.read_has_n ? a.read_has_n
+                                               : reinterpret_cast<const uint8_t *>(a.read_len);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const uint32_t r = p[q].r < a.n_reads ? p[q].r : 0u;
+                m[q] = a.read_len[r];
+                un[q] = flag[r];
+            }
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const uint32_t j = j0 + 256u * q;
+                if (j >= x.tile)
+                    break;
+                m[q] = p[q].r < a.n_reads ? m[q] : 0u;
+                uint32_t en = GK_INVALID | (GK_EST_NONE << 16), key = NBINS + 1;
+                if (base + j >= n || m[q] == 0u || m[q] > a.max_read_len) {
+                } else if ((uint64_t)p[q].pos + m[q] > a.ref_len || (a.read_has_n && un[q])) {
+                    en = GK_UNDEFINED | (GK_EST_NONE << 16);
+                } else {
+                    const uint32_t kmax = p[q].e < m[q] - 1u ? p[q].e : m[q] - 1u;
+                    const uint32_t w = (m[q] + 31u) / 32u;
+                    en = p[q].e | (m[q] << 8);
+                    key = kmax <= 31u ? (w - 1u) * 32u + (x.sort_e ? kmax : 0u) : NBINS;
+                }
+                t.pos[j] = p[q].pos;
+                t.read[j] = p[q].r;
+                t.entry[j] = en;
+                if (key <= NBINS)
+                    atomicAdd(&s.hist[key], 1u);
+                sorted[j] = (uint16_t)key;         // until step 3
+            }
         }
         __syncthreads();
 
@@ -217,26 +271,35 @@ __global__ __launch_bounds__(256) void k_mixed(FilterArgs a0, MixedArgs x)
                 s.hist[b] = run;
                 run += local[q];
             }
-            if (tid == 63)
-                s.wstart[16] = run;
+            if (tid == 63) {
+                s.wstart[FAR] = run;
+                s.wstart[FAR + 1] = run + s.hist[NBINS];
+                s.hist[NBINS] = run;
+            }
+        }
+        // keys to registers: the sorted slots take their place
+        uint32_t key8[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            const uint32_t j = tid + 256u * q;
+            key8[q] = j < x.tile ? sorted[j] : NBINS + 1u;
         }
         __syncthreads();
 
         // 3. scatter slots into bin order
-        for (uint32_t j = tid; j < x.tile; j += 256) {
-            const uint32_t key = keys[j];
-            if (key != KEY_DONE)
-                sorted[atomicAdd(&s.hist[key], 1u)] = (uint16_t)j;
-        }
+#pragma unroll
+        for (int q = 0; q < 8; ++q)
+            if (key8[q] <= NBINS)
+                sorted[atomicAdd(&s.hist[key8[q]], 1u)] = (uint16_t)(tid + 256u * q);
 
         // 4. chunks: runs of one W, 64 * ppl pairs at most.  A W's pairs are
         //    in ascending k_max, so its one partial chunk is put first, on the
         //    pairs with the fewest shifts: its idle lanes then wait through
         //    the shortest loop.
         if (tid < 64) {
-            const uint32_t ch = 64u * PPL;
-            const uint32_t w0 = tid < 16 ? s.wstart[tid] : 0u;
-            const uint32_t cnt = tid < 16 ? s.wstart[tid + 1] - w0 : 0u;
+            const uint32_t ch = tid == FAR ? 64u : 64u * PPL;
+            const uint32_t w0 = tid <= FAR ? s.wstart[tid] : 0u;
+            const uint32_t cnt = tid <= FAR ? s.wstart[tid + 1] - w0 : 0u;
             const uint32_t nch = (cnt + ch - 1) / ch;
             const uint32_t lead = cnt % ch == 0u ? ch : cnt % ch;   // size of chunk 0
             uint32_t incl = nch;
@@ -265,86 +328,66 @@ __global__ __launch_bounds__(256) void k_mixed(FilterArgs a0, MixedArgs x)
             uint32_t c = 0;
             if (lane == 0)
                 c = atomicAdd(&s.next_chunk, 1u);
-            c = __shfl(c, 0, 64);
+            c = __builtin_amdgcn_readfirstlane(c);
             if (c >= n_chunks)
                 break;
             c = n_chunks - 1u - c;
-            const uint32_t start = chunk_start[c];
-            const uint32_t info = chunk_info[c];
+            const uint32_t start = __builtin_amdgcn_readfirstlane(chunk_start[c]);
+            const uint32_t info = __builtin_amdgcn_readfirstlane(chunk_info[c]);
             const uint32_t cnt = info & 0xFFFFu;
-            const uint32_t w = __builtin_amdgcn_readfirstlane(info >> 16);
+            const uint32_t w = info >> 16;
+            // The arguments anew for each chunk: what all 16 widths derive from
+            // them (row addresses above all) does not fit the scalar registers
+            // when the compiler computes it before the loop.
+            FilterArgs a = a0;
+            if constexpr (!DIRECT) {
+                asm volatile("" : "+s"(batch));
+                a = table_args(x.table, batch);
+            }
+            asm volatile("" : "+s"(a.pitch), "+s"(a.rows), "+s"(a.max_read_len));
             if (lane < cnt) {
                 const uint32_t s0 = sorted[start + lane];
-                const bool has1 = lane + 64u < cnt;
-                const uint32_t s1 = has1 ? sorted[start + lane + 64u] : s0;
-                run_chunk<WMAX, L, PPL, VAR>(a, out, base, w, s0, has1, s1);
+                if (w == FAR + 1u) {
+                    run_chunk_pair<WMAX, L, true, VAR>(a, t, s0);
+                } else {
+                    const bool has1 = lane + 64u < cnt;
+                    const uint32_t s1 = has1 ? sorted[start + lane + 64u] : s0;
+                    run_chunk<WMAX, L, PPL, VAR>(a, t, w, s0, has1, s1);
+                }
             }
         }
         __syncthreads();
 
-        // 6. write the tile's results back in slot order (residual pairs'
-        //    slots hold placeholders; the residual pass overwrites them later)
+        // 6. write the tile's results back in slot order
         const uint32_t live = n - base < x.tile ? n - base : x.tile;
-        for (uint32_t j = tid; j < live; j += 256) {
-            a.accept[base + j] = out.acc[j];
-            a.est[base + j] = out.est[j];
+        for (uint32_t j = tid; j < x.tile; j += 256) {
+            const uint32_t v = t.entry[j];
+            if (j < live) {
+                a.accept[base + j] = (uint8_t)v;
+                a.est[base + j] = (uint16_t)(v >> 16);
+            }
+            if (a.accept_bits) {
+                const uint32_t res = v & 0xFFu;
+                const unsigned long long bits =
+                    __ballot(j < live && (res == GK_ACCEPT || res == GK_UNDEFINED));
+                if (lane == 0u && j < live)
+                    a.accept_bits[(base + j) >> 6] = bits;
+            }
         }
+        if (DIRECT)
+            break;
         __syncthreads();
     }
 }
 
-template <int W, int L, bool VAR = false>
-__global__ __launch_bounds__(256) void k_residual(FilterArgs a0, const BatchTable *table,
-                                                  uint32_t tile_size, const uint32_t *list,
-                                                  const uint32_t *count)
+__global__ __launch_bounds__(64) void k_reset(uint32_t *tile_counter)
 {
-    const uint32_t total = *count;
-    for (uint32_t j = blockIdx.x * 256u + threadIdx.x; j < total; j += gridDim.x * 256u) {
-        uint32_t i = list[j];
-        FilterArgs a = a0;
-        if (table) {
-            const uint32_t tile = i / tile_size;
-            const uint32_t b = table_batch(table, tile);
-            a = table->args[b];
-            i -= table->prefix[b] * tile_size;
-        }
-        const PairIdx p = load_idx(a, i);
-        PairData<W> d;
-        load_data<W>(a, p, d);
-        uint32_t est;
-        const uint32_t res = compute_pair<W, L, true, VAR>(a, p, d, est);
-        a.accept[i] = (uint8_t)res;
-        a.est[i] = (uint16_t)est;
-    }
-}
-
-__global__ __launch_bounds__(256) void k_reset(uint32_t *tile_counter, uint32_t *resid_count)
-{
-    if (threadIdx.x == 0) {
+    if (threadIdx.x == 0)
         *tile_counter = 0;
-        *resid_count = 0;
-    }
-}
-
-// One thread per 64 pairs: bit j of word t = pair 64t+j is ACCEPT or UNDEFINED.
-__global__ __launch_bounds__(256) void k_accept_bits(const uint8_t *accept, uint64_t n,
-                                                     unsigned long long *bits)
-{
-    const uint64_t t = (uint64_t)blockIdx.x * 256u + threadIdx.x;
-    if (t * 64 >= n)
-        return;
-    unsigned long long word = 0;
-    const uint64_t first = t * 64;
-    const uint32_t cnt = (uint32_t)(n - first < 64 ? n - first : 64);
-    for (uint32_t j = 0; j < cnt; ++j) {
-        const uint32_t v = accept[first + j];
-        word |= (unsigned long long)(v == GK_ACCEPT || v == GK_UNDEFINED) << j;
-    }
-    bits[t] = word;
 }
 
 template <int WMAX, int L>
-hipError_t launch_mixed_wl(const FilterArgs &a, const MixedArgs &x0, hipStream_t s)
+hipError_t launch_mixed_wl(const FilterArgs &a, const MixedArgs &x, hipStream_t s)
 {
     const uint64_t CHUNK = 1ull << 30;
     for (uint64_t first = 0; first < a.n_pairs; first += CHUNK) {
@@ -358,49 +401,23 @@ hipError_t launch_mixed_wl(const FilterArgs &a, const MixedArgs &x0, hipStream_t
         c.e_pair = a.e_pair ? a.e_pair + first : nullptr;
         c.accept = a.accept + first;
         c.est = a.est + first;
-        c.accept_bits = nullptr;
-        MixedArgs x = x0;
-        x.n_tiles = (uint32_t)((n + x.tile - 1) / x.tile);
-        hipLaunchKernelGGL(k_reset, dim3(1), dim3(64), 0, s, x.tile_counter, x.resid_count);
-        hipError_t e = hipGetLastError();
+        c.accept_bits = a.accept_bits ? a.accept_bits + first / 64 : nullptr;
+        const dim3 grid((uint32_t)((n + x.tile - 1) / x.tile));
+        const size_t lds = mixed_lds_bytes(x.tile);
+        bool two = false;
+        if constexpr (WMAX <= 10)
+            two = x.ppl == 2 && a.flags == 0u;
+        if (a.flags != 0u) {
+            // Variant semantics: their own kernel, one pair per lane.
+            hipLaunchKernelGGL((k_mixed<WMAX, L, 1, true, true>), grid, dim3(256), lds, s, c, x);
+        } else if (!two) {
+            hipLaunchKernelGGL((k_mixed<WMAX, L, 1, false, true>), grid, dim3(256), lds, s, c, x);
+        } else if constexpr (WMAX <= 10) {
+            hipLaunchKernelGGL((k_mixed<WMAX, L, 2, false, true>), grid, dim3(256), lds, s, c, x);
+        }
+        const hipError_t e = hipGetLastError();
         if (e != hipSuccess)
             return e;
-        const uint32_t blocks = x.blocks < x.n_tiles ? x.blocks : x.n_tiles;
-        if (c.flags != 0u) {
-            // Variant semantics: their own kernels, one pair per lane.
-            hipLaunchKernelGGL((k_mixed<WMAX, L, 1, true>), dim3(blocks), dim3(256),
-                               mixed_lds_bytes(x.tile), s, c, x);
-            if ((e = hipGetLastError()) != hipSuccess)
-                return e;
-            hipLaunchKernelGGL((k_residual<WMAX, L, true>), dim3(x.resid_blocks), dim3(256), 0,
-                               s, c, (const BatchTable *)nullptr, x.tile,
-                               (const uint32_t *)x.resid_list, (const uint32_t *)x.resid_count);
-        } else if constexpr (WMAX <= 10) {
-            if (x.ppl == 2)
-                hipLaunchKernelGGL((k_mixed<WMAX, L, 2>), dim3(blocks), dim3(256),
-                                   mixed_lds_bytes(x.tile), s, c, x);
-            else
-                hipLaunchKernelGGL((k_mixed<WMAX, L, 1>), dim3(blocks), dim3(256),
-                                   mixed_lds_bytes(x.tile), s, c, x);
-        } else {
-            hipLaunchKernelGGL((k_mixed<WMAX, L, 1>), dim3(blocks), dim3(256),
-                               mixed_lds_bytes(x.tile), s, c, x);
-        }
-        if ((e = hipGetLastError()) != hipSuccess)
-            return e;
-        if (c.flags == 0u)
-            hipLaunchKernelGGL((k_residual<WMAX, L>), dim3(x.resid_blocks), dim3(256), 0, s, c,
-                               (const BatchTable *)nullptr, x.tile,
-                               (const uint32_t *)x.resid_list, (const uint32_t *)x.resid_count);
-        if ((e = hipGetLastError()) != hipSuccess)
-            return e;
-        if (a.accept_bits) {
-            const uint64_t words = (n + 63) / 64;
-            hipLaunchKernelGGL(k_accept_bits, dim3((uint32_t)((words + 255) / 256)), dim3(256), 0,
-                               s, (const uint8_t *)c.accept, n, a.accept_bits + first / 64);
-            if ((e = hipGetLastError()) != hipSuccess)
-                return e;
-        }
     }
     return hipSuccess;
 }
@@ -409,26 +426,19 @@ template <int WMAX, int L>
 hipError_t launch_table_wl(const MixedArgs &x, hipStream_t s)
 {
     FilterArgs none{};
-    hipLaunchKernelGGL(k_reset, dim3(1), dim3(64), 0, s, x.tile_counter, x.resid_count);
-    hipError_t e = hipGetLastError();
+    hipLaunchKernelGGL(k_reset, dim3(1), dim3(64), 0, s, x.tile_counter);
+    const hipError_t e = hipGetLastError();
     if (e != hipSuccess)
         return e;
     if constexpr (WMAX <= 10) {
-        if (x.ppl == 2)
+        if (x.ppl == 2) {
             hipLaunchKernelGGL((k_mixed<WMAX, L, 2>), dim3(x.blocks), dim3(256),
                                mixed_lds_bytes(x.tile), s, none, x);
-        else
-            hipLaunchKernelGGL((k_mixed<WMAX, L, 1>), dim3(x.blocks), dim3(256),
-                               mixed_lds_bytes(x.tile), s, none, x);
-    } else {
-        hipLaunchKernelGGL((k_mixed<WMAX, L, 1>), dim3(x.blocks), dim3(256),
-                           mixed_lds_bytes(x.tile), s, none, x);
+            return hipGetLastError();
+        }
     }
-    if ((e = hipGetLastError()) != hipSuccess)
-        return e;
-    hipLaunchKernelGGL((k_residual<WMAX, L>), dim3(x.resid_blocks), dim3(256), 0, s, none,
-                       x.table, x.tile, (const uint32_t *)x.resid_list,
-                       (const uint32_t *)x.resid_count);
+    hipLaunchKernelGGL((k_mixed<WMAX, L, 1>), dim3(x.blocks), dim3(256), mixed_lds_bytes(x.tile),
+                       s, none, x);
     return hipGetLastError();
 }
 
@@ -456,8 +466,6 @@ hipError_t occupancy_wl(uint32_t tile, uint32_t ppl, int *blocks_per_cu)
 
 }  // namespace
 
-size_t mixed_lds_size(uint32_t tile) { return mixed_lds_bytes(tile); }
-
 hipError_t mixed_blocks_per_cu(uint32_t wmax, uint32_t layout, uint32_t tile, uint32_t ppl,
                                int *out)
 {
@@ -483,17 +491,6 @@ hipError_t launch_mixed_table(const MixedArgs &x, uint32_t wmax, uint32_t layout
                   : launch_table_wl<10, GK_READS_SPLIT>(x, s);
     return il ? launch_table_wl<16, GK_READS_INTERLEAVED>(x, s)
               : launch_table_wl<16, GK_READS_SPLIT>(x, s);
-}
-
-hipError_t launch_accept_bits(const uint8_t *accept, uint64_t n, unsigned long long *bits,
-                              hipStream_t s)
-{
-    if (n == 0)
-        return hipSuccess;
-    const uint64_t words = (n + 63) / 64;
-    hipLaunchKernelGGL(k_accept_bits, dim3((uint32_t)((words + 255) / 256)), dim3(256), 0, s,
-                       accept, n, bits);
-    return hipGetLastError();
 }
 
 hipError_t launch_mixed(const FilterArgs &a, const MixedArgs &x, uint32_t wmax, uint32_t layout,

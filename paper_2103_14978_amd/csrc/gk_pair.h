@@ -511,14 +511,20 @@ __device__ __forceinline__ void load_unknown_lines(const FilterArgs &a, uint32_t
 // With no reads the host points reads and read_len at memory that may be
 // read (pitch 0), and pair_gate ignores what comes.
 template <int W>
-__device__ __forceinline__ void load_data(const FilterArgs &a, const PairIdx &p, PairData<W> &d)
+__device__ __forceinline__ void load_words(const FilterArgs &a, uint32_t r, PairData<W> &d)
 {
-    const uint32_t r = p.r < a.n_reads ? p.r : 0u;
 #pragma unroll
     for (int j = 0; j < 2 * W; ++j) {
         const uint32_t row = (uint32_t)j < a.rows ? (uint32_t)j : a.rows - 1u;
         d.words[j] = a.reads[(size_t)row * a.pitch + r];
     }
+}
+
+template <int W>
+__device__ __forceinline__ void load_data(const FilterArgs &a, const PairIdx &p, PairData<W> &d)
+{
+    const uint32_t r = p.r < a.n_reads ? p.r : 0u;
+    load_words<W>(a, r, d);
     const uint8_t *flag = a.read_has_n ? a.read_has_n
                                        : reinterpret_cast<const uint8_t *>(a.read_len);
     d.m = (uint32_t)a.read_len[r];

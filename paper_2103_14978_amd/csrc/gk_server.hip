@@ -12,8 +12,9 @@
 //              all; a request with pairs left goes to the back of the
 //              queue), fills a batch table in pinned memory and replays a
 //              captured graph on the compute stream (table copy -> reset ->
-//              persistent kernel -> residual pass); at most two ticks are in
-//              flight, the two table buffers alternate;
+//              persistent kernel, of the width that the tick's longest read
+//              needs); at most two ticks are in flight, the two table buffers
+//              alternate;
 //   completer  waits for ticks in order, copies each part's results back,
 //              and once a request's last part is back frees its arena range
 //              and slot and wakes its waiter.
@@ -166,11 +167,12 @@ struct gk_server {
     // tick resources, double-buffered
     gkd::BatchTable *h_table[2] = {nullptr, nullptr};
     gkd::BatchTable *d_table[2] = {nullptr, nullptr};
-    hipGraphExec_t graph[2] = {nullptr, nullptr};
+    // tick graphs by the widest read of a tick (4, 10 or 16 words per mask)
+    static constexpr int WIDTHS = 3;
+    hipGraphExec_t graph[WIDTHS][2] = {};
     hipEvent_t tick_done[2] = {nullptr, nullptr};
     bool buf_busy[2] = {false, false};
     uint32_t *d_counters = nullptr;
-    uint32_t *d_resid = nullptr;
     gkd::MixedArgs margs{};
     uint64_t part_pairs = 0, tick_pairs = 0;   // batched mode: part and tick bounds
     uint64_t ticks = 0, tick_req_max = 0, pairs_done = 0;
@@ -233,6 +235,11 @@ void place(gk_server *s, Req *q)
     p += align_up(r.n_pairs);
     q->d_est = (uint16_t *)p;
 }
+
+// Tick kernels come for masks of up to 4, 10 and 16 words; the wider, the
+// fewer waves fit a SIMD, so a tick takes the narrowest that holds its reads.
+constexpr uint32_t WIDTH_WORDS[gk_server::WIDTHS] = {4, 10, 16};
+int width_class(uint32_t words) { return words <= 4 ? 0 : words <= 10 ? 1 : 2; }
 
 // Arguments of pairs [first, first + n) of a request.  With no pair_read
 // (pair i uses read i) the read arrays are offset too: the transposed rows
@@ -495,9 +502,10 @@ void scheduler_main(gk_server *s)
         gkd::trace_push("gk_server tick");
         gkd::BatchTable *h = s->h_table[t.buf];
         h->n_batches = (uint32_t)t.parts.size();
-        uint32_t tiles = 0;
+        uint32_t tiles = 0, words = 1;
         for (size_t b = 0; b < t.parts.size(); ++b) {
             const Part &p = t.parts[b];
+            words = std::max(words, (p.q->max_len + 31) / 32);
             h->prefix[b] = tiles;
             h->args[b] = args_for(s, p.q, p.first, p.n);
             tiles += (uint32_t)((p.n + s->margs.tile - 1) / s->margs.tile);
@@ -509,7 +517,7 @@ void scheduler_main(gk_server *s)
                 e = hipStreamWaitEvent(s->s_compute, p.q->ready, 0);
         t.t_launch = now_us();
         if (e == hipSuccess)
-            e = hipGraphLaunch(s->graph[t.buf], s->s_compute);
+            e = hipGraphLaunch(s->graph[width_class(words)][t.buf], s->s_compute);
         if (e == hipSuccess)
             e = hipEventRecord(s->tick_done[t.buf], s->s_compute);
         gkd::trace_pop();
@@ -603,8 +611,9 @@ void destroy_server(gk_server *s)
         if (st)
             (void)hipStreamSynchronize(st);
     for (int k = 0; k < 2; ++k) {
-        if (s->graph[k])
-            (void)hipGraphExecDestroy(s->graph[k]);
+        for (int c = 0; c < gk_server::WIDTHS; ++c)
+            if (s->graph[c][k])
+                (void)hipGraphExecDestroy(s->graph[c][k]);
         if (s->tick_done[k])
             (void)hipEventDestroy(s->tick_done[k]);
         if (s->h_table[k])
@@ -621,8 +630,6 @@ void destroy_server(gk_server *s)
         (void)hipFree(s->d_arena);
     if (s->d_counters)
         (void)hipFree(s->d_counters);
-    if (s->d_resid)
-        (void)hipFree(s->d_resid);
     for (hipStream_t st : s->s_copy)
         if (st)
             (void)hipStreamDestroy(st);
@@ -671,35 +678,16 @@ int gk_server_start(gk_ctx *ctx, uint64_t device_budget_bytes, uint32_t max_slot
         if (e == hipSuccess)
             e = hipStreamCreateWithFlags(st, hipStreamNonBlocking);
     if (e == hipSuccess)
-        e = gk_dmalloc(&s->d_counters, 2 * sizeof(uint32_t));
-    // Every pair takes at least 11 arena bytes, which bounds a tick's pairs.
-    const uint64_t resid_cap = device_budget_bytes / 11 + 1;
-    if (e == hipSuccess)
-        e = gk_dmalloc(&s->d_resid, resid_cap * sizeof(uint32_t));
+        e = gk_dmalloc(&s->d_counters, sizeof(uint32_t));
     if (e == hipSuccess && mode == GK_SERVER_BATCHED) {
         // The tick's persistent launch takes the context's mixed-batch
         // tuning (GK_OPT_MIXED_*, as gk_tune_mixed left it) at start.
         const MixedConfig mc = ctx->mixed;
-        const uint32_t ppl = mc.ppl == 2 && s->wmax <= 10 ? 2u : 1u;
-        int per_cu = 0;
-        e = gkd::mixed_blocks_per_cu(s->wmax, GK_READS_SPLIT, mc.tile, ppl, &per_cu);
-        if (per_cu < 1)
-            per_cu = 1;
-        const uint32_t bpc = mc.blocks_per_cu && (int)mc.blocks_per_cu < per_cu
-                                 ? mc.blocks_per_cu
-                                 : (uint32_t)per_cu;
         s->part_pairs = ctx->server_part_pairs;
         s->tick_pairs = ctx->server_tick_pairs;
-        s->margs.table = nullptr;
         s->margs.tile_counter = s->d_counters;
-        s->margs.resid_count = s->d_counters + 1;
-        s->margs.resid_list = s->d_resid;
-        s->margs.n_tiles = 0;
-        s->margs.tile = mc.tile;
-        s->margs.ppl = ppl;
+        s->margs.tile = gkd::mixed_tile(mc.tile);
         s->margs.sort_e = mc.sort_e;
-        s->margs.blocks = bpc * (uint32_t)ctx->cu_count;
-        s->margs.resid_blocks = 2u * (uint32_t)ctx->cu_count;
         hipStream_t cap = nullptr;
         if (e == hipSuccess)
             e = hipStreamCreateWithFlags(&cap, hipStreamNonBlocking);
@@ -712,24 +700,37 @@ int gk_server_start(gk_ctx *ctx, uint64_t device_budget_bytes, uint32_t max_slot
             if (e != hipSuccess)
                 break;
             std::memset(s->h_table[k], 0, sizeof(gkd::BatchTable));
-            // Tick graph: table copy, reset, persistent kernel, residual pass.
-            gkd::MixedArgs x = s->margs;
-            x.table = s->d_table[k];
-            hipGraph_t g = nullptr;
-            e = hipStreamBeginCapture(cap, hipStreamCaptureModeRelaxed);
-            if (e != hipSuccess)
-                break;
-            hipError_t le = hipMemcpyAsync(s->d_table[k], s->h_table[k], sizeof(gkd::BatchTable),
-                                           hipMemcpyHostToDevice, cap);
-            if (le == hipSuccess)
-                le = gkd::launch_mixed_table(x, s->wmax, GK_READS_SPLIT, cap);
-            e = hipStreamEndCapture(cap, &g);
-            if (le != hipSuccess)
-                e = le;
-            if (e == hipSuccess)
-                e = hipGraphInstantiate(&s->graph[k], g, nullptr, nullptr, 0);
-            if (g)
-                (void)hipGraphDestroy(g);
+            // Tick graphs: table copy, reset, persistent kernel.
+            for (int c = 0; c <= width_class(s->wmax) && e == hipSuccess; ++c) {
+                const uint32_t width = std::min(WIDTH_WORDS[c], s->wmax);
+                gkd::MixedArgs x = s->margs;
+                x.table = s->d_table[k];
+                x.ppl = mc.ppl == 2 && width <= 10 ? 2u : 1u;
+                int per_cu = 0;
+                e = gkd::mixed_blocks_per_cu(width, GK_READS_SPLIT, x.tile, x.ppl, &per_cu);
+                per_cu = std::max(per_cu, 1);
+                const uint32_t bpc = mc.blocks_per_cu && (int)mc.blocks_per_cu < per_cu
+                                         ? mc.blocks_per_cu
+                                         : (uint32_t)per_cu;
+                x.blocks = bpc * (uint32_t)ctx->cu_count;
+                hipGraph_t g = nullptr;
+                if (e == hipSuccess)
+                    e = hipStreamBeginCapture(cap, hipStreamCaptureModeRelaxed);
+                if (e != hipSuccess)
+                    break;
+                hipError_t le =
+                    hipMemcpyAsync(s->d_table[k], s->h_table[k], sizeof(gkd::BatchTable),
+                                   hipMemcpyHostToDevice, cap);
+                if (le == hipSuccess)
+                    le = gkd::launch_mixed_table(x, width, GK_READS_SPLIT, cap);
+                e = hipStreamEndCapture(cap, &g);
+                if (le != hipSuccess)
+                    e = le;
+                if (e == hipSuccess)
+                    e = hipGraphInstantiate(&s->graph[c][k], g, nullptr, nullptr, 0);
+                if (g)
+                    (void)hipGraphDestroy(g);
+            }
         }
         if (cap)
             (void)hipStreamDestroy(cap);
