@@ -306,8 +306,6 @@ void gk_destroy(gk_ctx *ctx)
             (void)hipFree(ctx->d_verify_list);
         if (ctx->d_verify_count)
             (void)hipFree(ctx->d_verify_count);
-        if (ctx->d_reads_rm)
-            (void)hipFree(ctx->d_reads_rm);
     }
     delete ctx;
 }
@@ -755,57 +753,38 @@ int gk_verify(gk_ctx *ctx, const gk_batch *b, const uint8_t *accept, uint16_t *d
     DeviceGuard g(ctx->device);
     if (!g.ok)
         return fail(ctx, GK_EDEVICE, "gk_verify: hipSetDevice failed");
-    // The pair list (one word per pair of a chunk of up to 2^30), one word
-    // per 4096 of those pairs for the listing's per-workgroup counts, the
-    // list of pairs the paired verify kernel leaves to the one-pair kernel,
-    // and the key counts and cursors of the listing by length and e.
-    const uint64_t need = std::min<uint64_t>(b->n_pairs, 1ull << 30);
-    if (need > ctx->verify_cap) {
-        if (ctx->d_verify_list)
-            (void)hipFree(ctx->d_verify_list);
-        ctx->d_verify_list = nullptr;
-        ctx->verify_cap = 0;
-        hipError_t e = gk_dmalloc(&ctx->d_verify_list,
-                                 (2 * need + (need + 4095) / 4096 + gkd::VERIFY_BIN_WORDS) *
-                                     sizeof(uint32_t));
-        if (e != hipSuccess)
-            return hip_fail(ctx, e, "gk_verify: hipMalloc list");
-        ctx->verify_cap = need;
-    }
+    const uint32_t words = (b->max_read_len + 31) / 32;
+    const bool lists = gkd::verify_lists(b->e != nullptr, b->e_uniform, b->n_pairs);
+    gk_detail_log(ctx, "gk_verify: %llu pairs, %s, %s", (unsigned long long)b->n_pairs,
+                  accept ? "accepted ones" : "every one",
+                  lists ? "one list" : "listed by tile");
+    hipError_t e;
     if (!ctx->d_verify_count) {
-        hipError_t e = gk_dmalloc(&ctx->d_verify_count, 2 * sizeof(uint32_t));
+        e = gk_dmalloc(&ctx->d_verify_count, sizeof(uint32_t));
         if (e != hipSuccess)
             return hip_fail(ctx, e, "gk_verify: hipMalloc count");
     }
-    // With a read index per pair and a threshold per pair, the listing orders
-    // the pairs by (length, e), which scatters each read's candidates: the
-    // one-pair-per-lane kernel then takes the reads from a row-major copy
-    // (one run of loads per read instead of a line per transposed row).
-    uint32_t *rm = nullptr;
-    if (b->pair_read && b->e && b->n_reads > 0) {
-        const uint64_t rm_words = (uint64_t)b->n_reads * gkd::verify_rm_stride(a.rows);
-        if (rm_words > ctx->reads_rm_cap) {
-            if (ctx->d_reads_rm)
-                (void)hipFree(ctx->d_reads_rm);
-            ctx->d_reads_rm = nullptr;
-            ctx->reads_rm_cap = 0;
-            hipError_t e = gk_dmalloc(&ctx->d_reads_rm, rm_words * sizeof(uint32_t));
+    if (lists) {
+        // The pair list (one word per pair of a chunk of up to 2^30) and one
+        // word per 4096 of those pairs for the listing's counts.
+        const uint64_t need = std::min<uint64_t>(b->n_pairs, 1ull << 30);
+        if (need > ctx->verify_cap) {
+            if (ctx->d_verify_list)
+                (void)hipFree(ctx->d_verify_list);
+            ctx->d_verify_list = nullptr;
+            ctx->verify_cap = 0;
+            e = gk_dmalloc(&ctx->d_verify_list, (need + (need + 4095) / 4096) * sizeof(uint32_t));
             if (e != hipSuccess)
-                return hip_fail(ctx, e, "gk_verify: hipMalloc row-major reads");
-            ctx->reads_rm_cap = rm_words;
+                return hip_fail(ctx, e, "gk_verify: hipMalloc list");
+            ctx->verify_cap = need;
         }
-        rm = ctx->d_reads_rm;
+        const gkd::VerifyScratch x{ctx->d_verify_list, ctx->d_verify_list + ctx->verify_cap,
+                                   ctx->d_verify_count};
+        e = gkd::launch_verify_listed(a, accept, dist, words, b->read_layout, x, ctx->cu_count,
+                                      (hipStream_t)stream);
+    } else {
+        e = gkd::launch_verify(a, accept, dist, words, b->read_layout, (hipStream_t)stream);
     }
-    const uint32_t words = (b->max_read_len + 31) / 32;
-    gk_detail_log(ctx, "gk_verify: %llu pairs, %s, pairs listed by %s%s",
-                  (unsigned long long)b->n_pairs, accept ? "accepted ones" : "every one",
-                  b->e ? "(length, e)" : "length", rm ? ", reads from a row-major copy" : "");
-    uint32_t *groups = ctx->d_verify_list + ctx->verify_cap;
-    uint32_t *deferred = groups + (ctx->verify_cap + 4095) / 4096;
-    uint32_t *bins = deferred + ctx->verify_cap;
-    hipError_t e = gkd::launch_verify(a, accept, dist, ctx->d_verify_list, groups, deferred,
-                                      ctx->d_verify_count, bins, rm, words, b->read_layout,
-                                      ctx->cu_count, (hipStream_t)stream);
     if (e != hipSuccess)
         return hip_fail(ctx, e, "gk_verify: launch");
     return GK_OK;

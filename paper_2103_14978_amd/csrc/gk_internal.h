@@ -109,14 +109,10 @@ struct gk_ctx {
     bool table_used[TABLE_RING] = {};
     uint32_t table_next = 0;
     HostPipe host;                            // gk_filter_host
-    uint32_t *d_verify_list = nullptr;        // gk_verify: selected pairs (verify_cap
-                                              // words), per-workgroup counts, deferred
-                                              // pairs (verify_cap words)
-    // d_verify_count: [0] selected pairs, [1] deferred pairs
-    uint32_t *d_verify_count = nullptr;
+    uint32_t *d_verify_list = nullptr;        // gk_verify: listed pairs (verify_cap
+                                              // words), per-workgroup counts
+    uint32_t *d_verify_count = nullptr;       // listed pairs
     uint64_t verify_cap = 0;
-    uint32_t *d_reads_rm = nullptr;           // gk_verify: row-major copy of the reads
-    uint64_t reads_rm_cap = 0;                // (words)
 };
 
 // gk_tune_mixed's use of its cache (environment GK_AUTOTUNE=use|refresh|off):

@@ -3,27 +3,168 @@
 // read mapper's verification step computes for the pairs the filter passes
 // (Sec. 3.3, Sec. 3.5), capped at e + 1.
 //
-// One lane computes one pair with a bit-parallel edit distance restricted to
-// the 2e+1 diagonals |i - j| <= e of the dynamic-programming matrix (a path
-// leaving them costs more than e).  The band's vertical differences are kept
-// in one word of 2e+1 bits (32-bit for e <= 15, 64-bit for e <= 31); per text
-// column the band slides down one row and the column step of Myers' bit-vector
-// algorithm (in Hyyro's formulation) updates it.  Boundary choices:
-//   - rows above row 0 are virtual with D[i][j] = j - i, which keeps
-//     D[0][j] = j and satisfies the recurrence whatever they match, so the
-//     band slides from the first column on;
-//   - the cell above the band takes D[i][j-1] + 1 and the cell entering at
-//     the band's bottom takes D[i-1][j] + 1: both bound the true values from
-//     above, so every band value is an upper bound, and it is exact along any
-//     path of cost <= e;
-//   - rows below the read end never influence row m.
-// The diagonal cell D[j][j] is tracked through the band's diagonal zero-delta
-// bit, and D[m][m] is the result.
+// One lane computes one pair, by one of two algorithms:
+//
+// Furthest-reaching points on the diagonals of the dynamic-programming matrix
+// (Ukkonen; Myers' O(ND) algorithm), for e <= 7: F(d, k) is the number of read
+// bases consumed by the furthest path with at most d edits that ends on
+// diagonal k = window position - read position,
+//   F(d, k) = slide(max(F(d-1, k) + 1, F(d-1, k+1) + 1, F(d-1, k-1))),
+// where slide follows matches along the diagonal, and the distance is the
+// least d with F(d, 0) = m.  A path on diagonal k after d edits needs |k| more
+// to come back, so with a cap of e only |k| <= min(d, e - d) is computed: 18
+// points for e = 5, of about 25 instructions each, where a band column takes
+// 22 (16 with two pairs to a word) for each of the read's bases.  A slide
+// compares 32 bases at a time: the pair's bit-planes lie in LDS, one column
+// per lane, two neighbouring words of read and window give the 32 bases from
+// any position with funnel shifts, and the first mismatch is a find-first-bit.
+//
+// The banded bit-vector algorithm above that (banded_distance): one pass over
+// the window's bases whatever e is, in a 32-bit word up to e = 15 and a 64-bit
+// one up to 31.  Its points overtake it in number from e = 10 on (61), and with
+// LDS latency in each they do from e = 8 (100 bases, e = 10, 2^22 pairs: 106 us
+// against 98).
+//
+// Tile form (k_verify_tile): a workgroup takes a tile of T consecutive pairs,
+// lists the ones to verify in LDS, counting-sorted by (words of the read, e) so
+// that a wave's lanes load alike and run alike, and its waves take 64 of the
+// list at a time, the longest first.  Distances replace the pairs' entries in
+// LDS and go to memory in pair order.  One launch; listing the whole batch
+// first took four to six (2^22 pairs of 100 bases at e = 5: 76 -> 63 us, 1,000
+// pairs 22 -> 9; 2^20 pairs of mixed lengths and thresholds 113 -> 72, 1,000
+// pairs 98 -> 39).
 #include "gk_pair.h"
 #include "gk_verify.h"
 
 namespace gkd {
 namespace {
+
+constexpr uint32_t VBINS = 16 * 32;          // words 1..16, e 0..31
+constexpr uint32_t FURTHEST_MAX_E = 7;
+constexpr uint32_t NOT_LISTED = 0xFFFFu;     // = GK_EST_NONE
+
+struct VerifyLds {
+    uint32_t hist[VBINS];
+    uint32_t total;
+    uint32_t next;
+    uint32_t pad_[2];
+};
+
+// Plane words of one wave: column `lane`, word w at [w * 64 + lane], the read's
+// in the first words + 1 rows, the window's in the next.  (The last row of each
+// only fills the funnel at a read's end.)
+__host__ __device__ inline uint32_t wave_planes(uint32_t words) { return 2u * (words + 1u) * 64u; }
+
+size_t verify_lds_bytes(uint32_t words, uint32_t tile)
+{
+    return sizeof(VerifyLds) + 4u * wave_planes(words) * sizeof(uint2) + 2u * tile * 2u;
+}
+
+// A lane's column of its wave's planes: the read's words at read[w * 64], the
+// window's at text[w * 64].
+struct Column {
+    uint2 *read, *text;
+};
+
+__device__ __forceinline__ uint32_t wave_max(uint32_t v)
+{
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        const uint32_t u = __shfl_xor(v, o, 64);
+        v = u > v ? u : v;
+    }
+    return __builtin_amdgcn_readfirstlane(v);
+}
+
+// Bit b: read base i + b differs from window base j + b (both inside the planes).
+__device__ __forceinline__ uint32_t differ32(const Column &col, int i, int j)
+{
+    const uint2 *r = col.read + ((uint32_t)i >> 5) * 64u;
+    const uint2 *g = col.text + ((uint32_t)j >> 5) * 64u;
+    const uint2 r0 = r[0], r1 = r[64], g0 = g[0], g1 = g[64];
+    // the funnel takes the shift modulo 32
+    const uint32_t rh = funnel(r1.x, r0.x, (uint32_t)i), rl = funnel(r1.y, r0.y, (uint32_t)i);
+    const uint32_t gh = funnel(g1.x, g0.x, (uint32_t)j), gl = funnel(g1.y, g0.y, (uint32_t)j);
+    return (rh ^ gh) | (rl ^ gl);
+}
+
+__device__ __forceinline__ int first_of(uint32_t x) { return x ? __builtin_ctz(x) : 32; }
+
+// Matches from read base i on diagonal k, at most `left` (0 or more), after
+// the first n (the first 32 compared).
+__device__ __forceinline__ int slide_on(const Column &col, int i, int k, int left, int n)
+{
+    int t = n;
+    while (n == 32 && t < left) {
+        n = first_of(differ32(col, i + t, i + t + k));
+        t += n;
+    }
+    return t < left ? t : left;
+}
+
+__device__ __forceinline__ int slide(const Column &col, int i, int k, int left)
+{
+    const int at = left > 0 ? i : 0;         // (any place inside the planes will do)
+    return slide_on(col, i, k, left,
+                          first_of(differ32(col, at, left > 0 ? i + k : 0)));
+}
+
+// Diagonals k and -k, then outwards, of one more edit: F[q + K + 1] = F(d, q)
+// from F(d-1, .) in place, up = F(d-1, k-1), down = F(d-1, 1-k).  The two
+// slides' first 32 bases are compared with both pairs of loads in flight.
+template <int K, int k>
+__device__ __forceinline__ void outwards(const Column &col, int m, int reach, int (&F)[2 * K + 3],
+                                         int up, int down)
+{
+    if constexpr (k <= K) {
+        if (k <= reach) {
+            const int hp = F[K + 1 + k], op = F[K + 2 + k];
+            const int hn = F[K + 1 - k], on = F[K - k];
+            int ip = (hp > op ? hp : op) + 1;
+            ip = ip > up ? ip : up;
+            ip = ip < m - k ? ip : m - k;
+            int in = (hn > down ? hn : down) + 1;
+            in = in > on ? in : on;
+            in = in < m ? in : m;
+            const int lp = m - k - ip, ln = m - in;
+            const uint32_t xp = differ32(col, lp > 0 ? ip : 0, lp > 0 ? ip + k : 0);
+            const uint32_t xn = differ32(col, ln > 0 ? in : k, ln > 0 ? in - k : 0);
+            F[K + 1 + k] = ip + slide_on(col, ip, k, lp, first_of(xp));
+            F[K + 1 - k] = in + slide_on(col, in, -k, ln, first_of(xn));
+            outwards<K, k + 1>(col, m, reach, F, hp, hn);
+        }
+    }
+}
+
+// min(distance, e + 1) of the lane's pair by furthest-reaching points;
+// E >= every lane's e, E / 2 <= K.  Lanes without a pair pass m = 0.
+template <int K>
+__device__ __forceinline__ uint32_t furthest_distance(const Column &col, int m, uint32_t e,
+                                                      uint32_t E)
+{
+    int F[2 * K + 3];
+#pragma unroll
+    for (int q = 0; q < 2 * K + 3; ++q)
+        F[q] = -1000;
+    F[K + 1] = slide(col, 0, 0, m);
+    uint32_t dist = F[K + 1] >= m ? 0u : e + 1u;
+#pragma unroll 1
+    for (uint32_t d = 1; d <= E; ++d) {
+        if (__ballot(dist > e && d <= e) == 0ull)
+            break;
+        const int here = F[K + 1];
+        int i = (here > F[K + 2] ? here : F[K + 2]) + 1;
+        i = i > F[K] ? i : F[K];
+        i = i < m ? i : m;
+        F[K + 1] = i + slide(col, i, 0, m - i);
+        // (m opaque: m - k of every diagonal is not kept in a register)
+        asm volatile("" : "+v"(m));
+        outwards<K, 1>(col, m, (int)(d < E - d ? d : E - d), F, here, here);
+        if (dist > e && d <= e && F[K + 1] >= m)
+            dist = d;
+    }
+    return dist;
+}
 
 // A 64-bit band word kept as two 32-bit halves, so that chains of logic
 // operations on it map onto 3-input logic instructions per half (whole 64-bit
@@ -105,6 +246,298 @@ __device__ __forceinline__ T bits_from(uint32_t a, uint32_t b, uint32_t c, uint3
         return B64{lo, funnel(c, b, s)};
 }
 
+// min(distance, e + 1) of the lane's pair by the band of the 2E+1 diagonals
+// |i - j| <= E, E >= every lane's e (E <= 15 in 32 bits, E <= 31 in 64); one
+// pass over the window's bases, whatever the distance.  The vertical
+// differences of the band are one word of 2E+1 bits; per text column the band
+// slides down one row and the column step of Myers' bit-vector algorithm (in
+// Hyyro's formulation) updates it.  Boundary choices:
+//   - rows above row 0 are virtual with D[i][j] = j - i, which keeps
+//     D[0][j] = j and satisfies the recurrence whatever they match, so the
+//     band slides from the first column on;
+//   - the cell above the band takes D[i][j-1] + 1 and the cell entering at
+//     the band's bottom takes D[i-1][j] + 1: both bound the true values from
+//     above, so every band value is an upper bound, and it is exact along any
+//     path of cost <= E;
+//   - rows below the read end never influence row m.
+// The diagonal cell D[j][j] is tracked through the band's diagonal zero-delta
+// bit, and D[m][m] is the result.
+//
+// Read bases are taken from [32 zero bits | plane words 0..words-1 | zeros]:
+// for text column j = 32 blk + c + 1 the band starts at extended bit
+// 32 blk + c + 32 - E, which lies in extended word blk (read word blk - 1)
+// while c < E and in word blk + 1 (read word blk) from c = E on; the column
+// loop is split there so each part reads fixed words.
+template <typename T>
+__device__ __forceinline__ uint32_t banded_distance(const Column &col, uint32_t m, uint32_t e,
+                                                    uint32_t E, uint32_t words)
+{
+    const uint64_t top64 = 1ull << (2 * E);        // band row 2E: enters each column
+    const uint64_t keep64 = top64 - 1;             // band rows 0 .. 2E-1 after a slide
+    const uint64_t vn0 = (2ull << E) - 1;          // column 0: rows -E..0 step -1,
+    const uint64_t vp0 = (top64 | keep64) & ~vn0;  //           rows 1..E step +1
+    const T top = from64<T>(top64), keep = from64<T>(keep64);
+    T vp = from64<T>(((vp0 >> 1) & keep64) | top64);   // slid into column 1's band
+    T vn = from64<T>((vn0 >> 1) & keep64);
+    uint32_t flat = 0;                             // columns j where D[j][j] = D[j-1][j-1]
+    uint2 r0 = make_uint2(0u, 0u), r1 = col.read[0], r2 = col.read[64];
+#pragma unroll 1
+    for (uint32_t blk = 0; blk < words; ++blk) {
+        const uint2 r3 = blk + 2u <= words ? col.read[(blk + 2u) * 64u] : make_uint2(0u, 0u);
+        const uint2 text = col.text[blk * 64u];
+        const int cols = (int)m - (int)(32u * blk) < 32 ? (int)m - (int)(32u * blk) : 32;
+        const int split = (int)E < cols ? (int)E : cols;
+        for (int c = 0; c < split; ++c) {          // band starts in read word blk - 1
+            const uint32_t s = (uint32_t)c + 32u - E;
+            band_step<T>(bits_from<T>(r0.x, r1.x, r2.x, s), bits_from<T>(r0.y, r1.y, r2.y, s),
+                         broadcast<T>(__builtin_amdgcn_sbfe(text.x, c, 1)),
+                         broadcast<T>(__builtin_amdgcn_sbfe(text.y, c, 1)), top, keep, E, vp, vn,
+                         flat);
+        }
+        for (int c = (int)E; c < cols; ++c) {      // band starts in read word blk
+            const uint32_t s = (uint32_t)c - E;
+            band_step<T>(bits_from<T>(r1.x, r2.x, r3.x, s), bits_from<T>(r1.y, r2.y, r3.y, s),
+                         broadcast<T>(__builtin_amdgcn_sbfe(text.x, c, 1)),
+                         broadcast<T>(__builtin_amdgcn_sbfe(text.y, c, 1)), top, keep, E, vp, vn,
+                         flat);
+        }
+        r0 = r1;
+        r1 = r2;
+        r2 = r3;
+    }
+    const uint32_t score = m - flat;               // D[m][m]: each diagonal step is 0 or +1
+    return score < e + 1u ? score : e + 1u;
+}
+
+// A wave whose pairs share the length keeps the column loops' bounds scalar.
+template <typename T>
+__device__ __forceinline__ uint32_t banded(const Column &col, uint32_t m, bool have, uint32_t e,
+                                           uint32_t E, uint32_t words)
+{
+    const uint32_t m0 = wave_max(have ? m : 0u);
+    if (__ballot(have && m != m0) == 0ull)
+        return banded_distance<T>(col, m0, e, E, words);
+    return banded_distance<T>(col, m, e, E, words);
+}
+
+// Loads one pair and puts its planes into the lane's column.  Returns whether
+// the pair can be compared.
+template <int W, int L>
+__device__ __forceinline__ bool load_planes(const FilterArgs &a, const PairIdx &p, const Column &col)
+{
+    PairData<W> d;
+    load_data<W>(a, p, d);
+    uint32_t m;
+    const bool ok = pair_gate<W>(a, p, d, m) == PAIR_OK;
+    uint32_t gh[W], gl[W], rh[W], rl[W];
+    pair_planes<W, L>(p, d, m, gh, gl, rh, rl);
+#pragma unroll
+    for (int w = 0; w < W; ++w) {
+        col.read[w * 64] = make_uint2(rh[w], rl[w]);
+        col.text[w * 64] = make_uint2(gh[w], gl[w]);
+    }
+    col.read[W * 64] = make_uint2(0u, 0u);
+    col.text[W * 64] = make_uint2(0u, 0u);
+    return ok;
+}
+
+template <int WMAX, int L>
+__device__ __forceinline__ bool load_planes_w(const FilterArgs &a, const PairIdx &p, uint32_t w,
+                                              const Column &col)
+{
+#define GK_CASE(N)                                                                 \
+    case N:                                                                        \
+        if (N <= WMAX)                                                             \
+            return load_planes<(N <= WMAX ? N : 1), L>(a, p, col);           \
+        break;
+    switch (w) {
+        GK_CASE(1) GK_CASE(2) GK_CASE(3) GK_CASE(4) GK_CASE(5) GK_CASE(6) GK_CASE(7) GK_CASE(8)
+        GK_CASE(9) GK_CASE(10) GK_CASE(11) GK_CASE(12) GK_CASE(13) GK_CASE(14) GK_CASE(15)
+        GK_CASE(16)
+    default:
+        break;
+    }
+#undef GK_CASE
+    return false;
+}
+
+template <int WMAX, int L>
+__global__ __launch_bounds__(256) void k_verify_tile(FilterArgs a, const uint8_t *accept,
+                                                     uint16_t *dist, uint32_t tile,
+                                                     uint32_t words)
+{
+    extern __shared__ uint32_t lds_raw[];
+    VerifyLds &s = *reinterpret_cast<VerifyLds *>(lds_raw);
+    uint2 *planes = reinterpret_cast<uint2 *>(lds_raw + sizeof(VerifyLds) / 4);
+    uint16_t *entry = reinterpret_cast<uint16_t *>(planes + 4u * wave_planes(words));
+    uint16_t *list = entry + tile;
+    const uint32_t tid = threadIdx.x, lane = tid & 63u;
+    const uint32_t n = (uint32_t)a.n_pairs;
+    const uint32_t base = blockIdx.x * tile;
+
+    for (uint32_t b = tid; b < VBINS; b += 256)
+        s.hist[b] = 0;
+    __syncthreads();
+
+    // 1. list the pairs to verify: entry = length | e << 10, key = words, e
+    for (uint32_t j0 = tid; j0 < tile; j0 += 1024) {
+        uint32_t on[4], r[4], e[4], m[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const uint32_t i = base + j0 + 256u * q, c = i < n ? i : n - 1u;
+            on[q] = accept ? (accept[c] == GK_ACCEPT) : 1u;
+            r[q] = a.pair_read ? a.pair_read[c] : c;
+            e[q] = a.e_pair ? (uint32_t)a.e_pair[c] : a.e_uniform;
+            on[q] = on[q] && i < n && e[q] <= GK_VERIFY_MAX_E && r[q] < a.n_reads;
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            m[q] = a.read_len[on[q] ? r[q] : 0u];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const uint32_t j = j0 + 256u * q;
+            if (j >= tile)
+                break;
+            uint32_t en = NOT_LISTED, key = NOT_LISTED;
+            if (on[q] && m[q] != 0u && m[q] <= a.max_read_len) {
+                en = m[q] | (e[q] << 10);
+                key = ((m[q] + 31u) / 32u - 1u) * 32u + e[q];
+                atomicAdd(&s.hist[key], 1u);
+            }
+            entry[j] = (uint16_t)en;
+            list[j] = (uint16_t)key;               // until step 3
+        }
+    }
+    __syncthreads();
+
+    // 2. exclusive prefix over the bins
+    if (tid < 64) {
+        uint32_t local[8], sum = 0;
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            local[q] = s.hist[tid * 8 + q];
+            sum += local[q];
+        }
+        uint32_t run = sum;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const uint32_t v = __shfl_up(run, o, 64);
+            if (lane >= (uint32_t)o)
+                run += v;
+        }
+        if (tid == 63) {
+            s.total = run;
+            s.next = 0;
+        }
+        run -= sum;
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            s.hist[tid * 8 + q] = run;
+            run += local[q];
+        }
+    }
+    uint32_t key8[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+        const uint32_t j = tid + 256u * q;
+        key8[q] = j < tile ? list[j] : NOT_LISTED;
+    }
+    __syncthreads();
+
+    // 3. slots in key order
+#pragma unroll
+    for (int q = 0; q < 8; ++q)
+        if (key8[q] != NOT_LISTED)
+            list[atomicAdd(&s.hist[key8[q]], 1u)] = (uint16_t)(tid + 256u * q);
+    __syncthreads();
+
+    // 4. waves take 64 at a time from the end of the list
+    const uint32_t total = s.total;
+    Column col;
+    col.read = planes + (tid >> 6) * wave_planes(words) + lane;
+    col.text = col.read + (words + 1u) * 64u;
+    while (true) {
+        uint32_t c = 0;
+        if (lane == 0)
+            c = atomicAdd(&s.next, 64u);
+        c = __builtin_amdgcn_readfirstlane(c);
+        if (c >= total)
+            break;
+        const uint32_t at = c + lane;
+        const bool have = at < total;
+        const uint32_t slot = list[have ? total - 1u - at : total - 1u];
+        const uint32_t en = entry[slot];
+        const uint32_t e = have ? en >> 10 : 0u;
+        PairIdx p = load_idx(a, base + slot);
+        p.e = en >> 10;
+        FilterArgs ac = a;     // (nor the row addresses of every width)
+        asm volatile("" : "+s"(ac.pitch), "+s"(ac.rows), "+s"(ac.max_read_len));
+        const uint32_t w = wave_max(((en & 0x3FFu) + 31u) / 32u);
+        const uint32_t E = wave_max(e);
+        const bool ok = load_planes_w<WMAX, L>(ac, p, w, col);
+        const int m = ok && have ? (int)(en & 0x3FFu) : 0;
+        uint32_t d;
+        if (E <= FURTHEST_MAX_E)
+            d = furthest_distance<FURTHEST_MAX_E / 2>(col, m, e, E);
+        else if (E <= 15u)
+            d = banded<uint32_t>(col, (uint32_t)m, ok && have, e, E, w);
+        else
+            d = banded<B64>(col, (uint32_t)m, ok && have, e, E, w);
+        if (have)
+            entry[slot] = (uint16_t)(ok ? d : GK_EST_NONE);
+    }
+    __syncthreads();
+
+    // 5. distances in pair order
+    for (uint32_t j = tid; j < tile; j += 256)
+        if (base + j < n)
+            dist[base + j] = entry[j];
+}
+
+template <int WMAX, int L>
+hipError_t tile_wl(const FilterArgs &a, const uint8_t *accept, uint16_t *dist, uint32_t words,
+                     uint32_t tile, hipStream_t s)
+{
+    const uint64_t CHUNK = 1ull << 30;
+    for (uint64_t first = 0; first < a.n_pairs; first += CHUNK) {
+        FilterArgs c = a;
+        const uint64_t n = a.n_pairs - first < CHUNK ? a.n_pairs - first : CHUNK;
+        c.n_pairs = n;
+        c.pair_read = a.pair_read ? a.pair_read + first : nullptr;
+        if (!a.pair_read && first > 0)
+            c.n_reads = 0;   // pair i uses read i < n_reads < 2^30: none here
+        c.cand_pos = a.cand_pos + first;
+        c.e_pair = a.e_pair ? a.e_pair + first : nullptr;
+        hipLaunchKernelGGL((k_verify_tile<WMAX, L>), dim3((uint32_t)((n + tile - 1) / tile)), dim3(256),
+                           verify_lds_bytes(words, tile), s, c, accept ? accept + first : nullptr,
+                           dist + first, tile, words);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess)
+            return e;
+    }
+    return hipSuccess;
+}
+
+template <int L>
+hipError_t tile_l(const FilterArgs &a, const uint8_t *accept, uint16_t *dist, uint32_t words,
+                  uint32_t tile, hipStream_t s)
+{
+    if (words <= 4)
+        return tile_wl<4, L>(a, accept, dist, words, tile, s);
+    if (words <= 8)
+        return tile_wl<8, L>(a, accept, dist, words, tile, s);
+    if (words <= 10)
+        return tile_wl<10, L>(a, accept, dist, words, tile, s);
+    return tile_wl<16, L>(a, accept, dist, words, tile, s);
+}
+
+// ---- one list over the whole batch ---------------------------------------
+//
+// Large batches under one threshold of 8 and more: the band's column loop is
+// the whole cost, and it runs fastest with the planes in registers (no LDS
+// but the tile form's, whose columns leave 3 waves per SIMD at 8 words) and
+// full waves from one list.
+
 // Read bases are taken from [32 zero bits | plane words 0..W-1 | zeros]: for
 // text column j = 32 blk + c + 1 the band starts at extended bit
 // 32 blk + c + 32 - e, which lies in extended word blk (read word blk - 1)
@@ -151,152 +584,27 @@ __device__ __forceinline__ uint32_t band_distance(const uint32_t (&rh)[W], const
     return score < e + 1u ? score : e + 1u;
 }
 
-// Two pairs with the same length m and the same e <= 7 in one 32-bit word:
-// pair 0's band in bits 0..15, pair 1's in bits 16..31.  A band of 2e+1 <= 15
-// rows keeps (eq & vp) + vp below 2^(2e+2) <= 2^16, so no carry crosses into
-// the other pair's half; the shift right moves bit 16 into half 0's bit 15,
-// above its band, where the masks clear it.  Both pairs share every logic
-// instruction; only the gathers of their read bits and text bits are
-// separate (byte permutes put the two halves together).  Returns
-// dist0 | dist1 << 16.
-__device__ __forceinline__ uint32_t halves(uint32_t hi_src, uint32_t lo_src)
-{
-    return __builtin_amdgcn_perm(hi_src, lo_src, 0x05040100u);   // {lo_src[15:0], hi_src[15:0]}
-}
-
-// One column of both pairs: h0, l0 / h1, l1 are 32 read-plane bits from each
-// pair's band start; the text bits are bit c of each pair's window words.
-__device__ __forceinline__ void band_step2(uint32_t h0, uint32_t l0, uint32_t h1, uint32_t l1,
-                                           uint32_t t0h, uint32_t t0l, uint32_t t1h,
-                                           uint32_t t1l, int c, uint32_t top, uint32_t keep,
-                                           uint32_t e, uint32_t &vp, uint32_t &vn,
-                                           uint32_t &flat)
-{
-    const uint32_t bh = halves(h1, h0), bl = halves(l1, l0);
-    const uint32_t th = halves((uint32_t)__builtin_amdgcn_sbfe(t1h, c, 1),
-                               (uint32_t)__builtin_amdgcn_sbfe(t0h, c, 1));
-    const uint32_t tl = halves((uint32_t)__builtin_amdgcn_sbfe(t1l, c, 1),
-                               (uint32_t)__builtin_amdgcn_sbfe(t0l, c, 1));
-    const uint32_t eq = ~((bh ^ th) | (bl ^ tl));
-    flat += (band_column<uint32_t>(eq, top, keep, vp, vn) >> e) & 0x00010001u;
-}
-
-template <int W>
-__device__ __forceinline__ uint32_t band_distance2(
-    const uint32_t (&rh0)[W], const uint32_t (&rl0)[W], const uint32_t (&gh0)[W],
-    const uint32_t (&gl0)[W], const uint32_t (&rh1)[W], const uint32_t (&rl1)[W],
-    const uint32_t (&gh1)[W], const uint32_t (&gl1)[W], uint32_t m, uint32_t e)
-{
-    const uint32_t top1 = 1u << (2 * e), keep1 = top1 - 1u;
-    const uint32_t vn0 = (2u << e) - 1u, vp0 = (top1 | keep1) & ~vn0;
-    const uint32_t vps = ((vp0 >> 1) & keep1) | top1, vns = (vn0 >> 1) & keep1;
-    const uint32_t top = top1 | (top1 << 16), keep = keep1 | (keep1 << 16);
-    uint32_t vp = vps | (vps << 16), vn = vns | (vns << 16);
-    uint32_t flat = 0;                   // two 16-bit counters
-#pragma unroll
-    for (int blk = 0; blk < W; ++blk) {
-        const uint32_t a0 = blk >= 1 ? rh0[blk - 1] : 0u, b0 = blk >= 1 ? rl0[blk - 1] : 0u;
-        const uint32_t c0 = blk >= 1 ? rh1[blk - 1] : 0u, d0 = blk >= 1 ? rl1[blk - 1] : 0u;
-        const uint32_t a1 = rh0[blk], b1 = rl0[blk], c1 = rh1[blk], d1 = rl1[blk];
-        const uint32_t a2 = blk + 1 < W ? rh0[blk + 1] : 0u, b2 = blk + 1 < W ? rl0[blk + 1] : 0u;
-        const uint32_t c2 = blk + 1 < W ? rh1[blk + 1] : 0u, d2 = blk + 1 < W ? rl1[blk + 1] : 0u;
-        const int cols = (int)m - 32 * blk < 32 ? (int)m - 32 * blk : 32;
-        const int split = (int)e < cols ? (int)e : cols;
-        const uint32_t t0h = gh0[blk], t0l = gl0[blk], t1h = gh1[blk], t1l = gl1[blk];
-        for (int c = 0; c < split; ++c)          // band starts in read word blk - 1
-            band_step2(funnel(a1, a0, (uint32_t)c + 32u - e), funnel(b1, b0, (uint32_t)c + 32u - e),
-                       funnel(c1, c0, (uint32_t)c + 32u - e), funnel(d1, d0, (uint32_t)c + 32u - e),
-                       t0h, t0l, t1h, t1l, c, top, keep, e, vp, vn, flat);
-        for (int c = split; c < cols; ++c)       // band starts in read word blk
-            band_step2(funnel(a2, a1, (uint32_t)c - e), funnel(b2, b1, (uint32_t)c - e),
-                       funnel(c2, c1, (uint32_t)c - e), funnel(d2, d1, (uint32_t)c - e),
-                       t0h, t0l, t1h, t1l, c, top, keep, e, vp, vn, flat);
-    }
-    const uint32_t s0 = m - (flat & 0xFFFFu), s1 = m - (flat >> 16);
-    return (s0 < e + 1u ? s0 : e + 1u) | ((s1 < e + 1u ? s1 : e + 1u) << 16);
-}
-
-// Distance of one pair that passed the gate.  When every active lane has the
-// same threshold and length (always so for one read length and a uniform e),
-// the band's shifts and trip counts come from scalar registers.
+// Distance of one pair that passed the gate under the batch's one threshold.
+// When every active lane has the same length (always so for one read length)
+// the band's trip counts come from scalar registers.
 template <int W, int L>
 __device__ __forceinline__ uint32_t verify_pair(const PairIdx &p, const PairData<W> &d,
-                                                uint32_t m)
+                                                uint32_t m, uint32_t e)
 {
     uint32_t gh[W], gl[W], rh[W], rl[W];
     pair_planes<W, L>(p, d, m, gh, gl, rh, rl);
-    const uint32_t e0 = __builtin_amdgcn_readfirstlane(p.e);
     const uint32_t m0 = __builtin_amdgcn_readfirstlane(m);
-    if (__ballot(p.e != e0 || m != m0) == 0ull)
-        return e0 <= 15u ? band_distance<W, uint32_t>(rh, rl, gh, gl, m0, e0)
-                         : band_distance<W, B64>(rh, rl, gh, gl, m0, e0);
-    return p.e <= 15u ? band_distance<W, uint32_t>(rh, rl, gh, gl, m, p.e)
-                      : band_distance<W, B64>(rh, rl, gh, gl, m, p.e);
+    if (__ballot(m != m0) == 0ull)
+        return e <= 15u ? band_distance<W, uint32_t>(rh, rl, gh, gl, m0, e)
+                        : band_distance<W, B64>(rh, rl, gh, gl, m0, e);
+    return e <= 15u ? band_distance<W, uint32_t>(rh, rl, gh, gl, m, e)
+                    : band_distance<W, B64>(rh, rl, gh, gl, m, e);
 }
 
-// A pair's loads as load_data does them, but with the read's words taken
-// from a row-major copy of the reads (read r's rows at rm[r * rm_stride ..],
-// rm_stride a multiple of 4 words, zero past the rows): one read is one run
-// of 16-byte loads from one or two lines, instead of a line per row of the
-// transposed layout (whose rows only share lines between neighbouring reads).
-template <int W>
-__device__ __forceinline__ void load_data_rm(const FilterArgs &a, const PairIdx &p,
-                                             PairData<W> &d, const uint32_t *rm,
-                                             uint32_t rm_stride)
-{
-    const uint32_t r = p.r < a.n_reads ? p.r : 0u;
-    const uint4 *q = reinterpret_cast<const uint4 *>(rm + (size_t)r * rm_stride);
-#pragma unroll
-    for (int j = 0; j < 2 * W; j += 4) {           // rows > 2W - 2 >= j
-        const uint4 v = q[j / 4];
-        const uint32_t w4[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-        for (int k = 0; k < 4; ++k)
-            if (j + k < 2 * W)
-                d.words[j + k] = w4[k];
-    }
-    const uint8_t *flag = a.read_has_n ? a.read_has_n
-                                       : reinterpret_cast<const uint8_t *>(a.read_len);
-    d.m = (uint32_t)a.read_len[r];
-    d.has_n = (uint32_t)flag[r];
-    load_window<W>(a, p.pos, d);
-    load_unknown_lines<W>(a, p.pos, d);
-}
-
-// Transposed read rows (word j of read r at reads[j * pitch + r]) to the
-// row-major copy load_data_rm takes: a workgroup stages 256 reads' rows in
-// LDS (each row read with consecutive lanes on consecutive words) and each
-// lane writes its read's rm_stride words as 16-byte stores (consecutive lanes,
-// consecutive reads).
-__global__ __launch_bounds__(256) void k_reads_rowmajor(const uint32_t *reads, uint32_t pitch,
-                                                        uint32_t rows, uint32_t n_reads,
-                                                        uint32_t rm_stride, uint32_t *rm)
-{
-    extern __shared__ uint32_t rm_lds[];
-    const uint32_t t = threadIdx.x;
-    const uint32_t r0 = blockIdx.x * 256u;
-    const uint32_t r = r0 + t;
-    const uint32_t ld = rm_stride + 1u;      // odd pitch: a row's words hit distinct banks
-    for (uint32_t j = 0; j < rows; ++j)
-        rm_lds[t * ld + j] = r < n_reads ? reads[(size_t)j * pitch + r] : 0u;
-    for (uint32_t j = rows; j < rm_stride; ++j)
-        rm_lds[t * ld + j] = 0u;
-    __syncthreads();
-    if (r < n_reads) {
-        uint4 *out = reinterpret_cast<uint4 *>(rm + (size_t)r * rm_stride);
-        for (uint32_t j = 0; j < rm_stride; j += 4)
-            out[j / 4] = make_uint4(rm_lds[t * ld + j], rm_lds[t * ld + j + 1],
-                                    rm_lds[t * ld + j + 2], rm_lds[t * ld + j + 3]);
-    }
-}
-
-// Persistent over the list, one pair per lane; RM: the reads come from the
-// row-major copy rm (load_data_rm).
-template <int W, int L, bool RM = false>
-__global__ __launch_bounds__(256) void k_verify(FilterArgs a, const uint32_t *list,
-                                                const uint32_t *count, uint16_t *dist,
-                                                const uint32_t *rm = nullptr,
-                                                uint32_t rm_stride = 0)
+// Persistent over the list, one pair per lane.
+template <int W, int L>
+__global__ __launch_bounds__(256) void k_verify_list(FilterArgs a, const uint32_t *list,
+                                                     const uint32_t *count, uint16_t *dist)
 {
     const uint32_t n = *count;
     const uint32_t stride = gridDim.x * 256u;
@@ -304,87 +612,11 @@ __global__ __launch_bounds__(256) void k_verify(FilterArgs a, const uint32_t *li
         const uint32_t i = list[t];
         const PairIdx p = load_idx(a, i);
         PairData<W> d;
-        if constexpr (RM)
-            load_data_rm<W>(a, p, d, rm, rm_stride);
-        else
-            load_data<W>(a, p, d);
+        load_data<W>(a, p, d);
         uint32_t m, out = GK_EST_NONE;
-        if (p.e <= GK_VERIFY_MAX_E && pair_gate<W>(a, p, d, m) == PAIR_OK)
-            out = verify_pair<W, L>(p, d, m);
+        if (pair_gate<W>(a, p, d, m) == PAIR_OK)
+            out = verify_pair<W, L>(p, d, m, a.e_uniform);
         dist[i] = (uint16_t)out;
-    }
-}
-
-// Persistent over the list, two entries per lane per step (t and t + 64),
-// for batches with one e <= 7 and reads of up to 8 words.  When every pair of
-// the wave that passes the gate has the length and e of the wave's first such
-// pair, each lane's two pairs share a 32-bit band word (band_distance2); pairs
-// that fail the gate get GK_EST_NONE.  Otherwise the wave appends its pairs to
-// `deferred` (one atomic per wave) for k_verify to do one per lane.  Keeping
-// that fallback out of this kernel keeps its registers low (two pairs' planes
-// already fill most of them).
-template <int W, int L>
-__global__ __launch_bounds__(256) void k_verify_paired(FilterArgs a, const uint32_t *list,
-                                                       const uint32_t *count, uint16_t *dist,
-                                                       uint32_t *deferred,
-                                                       uint32_t *deferred_count)
-{
-    const uint32_t n = *count;
-    const uint32_t lane = threadIdx.x & 63u;
-    // A wave takes blocks of 128 consecutive list entries, a lane entries
-    // lane and lane + 64 of the block: the list orders each listing group by
-    // read length, so the two halves of a block mostly share one.
-    const uint32_t first = (blockIdx.x * 4u + (threadIdx.x >> 6)) * 128u + lane;
-    const uint32_t step = gridDim.x * 4u * 128u;
-    for (uint32_t t = first; t < n; t += step) {
-        const bool has1 = t + 64u < n;
-        const uint32_t i0 = list[t];
-        const uint32_t i1 = has1 ? list[t + 64u] : i0;
-        const PairIdx p0 = load_idx(a, i0);
-        const PairIdx p1 = load_idx(a, i1);
-        PairData<W> d0, d1;
-        load_data<W>(a, p0, d0);
-        load_data<W>(a, p1, d1);
-        uint32_t m0 = 0, m1 = 0;
-        const bool ok0 = p0.e <= GK_VERIFY_MAX_E && pair_gate<W>(a, p0, d0, m0) == PAIR_OK;
-        const bool ok1 = p1.e <= GK_VERIFY_MAX_E && pair_gate<W>(a, p1, d1, m1) == PAIR_OK;
-        // the wave's length and e: those of its first pair that passed the gate
-        const unsigned long long v0 = __ballot(ok0), v1 = __ballot(ok1);
-        uint32_t ew = 0, mw = 0;
-        if (v0) {
-            const int src = __builtin_ctzll(v0);
-            ew = (uint32_t)__builtin_amdgcn_readlane((int)p0.e, src);
-            mw = (uint32_t)__builtin_amdgcn_readlane((int)m0, src);
-        } else if (v1) {
-            const int src = __builtin_ctzll(v1);
-            ew = (uint32_t)__builtin_amdgcn_readlane((int)p1.e, src);
-            mw = (uint32_t)__builtin_amdgcn_readlane((int)m1, src);
-        }
-        const bool fits = (!ok0 || (p0.e == ew && m0 == mw)) && (!ok1 || (p1.e == ew && m1 == mw));
-        if ((v0 | v1) == 0ull) {
-            dist[i0] = (uint16_t)GK_EST_NONE;
-            if (has1)
-                dist[i1] = (uint16_t)GK_EST_NONE;
-        } else if (ew <= 7u && __ballot(!fits) == 0ull) {
-            uint32_t gh0[W], gl0[W], rh0[W], rl0[W], gh1[W], gl1[W], rh1[W], rl1[W];
-            pair_planes<W, L>(p0, d0, mw, gh0, gl0, rh0, rl0);
-            pair_planes<W, L>(p1, d1, mw, gh1, gl1, rh1, rl1);
-            const uint32_t two = band_distance2<W>(rh0, rl0, gh0, gl0, rh1, rl1, gh1, gl1, mw, ew);
-            dist[i0] = (uint16_t)(ok0 ? (two & 0xFFFFu) : GK_EST_NONE);
-            if (has1)
-                dist[i1] = (uint16_t)(ok1 ? (two >> 16) : GK_EST_NONE);
-        } else {
-            const unsigned long long act = __ballot(true), two = __ballot(has1);
-            const uint32_t n_act = (uint32_t)__popcll(act), n_two = (uint32_t)__popcll(two);
-            uint32_t base = 0;
-            if (lane == (uint32_t)__builtin_ctzll(act))
-                base = atomicAdd(deferred_count, n_act + n_two);
-            base = (uint32_t)__builtin_amdgcn_readlane((int)base, __builtin_ctzll(act));
-            const unsigned long long below = (1ull << lane) - 1ull;
-            deferred[base + (uint32_t)__popcll(act & below)] = i0;
-            if (has1)
-                deferred[base + n_act + (uint32_t)__popcll(two & below)] = i1;
-        }
     }
 }
 
@@ -395,8 +627,8 @@ __global__ __launch_bounds__(256) void k_verify_paired(FilterArgs a, const uint3
 // counts into offsets (and the total into *count), k_select_write puts each
 // workgroup's pairs at its offset through LDS: in pair order when they all
 // have one sort key, else ordered by key (read length; with a per-pair e,
-// also whether e > 15), so that the waves of the verify kernels see one
-// length and one band width (their fast paths need it).  VEC needs accept
+// also whether e > 15), so that the waves of the verify kernel see one
+// length (its fast path needs it).  VEC needs accept
 // and dist aligned to 16 bytes; the host checks.
 constexpr uint32_t SEL_PER_LANE = 16u, SEL_PER_GROUP = 256u * SEL_PER_LANE;
 
@@ -452,7 +684,7 @@ __global__ __launch_bounds__(256) void k_select_count(const uint8_t *accept, uin
 }
 
 // One workgroup of 1024 lanes: exclusive prefix sums of groups (<= 2^18)
-// counts in place, the total into count[0] and 0 into count[1].
+// counts in place, the total into *count.
 __global__ __launch_bounds__(1024) void k_select_scan(uint32_t *group_count, uint32_t groups,
                                                       uint32_t *count)
 {
@@ -485,14 +717,13 @@ __global__ __launch_bounds__(1024) void k_select_scan(uint32_t *group_count, uin
     }
     if (threadIdx.x == 1023u) {
         count[0] = before + incl;
-        count[1] = 0u;               // k_verify_paired's deferred pairs
     }
 }
 
 // Sort keys of the 16 pairs i0 .. i0 + 15 a lane lists (bit j of sel): the
 // read length when a pair can be compared at it (1..max_read_len), else 0 (it
-// fails the gate); with a per-pair e, twice that plus whether e > 15.  With no pair-to-read map the 16 lengths are consecutive
-// and come in two 16-byte loads when aligned.
+// fails the gate).  With no pair-to-read map the 16 lengths are consecutive and
+// come in two 16-byte loads when aligned.
 __device__ __forceinline__ void length_keys(const FilterArgs &a, uint32_t i0, uint32_t sel,
                                             uint32_t (&key)[SEL_PER_LANE])
 {
@@ -533,13 +764,6 @@ __device__ __forceinline__ void length_keys(const FilterArgs &a, uint32_t i0, ui
 #pragma unroll
     for (uint32_t j = 0; j < SEL_PER_LANE; ++j)
         key[j] = key[j] <= a.max_read_len ? key[j] : 0u;
-    // With a per-pair e, pairs on the 32-bit band (e <= 15) and on the 64-bit
-    // one are kept apart too, so that a wave runs one band width.
-    if (a.e_pair) {
-#pragma unroll
-        for (uint32_t j = 0; j < SEL_PER_LANE; ++j)
-            key[j] = 2u * key[j] + ((sel & (1u << j)) && a.e_pair[i0 + j] > 15u ? 1u : 0u);
-    }
 }
 
 template <bool VEC>
@@ -549,7 +773,7 @@ __global__ __launch_bounds__(256) void k_select_write(FilterArgs a, const uint8_
 {
     // stage[t]: sort key << 12 | the pair's offset in the group (< 4096)
     __shared__ uint32_t stage[SEL_PER_GROUP];
-    __shared__ uint32_t hist[2u * GK_MAX_READ_LEN + 2u];
+    __shared__ uint32_t hist[GK_MAX_READ_LEN + 1u];
     __shared__ uint32_t wave_sum[4], wave_min[4], wave_max[4];
     const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
     const uint32_t i0 = blockIdx.x * SEL_PER_GROUP + threadIdx.x * SEL_PER_LANE;
@@ -640,151 +864,15 @@ __global__ __launch_bounds__(256) void k_select_write(FilterArgs a, const uint8_
     }
 }
 
-// ---- listing by (read length in words, e) over the whole batch ----------
-//
-// With a threshold per pair, a wave of the one-pair-per-lane kernel takes its
-// scalar path (one band width, one shift schedule, scalar trip counts) only
-// if its pairs share e and the read length.  After the filter a 4096-pair
-// group lists a few hundred pairs over as many (length, e) combinations, so
-// sorting within groups leaves nearly every wave mixed.  These kernels sort
-// the listed pairs of the whole batch by key = (ceil(m / 32) - 1) * 32 +
-// min(e, 31) (512 keys; within a key the lengths differ in the last word
-// only): each group counts its pairs per key in LDS and adds the counts to
-// one of BIN_COPIES copies of the key counts (by group number, so that no
-// count is added to by more than 1 / BIN_COPIES of the groups); a scan turns
-// the counts into starts, key-major and copy-minor; each group then reserves
-// its run in its copy of each key with one atomic and writes its pairs there
-// (the order within a key does not matter: every result is written at its
-// own pair index).
-constexpr uint32_t NKEYS = 512u;
-constexpr uint32_t BIN_COPIES = 32u;
-constexpr uint32_t BIN_CELLS = NKEYS * BIN_COPIES;   // counts, then cursors, then starts
-
-__device__ __forceinline__ void bin_keys(const FilterArgs &a, uint32_t i0, uint32_t sel,
-                                         uint32_t (&key)[SEL_PER_LANE])
-{
-    FilterArgs la = a;
-    la.e_pair = nullptr;                 // plain read lengths
-    uint32_t len[SEL_PER_LANE];
-    length_keys(la, i0, sel, len);
-#pragma unroll
-    for (uint32_t j = 0; j < SEL_PER_LANE; ++j) {
-        const uint32_t e = (sel & (1u << j)) ? (uint32_t)a.e_pair[i0 + j] : 0u;
-        key[j] = len[j] ? ((len[j] + 31u) / 32u - 1u) * 32u + (e < 31u ? e : 31u) : 0u;
-    }
-}
-
-// counts and cursors to zero
-__global__ __launch_bounds__(256) void k_bin_zero(uint32_t *bins)
-{
-    for (uint32_t b = blockIdx.x * 256u + threadIdx.x; b < 2u * BIN_CELLS; b += gridDim.x * 256u)
-        bins[b] = 0u;
-}
-
-template <bool VEC>
-__global__ __launch_bounds__(256) void k_bin_count(FilterArgs a, const uint8_t *accept,
-                                                   uint32_t n, uint32_t *bins, uint16_t *dist)
-{
-    __shared__ uint32_t h[NKEYS];
-    for (uint32_t b = threadIdx.x; b < NKEYS; b += 256u)
-        h[b] = 0u;
-    __syncthreads();
-    const uint32_t i0 = blockIdx.x * SEL_PER_GROUP + threadIdx.x * SEL_PER_LANE;
-    const uint32_t sel = select_bits<VEC>(accept, n, i0, dist, true);
-    uint32_t key[SEL_PER_LANE];
-    bin_keys(a, i0, sel, key);
-#pragma unroll
-    for (uint32_t j = 0; j < SEL_PER_LANE; ++j)
-        if (sel & (1u << j))
-            atomicAdd(&h[key[j]], 1u);
-    __syncthreads();
-    uint32_t *copy = bins + (blockIdx.x % BIN_COPIES) * NKEYS;
-    for (uint32_t b = threadIdx.x; b < NKEYS; b += 256u)
-        if (h[b])
-            atomicAdd(&copy[b], h[b]);
-}
-
-// Starts of every (key, copy) cell, key-major: bins[2 BIN_CELLS + c * NKEYS +
-// b] for copy c of key b; count[0] = the total, count[1] = 0.
-__global__ __launch_bounds__(1024) void k_bin_scan(uint32_t *bins, uint32_t *count)
-{
-    __shared__ uint32_t wave_sum[16];
-    constexpr uint32_t PER = BIN_CELLS / 1024u;       // cells per thread, key-major
-    const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
-    uint32_t local[PER], sum = 0;
-#pragma unroll
-    for (uint32_t q = 0; q < PER; ++q) {
-        const uint32_t cell = threadIdx.x * PER + q;  // = key * BIN_COPIES + copy
-        local[q] = bins[(cell % BIN_COPIES) * NKEYS + cell / BIN_COPIES];
-        sum += local[q];
-    }
-    uint32_t incl = sum;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const uint32_t t = __shfl_up(incl, o, 64);
-        if (lane >= (uint32_t)o)
-            incl += t;
-    }
-    if (lane == 63u)
-        wave_sum[wave] = incl;
-    __syncthreads();
-    uint32_t before = 0;
-    for (uint32_t w = 0; w < wave; ++w)
-        before += wave_sum[w];
-    uint32_t run = before + incl - sum;
-#pragma unroll
-    for (uint32_t q = 0; q < PER; ++q) {
-        const uint32_t cell = threadIdx.x * PER + q;
-        bins[2u * BIN_CELLS + (cell % BIN_COPIES) * NKEYS + cell / BIN_COPIES] = run;
-        run += local[q];
-    }
-    if (threadIdx.x == 1023u) {
-        count[0] = before + incl;
-        count[1] = 0u;
-    }
-}
-
-template <bool VEC>
-__global__ __launch_bounds__(256) void k_bin_write(FilterArgs a, const uint8_t *accept,
-                                                   uint32_t n, uint32_t *bins, uint32_t *list)
-{
-    __shared__ uint32_t h[NKEYS];
-    for (uint32_t b = threadIdx.x; b < NKEYS; b += 256u)
-        h[b] = 0u;
-    __syncthreads();
-    const uint32_t i0 = blockIdx.x * SEL_PER_GROUP + threadIdx.x * SEL_PER_LANE;
-    const uint32_t sel = select_bits<VEC>(accept, n, i0, nullptr, false);
-    uint32_t key[SEL_PER_LANE], rank[SEL_PER_LANE];
-    bin_keys(a, i0, sel, key);
-#pragma unroll
-    for (uint32_t j = 0; j < SEL_PER_LANE; ++j)
-        rank[j] = (sel & (1u << j)) ? atomicAdd(&h[key[j]], 1u) : 0u;
-    __syncthreads();
-    // this group's run in its copy of each key: the cell's start plus a
-    // reservation on the cell's cursor
-    const uint32_t c = (blockIdx.x % BIN_COPIES) * NKEYS;
-    for (uint32_t b = threadIdx.x; b < NKEYS; b += 256u)
-        if (h[b])
-            h[b] = bins[2u * BIN_CELLS + c + b] + atomicAdd(&bins[BIN_CELLS + c + b], h[b]);
-    __syncthreads();
-#pragma unroll
-    for (uint32_t j = 0; j < SEL_PER_LANE; ++j)
-        if (sel & (1u << j))
-            list[h[key[j]] + rank[j]] = i0 + j;
-}
-
-// Resident 256-lane workgroups per CU of k_verify (PAIRED false) or
-// k_verify_paired (true).
-template <int W, int L, bool PAIRED, bool RM = false>
-hipError_t verify_blocks_per_cu(int &out)
+// Resident 256-lane workgroups per CU of k_verify_list.
+template <int W, int L>
+hipError_t list_blocks_per_cu(int &out)
 {
     static int per_cu = -1;
     if (per_cu < 0) {
         int v = 0;
-        hipError_t e = PAIRED ? hipOccupancyMaxActiveBlocksPerMultiprocessor(
-                                    &v, k_verify_paired<W, L>, 256, 0)
-                              : hipOccupancyMaxActiveBlocksPerMultiprocessor(
-                                    &v, k_verify<W, L, RM>, 256, 0);
+        const hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
+            &v, k_verify_list<W, L>, 256, 0);
         if (e != hipSuccess)
             return e;
         per_cu = v > 0 ? v : 1;
@@ -794,28 +882,13 @@ hipError_t verify_blocks_per_cu(int &out)
 }
 
 template <int W, int L>
-hipError_t verify_wl(const FilterArgs &a, const uint8_t *accept, uint16_t *dist, uint32_t *list,
-                     uint32_t *groups_buf, uint32_t *deferred, uint32_t *count, uint32_t *bins,
-                     uint32_t *rm, int cus, hipStream_t s)
+hipError_t list_wl(const FilterArgs &a, const uint8_t *accept, uint16_t *dist,
+                   const VerifyScratch &x, int cus, hipStream_t s)
 {
-    const bool paired = W <= 8 && a.e_pair == nullptr && a.e_uniform <= 7u;
-    const bool use_rm = rm != nullptr && !paired;
-    const uint32_t rm_stride = (a.rows + 3u) & ~3u;
-    int per_cu = 1, per_cu1 = 1;
-    hipError_t oe = use_rm ? verify_blocks_per_cu<W, L, false, true>(per_cu1)
-                           : verify_blocks_per_cu<W, L, false>(per_cu1);
-    if (oe == hipSuccess && paired)
-        oe = verify_blocks_per_cu<W, L, true>(per_cu);
+    int per_cu = 1;
+    const hipError_t oe = list_blocks_per_cu<W, L>(per_cu);
     if (oe != hipSuccess)
         return oe;
-    if (use_rm && a.n_reads > 0) {
-        hipLaunchKernelGGL(k_reads_rowmajor, dim3((a.n_reads + 255u) / 256u), dim3(256),
-                           (size_t)256u * (rm_stride + 1u) * 4u, s, a.reads, a.pitch, a.rows,
-                           a.n_reads, rm_stride, rm);
-        hipError_t e = hipGetLastError();
-        if (e != hipSuccess)
-            return e;
-    }
     const uint64_t CHUNK = 1ull << 30;
     for (uint64_t first = 0; first < a.n_pairs; first += CHUNK) {
         FilterArgs c = a;
@@ -825,71 +898,35 @@ hipError_t verify_wl(const FilterArgs &a, const uint8_t *accept, uint16_t *dist,
         if (!a.pair_read && first > 0)
             c.n_reads = 0;   // pair i uses read i < n_reads < 2^30: none here
         c.cand_pos = a.cand_pos + first;
-        c.e_pair = a.e_pair ? a.e_pair + first : nullptr;
         c.accept = nullptr;
         c.est = nullptr;
         c.accept_bits = nullptr;
         const uint8_t *acc = accept ? accept + first : nullptr;
         uint16_t *out = dist + first;
-        const uint64_t want = (n + 255) / 256;
         const uint32_t groups = (uint32_t)((n + SEL_PER_GROUP - 1) / SEL_PER_GROUP);
         const bool vec = ((uintptr_t)acc & 15u) == 0 && ((uintptr_t)out & 15u) == 0;
-        if (c.e_pair) {
-            // per-pair e: listed by (length in words, e) over the whole batch
-            hipLaunchKernelGGL(k_bin_zero, dim3(32), dim3(256), 0, s, bins);
-            if (vec)
-                hipLaunchKernelGGL(k_bin_count<true>, dim3(groups), dim3(256), 0, s, c, acc,
-                                   (uint32_t)n, bins, out);
-            else
-                hipLaunchKernelGGL(k_bin_count<false>, dim3(groups), dim3(256), 0, s, c, acc,
-                                   (uint32_t)n, bins, out);
-            hipLaunchKernelGGL(k_bin_scan, dim3(1), dim3(1024), 0, s, bins, count);
-            if (vec)
-                hipLaunchKernelGGL(k_bin_write<true>, dim3(groups), dim3(256), 0, s, c, acc,
-                                   (uint32_t)n, bins, list);
-            else
-                hipLaunchKernelGGL(k_bin_write<false>, dim3(groups), dim3(256), 0, s, c, acc,
-                                   (uint32_t)n, bins, list);
-        } else {
-            if (vec)
-                hipLaunchKernelGGL(k_select_count<true>, dim3(groups), dim3(256), 0, s, acc,
-                                   (uint32_t)n, groups_buf, out);
-            else
-                hipLaunchKernelGGL(k_select_count<false>, dim3(groups), dim3(256), 0, s, acc,
-                                   (uint32_t)n, groups_buf, out);
-            hipLaunchKernelGGL(k_select_scan, dim3(1), dim3(1024), 0, s, groups_buf, groups,
-                               count);
-            if (vec)
-                hipLaunchKernelGGL(k_select_write<true>, dim3(groups), dim3(256), 0, s, c, acc,
-                                   (uint32_t)n, groups_buf, list);
-            else
-                hipLaunchKernelGGL(k_select_write<false>, dim3(groups), dim3(256), 0, s, c, acc,
-                                   (uint32_t)n, groups_buf, list);
-        }
-        // Grids of up to 8 times the resident workgroups: later workgroups
-        // start as earlier ones finish, so the waves' gathers do not all come
-        // at once (measured faster than one resident round at every sweep
-        // point; the list length is only known on the device).
-        const uint64_t vb1 = want < 8ull * cus * per_cu1 ? want : 8ull * cus * per_cu1;
-        if (paired) {
-            const uint64_t want2 = (n + 511) / 512;        // two pairs per lane
-            const uint64_t vb = want2 < 8ull * cus * per_cu ? want2 : 8ull * cus * per_cu;
-            hipLaunchKernelGGL((k_verify_paired<W, L>), dim3((uint32_t)vb), dim3(256), 0, s, c,
-                               list, count, out, deferred, count + 1);
-            // the waves it could not pair (count[1] entries, usually none:
-            // one resident round)
-            const uint64_t vbd = want < (uint64_t)cus * per_cu1 ? want : (uint64_t)cus * per_cu1;
-            hipLaunchKernelGGL((k_verify<W, L>), dim3((uint32_t)vbd), dim3(256), 0, s, c,
-                               (const uint32_t *)deferred, (const uint32_t *)(count + 1), out,
-                               (const uint32_t *)nullptr, 0u);
-        } else if (use_rm) {
-            hipLaunchKernelGGL((k_verify<W, L, true>), dim3((uint32_t)vb1), dim3(256), 0, s, c,
-                               list, count, out, (const uint32_t *)rm, rm_stride);
-        } else {
-            hipLaunchKernelGGL((k_verify<W, L>), dim3((uint32_t)vb1), dim3(256), 0, s, c, list,
-                               count, out, (const uint32_t *)nullptr, 0u);
-        }
-        hipError_t e = hipGetLastError();
+        if (vec)
+            hipLaunchKernelGGL(k_select_count<true>, dim3(groups), dim3(256), 0, s, acc,
+                               (uint32_t)n, x.groups, out);
+        else
+            hipLaunchKernelGGL(k_select_count<false>, dim3(groups), dim3(256), 0, s, acc,
+                               (uint32_t)n, x.groups, out);
+        hipLaunchKernelGGL(k_select_scan, dim3(1), dim3(1024), 0, s, x.groups, groups, x.count);
+        if (vec)
+            hipLaunchKernelGGL(k_select_write<true>, dim3(groups), dim3(256), 0, s, c, acc,
+                               (uint32_t)n, x.groups, x.list);
+        else
+            hipLaunchKernelGGL(k_select_write<false>, dim3(groups), dim3(256), 0, s, c, acc,
+                               (uint32_t)n, x.groups, x.list);
+        // Up to 8 times the resident workgroups: later workgroups start as
+        // earlier ones finish, so the waves' gathers do not all come at once
+        // (measured faster than one resident round at every sweep point; the
+        // list length is only known on the device).
+        const uint64_t want = (n + 255) / 256, most = 8ull * cus * per_cu;
+        hipLaunchKernelGGL((k_verify_list<W, L>), dim3((uint32_t)(want < most ? want : most)),
+                           dim3(256), 0, s, c, (const uint32_t *)x.list,
+                           (const uint32_t *)x.count, out);
+        const hipError_t e = hipGetLastError();
         if (e != hipSuccess)
             return e;
     }
@@ -897,43 +934,26 @@ hipError_t verify_wl(const FilterArgs &a, const uint8_t *accept, uint16_t *dist,
 }
 
 template <int L>
-hipError_t verify_l(const FilterArgs &a, const uint8_t *accept, uint16_t *dist, uint32_t *list,
-                    uint32_t *groups_buf, uint32_t *deferred, uint32_t *count, uint32_t *bins,
-                    uint32_t *rm, uint32_t words, int cus, hipStream_t s)
+hipError_t list_l(const FilterArgs &a, const uint8_t *accept, uint16_t *dist, uint32_t words,
+                  const VerifyScratch &x, int cus, hipStream_t s)
 {
     switch (words) {
-    case 1: return verify_wl<1, L>(a, accept, dist, list, groups_buf, deferred, count, bins, rm, cus,
-                                  s);
-    case 2: return verify_wl<2, L>(a, accept, dist, list, groups_buf, deferred, count, bins, rm, cus,
-                                  s);
-    case 3: return verify_wl<3, L>(a, accept, dist, list, groups_buf, deferred, count, bins, rm, cus,
-                                  s);
-    case 4: return verify_wl<4, L>(a, accept, dist, list, groups_buf, deferred, count, bins, rm, cus,
-                                  s);
-    case 5: return verify_wl<5, L>(a, accept, dist, list, groups_buf, deferred, count, bins, rm, cus,
-                                  s);
-    case 6: return verify_wl<6, L>(a, accept, dist, list, groups_buf, deferred, count, bins, rm, cus,
-                                  s);
-    case 7: return verify_wl<7, L>(a, accept, dist, list, groups_buf, deferred, count, bins, rm, cus,
-                                  s);
-    case 8: return verify_wl<8, L>(a, accept, dist, list, groups_buf, deferred, count, bins, rm, cus,
-                                  s);
-    case 9: return verify_wl<9, L>(a, accept, dist, list, groups_buf, deferred, count, bins, rm, cus,
-                                  s);
-    case 10: return verify_wl<10, L>(a, accept, dist, list, groups_buf, deferred, count, bins, rm, cus,
-                                  s);
-    case 11: return verify_wl<11, L>(a, accept, dist, list, groups_buf, deferred, count, bins, rm, cus,
-                                  s);
-    case 12: return verify_wl<12, L>(a, accept, dist, list, groups_buf, deferred, count, bins, rm, cus,
-                                  s);
-    case 13: return verify_wl<13, L>(a, accept, dist, list, groups_buf, deferred, count, bins, rm, cus,
-                                  s);
-    case 14: return verify_wl<14, L>(a, accept, dist, list, groups_buf, deferred, count, bins, rm, cus,
-                                  s);
-    case 15: return verify_wl<15, L>(a, accept, dist, list, groups_buf, deferred, count, bins, rm, cus,
-                                  s);
-    case 16: return verify_wl<16, L>(a, accept, dist, list, groups_buf, deferred, count, bins, rm, cus,
-                                  s);
+    case 1: return list_wl<1, L>(a, accept, dist, x, cus, s);
+    case 2: return list_wl<2, L>(a, accept, dist, x, cus, s);
+    case 3: return list_wl<3, L>(a, accept, dist, x, cus, s);
+    case 4: return list_wl<4, L>(a, accept, dist, x, cus, s);
+    case 5: return list_wl<5, L>(a, accept, dist, x, cus, s);
+    case 6: return list_wl<6, L>(a, accept, dist, x, cus, s);
+    case 7: return list_wl<7, L>(a, accept, dist, x, cus, s);
+    case 8: return list_wl<8, L>(a, accept, dist, x, cus, s);
+    case 9: return list_wl<9, L>(a, accept, dist, x, cus, s);
+    case 10: return list_wl<10, L>(a, accept, dist, x, cus, s);
+    case 11: return list_wl<11, L>(a, accept, dist, x, cus, s);
+    case 12: return list_wl<12, L>(a, accept, dist, x, cus, s);
+    case 13: return list_wl<13, L>(a, accept, dist, x, cus, s);
+    case 14: return list_wl<14, L>(a, accept, dist, x, cus, s);
+    case 15: return list_wl<15, L>(a, accept, dist, x, cus, s);
+    case 16: return list_wl<16, L>(a, accept, dist, x, cus, s);
     default: return hipErrorInvalidValue;
     }
 }
@@ -941,15 +961,21 @@ hipError_t verify_l(const FilterArgs &a, const uint8_t *accept, uint16_t *dist, 
 }  // namespace
 
 hipError_t launch_verify(const FilterArgs &a, const uint8_t *accept, uint16_t *dist,
-                         uint32_t *list, uint32_t *groups, uint32_t *deferred, uint32_t *count,
-                         uint32_t *bins, uint32_t *reads_rm, uint32_t words, uint32_t layout,
-                         int cus, hipStream_t s)
+                         uint32_t words, uint32_t layout, hipStream_t s)
+{
+    const uint32_t tile = verify_tile(a.n_pairs);
+    return layout == GK_READS_INTERLEAVED
+               ? tile_l<GK_READS_INTERLEAVED>(a, accept, dist, words, tile, s)
+               : tile_l<GK_READS_SPLIT>(a, accept, dist, words, tile, s);
+}
+
+hipError_t launch_verify_listed(const FilterArgs &a, const uint8_t *accept, uint16_t *dist,
+                                uint32_t words, uint32_t layout, const VerifyScratch &x, int cus,
+                                hipStream_t s)
 {
     return layout == GK_READS_INTERLEAVED
-               ? verify_l<GK_READS_INTERLEAVED>(a, accept, dist, list, groups, deferred, count,
-                                                bins, reads_rm, words, cus, s)
-               : verify_l<GK_READS_SPLIT>(a, accept, dist, list, groups, deferred, count, bins,
-                                          reads_rm, words, cus, s);
+               ? list_l<GK_READS_INTERLEAVED>(a, accept, dist, words, x, cus, s)
+               : list_l<GK_READS_SPLIT>(a, accept, dist, words, x, cus, s);
 }
 
 }  // namespace gkd
