@@ -632,9 +632,19 @@ gkd::MixedArgs direct_args(const gk_ctx *ctx, uint64_t n_pairs, uint32_t wmax)
     const MixedConfig &c = ctx->mixed;
     gkd::MixedArgs x{};
     x.tile = c.untouched() ? gkd::mixed_auto_tile(n_pairs, wmax) : gkd::mixed_tile(c.tile);
+    x.lg = c.untouched() ? gkd::mixed_auto_lanes(n_pairs, wmax) : 0u;
     x.ppl = c.ppl;
     x.sort_e = c.sort_e;
     return x;
+}
+
+// The direct form, or the plain launch where a batch is too small to sort.
+hipError_t launch_direct(const gk_ctx *ctx, const gkd::FilterArgs &a, const gkd::MixedArgs &x,
+                         uint32_t wmax, uint32_t layout, hipStream_t s)
+{
+    if (ctx->mixed.untouched() && gkd::mixed_unsorted(a.n_pairs, wmax))
+        return gkd::launch_filter(a, wmax, layout, 0, s);
+    return gkd::launch_mixed(a, x, wmax, layout, s);
 }
 
 int mixed_args(gk_ctx *ctx, const MixedConfig &c, uint32_t wmax, uint32_t layout,
@@ -818,7 +828,7 @@ int gk_filter_mixed(gk_ctx *ctx, const gk_batch *b, void *stream)
         ctx->mixed.untouched() || n_tiles >= (uint64_t)ctx->cu_count) {
         gk_detail_log(ctx, "gk_filter_mixed: %llu pairs, direct launch (tile %u, %u per lane, "
                       "sort by e %u)", (unsigned long long)b->n_pairs, x.tile, x.ppl, x.sort_e);
-        e = gkd::launch_mixed(a, x, wmax, b->read_layout, hs);
+        e = launch_direct(ctx, a, x, wmax, b->read_layout, hs);
         if (e != hipSuccess)
             return hip_fail(ctx, e, "gk_filter_mixed: launch");
         return GK_OK;
@@ -890,7 +900,8 @@ int gk_filter_mixed_noalloc(gk_ctx *ctx, const gk_batch *b, void *stream)
         return fail(ctx, GK_EDEVICE, "gk_filter_mixed_noalloc: hipSetDevice failed");
     const uint32_t wmax = (b->max_read_len + 31) / 32;
     const gkd::MixedArgs x = direct_args(ctx, b->n_pairs, wmax);
-    const hipError_t e = gkd::launch_mixed(a, x, wmax, b->read_layout, (hipStream_t)stream);
+    const hipError_t e =
+        launch_direct(ctx, a, x, wmax, b->read_layout, (hipStream_t)stream);
     if (e != hipSuccess)
         return hip_fail(ctx, e, "gk_filter_mixed_noalloc: launch");
     return GK_OK;

@@ -68,18 +68,56 @@ struct BatchTable {
     FilterArgs args[MAX_TABLE_BATCHES];
 };
 
+// Lanes per pair (log2) of a small batch: below one wave per SIMD (65,536
+// lanes) a launch takes as long as its slowest lane, whose time is its chain of
+// masks, so the masks are shared out.  e: the threshold, or where each pair has
+// its own the one that a tenth of the longest read would have.  Sharing costs
+// about 1 us (masks by lane, the AND across lanes).  250 bases, e = 25: 11.3
+// -> 5.4 us with 8 lanes (8,192 pairs), 11.5 -> 6.5 with 4 (16,384), 11.5 -> 9.0
+// with 2 (32,768); 150 bases, e = 7: 5.0 -> 3.9, 5.1 -> 4.3 and 5.1 -> 5.3; 100
+// bases, e = 5: 3.7 -> 3.6, 3.7 -> 4.0.
+inline uint32_t split_lanes(uint64_t n_pairs, uint32_t e, uint32_t words)
+{
+    const uint32_t work = (e < 31u ? e : 31u) * words;
+    if (n_pairs <= 12288)
+        return work >= 30u ? 3u : 0u;
+    if (n_pairs <= 24576)
+        return work >= 30u ? 2u : 0u;
+    return n_pairs <= 49152 && work >= 100u ? 1u : 0u;
+}
+
 // Pairs per tile of the mixed launch for a value of GK_OPT_MIXED_TILE.
 inline uint32_t mixed_tile(uint32_t option) { return option / 4; }
 
 // Pairs per tile where no tuning was set.  A small batch needs tiles enough
-// for every compute unit (60,001 mixed pairs over 3.1 Gbp: 21 us with 512, 30
-// with 1024, 47 with 2048 pairs); a large one gains from fuller chunks (2^24
-// pairs: 1,092, 837 and 805 us; 2^20: 81, 66 and 68).  Up to 4 words per mask
-// eight waves per SIMD fit the registers, and only 512-pair tiles leave the LDS
-// for them (2^24 pairs of 100 bases: 475, 563 and 774 us).
+// for every compute unit (60,001 mixed pairs over 3.1 Gbp: 18 us with 256, 21
+// with 512, 30 with 1024 pairs); a large one gains from fuller chunks (2^24
+// pairs: 1,092, 837 and 805 us with 512, 1024 and 2048; 2^20: 81, 66 and 68).
+// Up to 4 words per mask eight waves per SIMD fit the registers, and only
+// 512-pair tiles leave the LDS for them (2^24 pairs of 100 bases: 475, 563 and
+// 774 us).
 inline uint32_t mixed_auto_tile(uint64_t n_pairs, uint32_t wmax)
 {
-    return wmax <= 4 || n_pairs < (1u << 19) ? 512u : n_pairs < (1u << 22) ? 1024u : 2048u;
+    if (wmax <= 4)
+        return 512u;
+    return n_pairs <= (1u << 17) ? 256u : n_pairs < (1u << 19) ? 512u
+         : n_pairs < (1u << 22) ? 1024u : 2048u;
+}
+
+// Lanes per pair (log2) of those tiles: 60,001 pairs 17.8 -> 15.2 us with two
+// lanes, 131,072 pairs 25.9 -> 21.3 (17.8 and 23.7 with four).
+inline uint32_t mixed_auto_lanes(uint64_t n_pairs, uint32_t wmax)
+{
+    return wmax > 4 && n_pairs <= (1u << 17) ? 1u : 0u;
+}
+
+// Batches too small for the sort's steps to pay: with 8 or 4 lanes per pair
+// the plain kernel takes 8 to 11 us for up to 16,384 mixed pairs, the sorted one
+// 14 and more; at 4 words per mask and fewer it needs no lanes for that (65,536
+// pairs of 64 to 128 bases: 7.2 against 9.7 us; 262,144: 14.9 against 12.9).
+inline bool mixed_unsorted(uint64_t n_pairs, uint32_t wmax)
+{
+    return n_pairs <= (wmax <= 4 ? 1u << 17 : 24576u);
 }
 
 // Whether the plain call sorts its pairs first (the direct form of the mixed
@@ -101,6 +139,7 @@ struct MixedArgs {
     uint32_t ppl;                // 1 or 2
     uint32_t sort_e;             // 0 or 1
     uint32_t blocks;             // table form: persistent workgroups
+    uint32_t lg;                 // direct form: 2^lg lanes per pair (0, 1 or 2)
 };
 
 }  // namespace gkd

@@ -37,6 +37,35 @@ __global__ __launch_bounds__(256) void k_filter_single(FilterArgs a)
     }
 }
 
+// A small batch: `lanes` = 2^lg neighbouring lanes per pair, each with every
+// lanes-th shift of its masks.  Below one wave per SIMD the launch takes as
+// long as one lane does, and a lane's time is its chain of masks.
+template <int W, int L>
+__global__ __launch_bounds__(256) void k_filter_split(FilterArgs a, uint32_t lg)
+{
+    const uint32_t n = (uint32_t)a.n_pairs;
+    const uint32_t lanes = 1u << lg;
+    const uint32_t i = (blockIdx.x * 256u + threadIdx.x) >> lg;
+    const uint32_t sub = threadIdx.x & (lanes - 1u);
+    uint32_t res = GK_INVALID;
+    if (i < n) {
+        const PairIdx p = load_idx(a, i);
+        PairData<W> d;
+        load_data<W>(a, p, d);
+        uint32_t est;
+        res = compute_pair<W, L, true, false, false, true>(a, p, d, est, sub, lanes);
+        if (sub == 0u) {
+            a.accept[i] = (uint8_t)res;
+            a.est[i] = (uint16_t)est;
+        }
+    }
+    if (a.accept_bits) {
+        // (the grid covers whole words)
+        store_split_bits(a, i, lg, sub == 0u && i < n &&
+                                       (res == GK_ACCEPT || res == GK_UNDEFINED));
+    }
+}
+
 template <int W, int L>
 __global__ __launch_bounds__(256) void k_filter(FilterArgs a)
 {
@@ -127,6 +156,16 @@ hipError_t launch_wl(const FilterArgs &a, uint32_t pairs_per_lane, hipStream_t s
             hipLaunchKernelGGL((k_filter_single<W, L, true>), dim3((uint32_t)full), dim3(256), 0,
                                s, c);
             hipError_t e = hipGetLastError();
+            if (e != hipSuccess)
+                return e;
+            continue;
+        }
+        const uint32_t lg = pairs_per_lane == 0 ? split_lanes(n, a.e_pair ? 3u * W : a.e_uniform, W) : 0u;
+        if (lg != 0u) {
+            const uint64_t lanes = ((n + 63) / 64 * 64) << lg;
+            hipLaunchKernelGGL((k_filter_split<W, L>), dim3((uint32_t)((lanes + 255) / 256)),
+                               dim3(256), 0, s, c, lg);
+            const hipError_t e = hipGetLastError();
             if (e != hipSuccess)
                 return e;
             continue;

@@ -45,11 +45,13 @@ __device__ __forceinline__ uint32_t word_direct(const uint8_t *ascii, uint64_t o
 
 // Up to 4 words per mask (reads of 128 bases) the paper's filter fits in 64
 // registers, so eight waves per SIMD.
-template <int W, bool VAR>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(W <= 4 && !VAR ? 8 : 1)))
-void k_filter_ascii(FilterArgs a, const uint8_t *ascii,
-                                                      const uint64_t *read_off)
+// SPLIT: a small batch, 2^lg lanes per pair (split_lanes).
+template <int W, bool VAR, bool SPLIT = false>
+__global__ __launch_bounds__(256)
+__attribute__((amdgpu_waves_per_eu(W <= 4 && !VAR && !SPLIT ? 8 : 1)))
+void k_filter_ascii(FilterArgs a, const uint8_t *ascii, const uint64_t *read_off, uint32_t lg)
 {
+    const uint32_t reads = SPLIT ? ENC_G >> lg : ENC_G;    // of this workgroup
     extern __shared__ uint32_t fa_lds[];
     const uint32_t rows = a.rows;
     const uint32_t cap = enc_cap_words(rows);
@@ -58,9 +60,9 @@ void k_filter_ascii(FilterArgs a, const uint8_t *ascii,
     uint32_t *p_un = fa_lds + 2u * (cap + 1u);
 
     const uint32_t n = (uint32_t)a.n_pairs;
-    const uint32_t r0 = blockIdx.x * ENC_G;
-    const uint32_t r1 = n - r0 < ENC_G ? n : r0 + ENC_G;
-    const uint64_t base = read_off[r0];
+    const uint32_t r0 = blockIdx.x * reads;
+    const uint32_t r1 = n < r0 + reads ? n : r0 + reads;
+    const uint64_t base = read_off[SPLIT && r0 > n ? n : r0];
     const uint64_t end = read_off[r1];
     const uint64_t a0 = base & ~31ull;                  // span start, 32-byte aligned
     const bool staged = end >= base && end - a0 <= 32ull * cap;
@@ -86,7 +88,8 @@ void k_filter_ascii(FilterArgs a, const uint8_t *ascii,
     }
     __syncthreads();
 
-    const uint32_t i = r0 + threadIdx.x;
+    const uint32_t i = r0 + (SPLIT ? threadIdx.x >> lg : threadIdx.x);
+    const uint32_t sub = SPLIT ? threadIdx.x & ((1u << lg) - 1u) : 0u;
     uint32_t res = GK_INVALID;
     if (i < n) {
         PairIdx p;
@@ -132,17 +135,23 @@ void k_filter_ascii(FilterArgs a, const uint8_t *ascii,
         }
         d.m = (uint32_t)(len < 0xFFFFu ? len : 0xFFFFu);
         uint32_t est;
-        res = compute_pair<W, GK_READS_SPLIT, true, VAR, true>(a, p, d, est);
+        res = compute_pair<W, GK_READS_SPLIT, true, VAR, true, SPLIT>(a, p, d, est, sub, 1u << lg);
         // An unknown base in a read of a valid length makes the pair
         // undefined, as the read's unknown flag does for the plain launch.
         if (unknown && d.m != 0u && d.m <= a.max_read_len) {
             res = GK_UNDEFINED;
             est = GK_EST_NONE;
         }
-        __builtin_nontemporal_store((uint8_t)res, a.accept + i);
-        __builtin_nontemporal_store((uint16_t)est, a.est + i);
+        if (sub == 0u) {
+            __builtin_nontemporal_store((uint8_t)res, a.accept + i);
+            __builtin_nontemporal_store((uint16_t)est, a.est + i);
+        }
     }
-    if (a.accept_bits) {
+    if (SPLIT && a.accept_bits) {
+        // (the grid covers whole words)
+        store_split_bits(a, i, lg, sub == 0u && i < n &&
+                                       (res == GK_ACCEPT || res == GK_UNDEFINED));
+    } else if (a.accept_bits) {
         const unsigned long long bits = __ballot(i < n && (res == GK_ACCEPT || res == GK_UNDEFINED));
         if ((threadIdx.x & 63u) == 0u && i < n)
             a.accept_bits[i >> 6] = bits;
@@ -166,12 +175,19 @@ hipError_t launch_w(const FilterArgs &a, const uint8_t *ascii, const uint64_t *r
         c.est = a.est + first;
         c.accept_bits = a.accept_bits ? a.accept_bits + first / 64 : nullptr;
         const dim3 grid((uint32_t)((n + ENC_G - 1) / ENC_G));
-        if (a.flags != 0u)
+        const uint32_t lg = split_lanes(n, a.e_pair ? 3u * W : a.e_uniform, W);
+        if (a.flags != 0u) {
             hipLaunchKernelGGL((k_filter_ascii<W, true>), grid, dim3(256), lds, s, c, ascii,
-                               read_off + first);
-        else
+                               read_off + first, 0u);
+        } else if (lg != 0u) {
+            const uint64_t lanes = ((n + 63) / 64 * 64) << lg;
+            hipLaunchKernelGGL((k_filter_ascii<W, false, true>),
+                               dim3((uint32_t)((lanes + 255) / 256)), dim3(256), lds, s, c, ascii,
+                               read_off + first, lg);
+        } else {
             hipLaunchKernelGGL((k_filter_ascii<W, false>), grid, dim3(256), lds, s, c, ascii,
-                               read_off + first);
+                               read_off + first, 0u);
+        }
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess)
             return e;

@@ -41,13 +41,17 @@ struct MixedLds {
 };
 
 // Dynamic LDS after MixedLds: the tile's pair entries pos[T], read[T],
-// entry[T] u32, chunk_start[C] u32, chunk_info[C] u32 with C = T/64 + 17,
-// sorted[T] u16 (first the pairs' sort keys, then the slots in sorted order).
-__host__ __device__ inline uint32_t mixed_chunk_cap(uint32_t tile) { return tile / 64 + 17; }
-
-__host__ inline size_t mixed_lds_bytes(uint32_t tile)
+// entry[T] u32, chunk_start[C] u32, chunk_info[C] u32 with C = T/64 + 17
+// (T/64 times the lanes per pair), sorted[T] u16 (first the pairs' sort keys,
+// then the slots in sorted order).
+__host__ __device__ inline uint32_t mixed_chunk_cap(uint32_t tile, uint32_t lg)
 {
-    return sizeof(MixedLds) + 12u * tile + 8u * mixed_chunk_cap(tile) + 2u * tile;
+    return (tile << lg) / 64 + 17;
+}
+
+__host__ inline size_t mixed_lds_bytes(uint32_t tile, uint32_t lg = 0)
+{
+    return sizeof(MixedLds) + 12u * tile + 8u * mixed_chunk_cap(tile, lg) + 2u * tile;
 }
 
 // The tile's pairs: entry[slot] is e | length << 8 until the pair is done, then
@@ -81,15 +85,16 @@ __device__ __forceinline__ PairIdx load_slot(const FilterArgs &a, const TilePair
     return p;
 }
 
-template <int W, int L, bool GENERAL, bool VAR>
+template <int W, int L, bool GENERAL, bool VAR, bool SPLIT>
 __device__ __forceinline__ void run_chunk_pair(const FilterArgs &a, const TilePairs &t,
-                                               uint32_t slot)
+                                               uint32_t slot, uint32_t sub, uint32_t lanes)
 {
     PairData<W> d;
     const PairIdx p = load_slot<W>(a, t, slot, d);
     uint32_t est;
-    const uint32_t res = compute_pair<W, L, GENERAL, VAR>(a, p, d, est);
-    tile_done(t, slot, res, est);
+    const uint32_t res = compute_pair<W, L, GENERAL, VAR, false, SPLIT>(a, p, d, est, sub, lanes);
+    if (sub == 0u)
+        tile_done(t, slot, res, est);
 }
 
 template <int W, int L, bool VAR>
@@ -109,9 +114,10 @@ __device__ __forceinline__ void run_chunk_pair2(const FilterArgs &a, const TileP
     }
 }
 
-template <int WMAX, int L, int PPL, bool VAR>
+template <int WMAX, int L, int PPL, bool VAR, bool SPLIT>
 __device__ __forceinline__ void run_chunk(const FilterArgs &a, const TilePairs &t, uint32_t w,
-                                          uint32_t s0, bool has1, uint32_t s1)
+                                          uint32_t s0, bool has1, uint32_t s1, uint32_t sub,
+                                          uint32_t lanes)
 {
 #define GK_CASE(N)                                                                 \
     case N:                                                                        \
@@ -119,7 +125,7 @@ __device__ __forceinline__ void run_chunk(const FilterArgs &a, const TilePairs &
             if (PPL == 2)                                                          \
                 run_chunk_pair2<(N <= WMAX ? N : 1), L, VAR>(a, t, s0, has1, s1);  \
             else                                                                   \
-                run_chunk_pair<(N <= WMAX ? N : 1), L, false, VAR>(a, t, s0);      \
+                run_chunk_pair<(N <= WMAX ? N : 1), L, false, VAR, SPLIT>(a, t, s0, sub, lanes); \
         }                                                                          \
         break;
     switch (w) {
@@ -164,9 +170,10 @@ __device__ __forceinline__ FilterArgs table_args(const BatchTable *t, uint32_t b
     return a;
 }
 
-template <int WMAX, int L, int PPL, bool VAR = false, bool DIRECT = false>
+// SPLIT: a small batch, 2^x.lg lanes per pair (split_lanes).
+template <int WMAX, int L, int PPL, bool VAR = false, bool DIRECT = false, bool SPLIT = false>
 __global__ __launch_bounds__(256)
-__attribute__((amdgpu_waves_per_eu(WMAX <= 10 && PPL == 1 && !VAR ? 4 : 1)))
+__attribute__((amdgpu_waves_per_eu(WMAX <= 10 && PPL == 1 && !VAR && !SPLIT ? 4 : 1)))
 void k_mixed(FilterArgs a0, MixedArgs x)
 {
     extern __shared__ uint32_t lds_raw[];
@@ -176,8 +183,8 @@ void k_mixed(FilterArgs a0, MixedArgs x)
     t.read = t.pos + x.tile;
     t.entry = t.read + x.tile;
     uint32_t *chunk_start = t.entry + x.tile;
-    uint32_t *chunk_info = chunk_start + mixed_chunk_cap(x.tile);
-    uint16_t *sorted = reinterpret_cast<uint16_t *>(chunk_info + mixed_chunk_cap(x.tile));
+    uint32_t *chunk_info = chunk_start + mixed_chunk_cap(x.tile, SPLIT ? x.lg : 0u);
+    uint16_t *sorted = reinterpret_cast<uint16_t *>(chunk_info + mixed_chunk_cap(x.tile, SPLIT ? x.lg : 0u));
 
     while (true) {
         // (not known to be the same in the next tile's round, so that nothing
@@ -297,7 +304,7 @@ void k_mixed(FilterArgs a0, MixedArgs x)
         //    pairs with the fewest shifts: its idle lanes then wait through
         //    the shortest loop.
         if (tid < 64) {
-            const uint32_t ch = tid == FAR ? 64u : 64u * PPL;
+            const uint32_t ch = SPLIT ? 64u >> x.lg : tid == FAR ? 64u : 64u * PPL;
             const uint32_t w0 = tid <= FAR ? s.wstart[tid] : 0u;
             const uint32_t cnt = tid <= FAR ? s.wstart[tid + 1] - w0 : 0u;
             const uint32_t nch = (cnt + ch - 1) / ch;
@@ -345,14 +352,16 @@ void k_mixed(FilterArgs a0, MixedArgs x)
                 a = table_args(x.table, batch);
             }
             asm volatile("" : "+s"(a.pitch), "+s"(a.rows), "+s"(a.max_read_len));
-            if (lane < cnt) {
-                const uint32_t s0 = sorted[start + lane];
+            const uint32_t lanes = SPLIT ? 1u << x.lg : 1u, sub = lane & (lanes - 1u);
+            const uint32_t at = SPLIT ? lane >> x.lg : lane;
+            if (at < cnt) {
+                const uint32_t s0 = sorted[start + at];
                 if (w == FAR + 1u) {
-                    run_chunk_pair<WMAX, L, true, VAR>(a, t, s0);
+                    run_chunk_pair<WMAX, L, true, VAR, SPLIT>(a, t, s0, sub, lanes);
                 } else {
                     const bool has1 = lane + 64u < cnt;
                     const uint32_t s1 = has1 ? sorted[start + lane + 64u] : s0;
-                    run_chunk<WMAX, L, PPL, VAR>(a, t, w, s0, has1, s1);
+                    run_chunk<WMAX, L, PPL, VAR, SPLIT>(a, t, w, s0, has1, s1, sub, lanes);
                 }
             }
         }
@@ -403,13 +412,16 @@ hipError_t launch_mixed_wl(const FilterArgs &a, const MixedArgs &x, hipStream_t 
         c.est = a.est + first;
         c.accept_bits = a.accept_bits ? a.accept_bits + first / 64 : nullptr;
         const dim3 grid((uint32_t)((n + x.tile - 1) / x.tile));
-        const size_t lds = mixed_lds_bytes(x.tile);
+        const size_t lds = mixed_lds_bytes(x.tile, x.lg);
         bool two = false;
         if constexpr (WMAX <= 10)
             two = x.ppl == 2 && a.flags == 0u;
         if (a.flags != 0u) {
             // Variant semantics: their own kernel, one pair per lane.
             hipLaunchKernelGGL((k_mixed<WMAX, L, 1, true, true>), grid, dim3(256), lds, s, c, x);
+        } else if (x.lg != 0u) {
+            hipLaunchKernelGGL((k_mixed<WMAX, L, 1, false, true, true>), grid, dim3(256), lds, s,
+                               c, x);
         } else if (!two) {
             hipLaunchKernelGGL((k_mixed<WMAX, L, 1, false, true>), grid, dim3(256), lds, s, c, x);
         } else if constexpr (WMAX <= 10) {

@@ -199,11 +199,16 @@ __device__ __forceinline__ void widen(const uint32_t (&A)[W], uint32_t below, ui
 // planes are shifted up so that the last base is bit 31 of the top word, which
 // keeps the masks of both directions in one word and, with one k per step, in
 // scalar registers.
-template <int W, bool ANY, bool REFINE>
+//
+// SPLIT: this lane takes shifts k0, k0 + step, ... only (F is then the AND of
+// those masks and the Hamming mask).
+template <int W, bool ANY, bool REFINE, bool SPLIT>
 __device__ __forceinline__ void near_masks(uint32_t (&rh)[W], uint32_t (&rl)[W],
                                            uint32_t (&gh)[W], uint32_t (&gl)[W], uint32_t m,
-                                           uint32_t kmax, uint32_t (&F)[W])
+                                           uint32_t kmax, uint32_t (&F)[W], uint32_t k0,
+                                           uint32_t step)
 {
+    const uint32_t kfirst = SPLIT ? k0 : 1u, kstep = SPLIT ? step : 1u;
     uint32_t A[W], M[W], sh[W], sl[W];
     mismatch<W>(rh, rl, gh, gl, M);            // Hamming mask (never refined)
     uint32_t first = M[0], last = M[W - 1];    // mask bits 0 and 32W - 1 (centres -1 and 32W)
@@ -214,7 +219,7 @@ __device__ __forceinline__ void near_masks(uint32_t (&rh)[W], uint32_t (&rl)[W],
     // Deletion masks: read[i-k] against window[i].
     uint32_t PA = 0xFFFFFFFFu, PB = 0xFFFFFFFFu;
     const uint32_t vtop = ones_below((int)m - 32 * (W - 1));
-    for (uint32_t k = 1; k <= kmax; ++k) {
+    for (uint32_t k = kfirst; k <= kmax; k += kstep) {
 #pragma unroll
         for (int w = 0; w < W; ++w) {
             sh[w] = w > 0 ? funnel(rh[w], rh[w - 1], 32u - k) : (rh[0] << k);
@@ -262,7 +267,7 @@ __device__ __forceinline__ void near_masks(uint32_t (&rh)[W], uint32_t (&rl)[W],
     for (int w = 0; w < W; ++w)
         A[w] = 0xFFFFFFFFu;
     const uint32_t vlow = 0xFFFFFFFFu << (q & 31u);
-    for (uint32_t k = 1; k <= kmax; ++k) {
+    for (uint32_t k = kfirst; k <= kmax; k += kstep) {
 #pragma unroll
         for (int w = 0; w < W; ++w) {
             sh[w] = w < W - 1 ? funnel(rh[w + 1], rh[w], k) : (rh[W - 1] >> k);
@@ -304,22 +309,6 @@ __device__ __forceinline__ void near_masks(uint32_t (&rh)[W], uint32_t (&rl)[W],
         F[w] &= G[w];
 }
 
-// Fast path: 32(W-1) < m <= 32W and kmax <= 31.
-template <int W, bool REFINE = true>
-__device__ __forceinline__ uint32_t filter_exact(uint32_t (&rh)[W], uint32_t (&rl)[W],
-                                                 uint32_t (&gh)[W], uint32_t (&gl)[W],
-                                                 uint32_t m, uint32_t kmax)
-{
-    uint32_t F[W];
-    near_masks<W, false, REFINE>(rh, rl, gh, gl, m, kmax, F);
-    F[W - 1] &= ones_below((int)m - 32 * (W - 1));
-    uint32_t est = 0;
-#pragma unroll
-    for (int w = 0; w < W; ++w)
-        est += __builtin_popcount(F[w]);
-    return est;
-}
-
 // Read r's plane words 0..W-1 from global memory (words at or beyond the read
 // length are 0), for the general path.
 template <int W, int L>
@@ -336,27 +325,27 @@ __device__ __forceinline__ void load_read(const FilterArgs &a, uint32_t r, uint3
     }
 }
 
-// General path: any m <= 32W and any k <= m-1 <= 511.  Shifts below 32 as
-// near_masks; from 32 bases on whole words move: the read planes are shifted
+// General path: any m <= 32W and any k <= m-1 <= 511, ANDed into acc (bits at or
+// beyond m are left as they come).  Shifts below 32 as near_masks; from 32 bases on whole words move: the read planes are shifted
 // in place by one word each time k passes a multiple of 32, each mask is
 // amended by itself, and the planes are rebuilt between the deletion and the
 // insertion loop: reloaded from the read rows in memory, or, with KEPT (reads
 // that exist only in registers), taken again from the pair's words.
-template <int W, int L, bool REFINE = true, bool KEPT = false>
-__device__ __forceinline__ uint32_t filter_general(const FilterArgs &a, uint32_t r,
-                                                   const uint32_t (&words)[2 * W],
-                                                   uint32_t (&rh)[W], uint32_t (&rl)[W],
-                                                   uint32_t (&gh)[W], uint32_t (&gl)[W],
-                                                   uint32_t m, uint32_t kmax)
+template <int W, int L, bool REFINE, bool KEPT, bool SPLIT>
+__device__ __forceinline__ void general_masks(const FilterArgs &a, uint32_t r,
+                                              const uint32_t (&words)[2 * W], uint32_t (&rh)[W],
+                                              uint32_t (&rl)[W], uint32_t (&gh)[W],
+                                              uint32_t (&gl)[W], uint32_t m, uint32_t kmax,
+                                              uint32_t (&acc)[W], uint32_t k0, uint32_t step)
 {
-    uint32_t V[W], acc[W];
+    uint32_t V[W];
 #pragma unroll
     for (int w = 0; w < W; ++w) {
         V[w] = ones_below((int)m - 32 * w);
         rh[w] &= V[w];
         rl[w] &= V[w];
     }
-    near_masks<W, true, REFINE>(rh, rl, gh, gl, m, kmax < 31u ? kmax : 31u, acc);
+    near_masks<W, true, REFINE, SPLIT>(rh, rl, gh, gl, m, kmax < 31u ? kmax : 31u, acc, k0, step);
 
     if (W > 1 && kmax > 31u) {
         const uint32_t q = 32u * W - m;
@@ -421,12 +410,6 @@ __device__ __forceinline__ uint32_t filter_general(const FilterArgs &a, uint32_t
             amend_and<W>(M, acc, X);
         }
     }
-
-    uint32_t est = 0;
-#pragma unroll
-    for (int w = 0; w < W; ++w)
-        est += __builtin_popcount(acc[w] & V[w]);
-    return est;
 }
 
 // Indices of one pair (first-level loads).
@@ -603,17 +586,21 @@ __device__ __forceinline__ void pair_planes(const PairIdx &p, const PairData<W> 
 // variant semantics of a.flags (GK_FLAG_*); without it a.flags must be 0, and
 // the paper's filter is the only code in the kernel.  KEPT: the read has no
 // rows in memory (a.reads is not used), and the general path rebuilds its
-// planes from d.words.
-template <int W, int L, bool GENERAL = true, bool VAR = false, bool KEPT = false>
+// planes from d.words.  SPLIT: `lanes` neighbouring lanes (2, 4 or 8, aligned)
+// hold the same pair and take its shifts in turn, lane `sub` of them from
+// sub + 1 on; all return the result.
+template <int W, int L, bool GENERAL = true, bool VAR = false, bool KEPT = false,
+          bool SPLIT = false>
 __device__ __forceinline__ uint32_t compute_pair(const FilterArgs &a, const PairIdx &p,
-                                                 const PairData<W> &d, uint32_t &est)
+                                                 const PairData<W> &d, uint32_t &est,
+                                                 uint32_t sub = 0, uint32_t lanes = 1)
 {
     est = GK_EST_NONE;
     uint32_t m;
     const uint32_t gate = pair_gate<W>(a, p, d, m);
     if (gate != PAIR_OK)
         return gate;
-    uint32_t gh[W], gl[W], rh[W], rl[W];
+    uint32_t gh[W], gl[W], rh[W], rl[W], F[W];
     pair_planes<W, L>(p, d, m, gh, gl, rh, rl);
     const uint32_t kmax = p.e < m - 1u ? p.e : m - 1u;
     const bool exact = !GENERAL || (m > 32u * (W - 1) && kmax <= 31u);
@@ -622,6 +609,7 @@ __device__ __forceinline__ uint32_t compute_pair(const FilterArgs &a, const Pair
         rh[W - 1] &= vtop;
         rl[W - 1] &= vtop;
     }
+    bool refine = true;
     if constexpr (VAR) {                       // variants (uniform per launch)
         if (a.flags & GK_FLAG_HAMMING_FASTPATH) {
             uint32_t hd = 0;
@@ -635,15 +623,67 @@ __device__ __forceinline__ uint32_t compute_pair(const FilterArgs &a, const Pair
             }
         }
         if (a.flags & GK_FLAG_NO_REFINE) {
-            est = exact ? filter_exact<W, false>(rh, rl, gh, gl, m, kmax)
-                        : filter_general<W, L, false, KEPT>(a, p.r, d.words, rh, rl, gh, gl,
-                                                                  m, kmax);
-            return est <= p.e ? GK_ACCEPT : GK_REJECT;
+            refine = false;
+            if (exact)
+                near_masks<W, false, false, SPLIT>(rh, rl, gh, gl, m, kmax, F, sub + 1u, lanes);
+            else
+                general_masks<W, L, false, KEPT, SPLIT>(a, p.r, d.words, rh, rl, gh, gl, m, kmax,
+                                                        F, sub + 1u, lanes);
         }
     }
-    est = exact ? filter_exact<W>(rh, rl, gh, gl, m, kmax)
-                : filter_general<W, L, true, KEPT>(a, p.r, d.words, rh, rl, gh, gl, m, kmax);
+    if (refine) {
+        if (exact)
+            near_masks<W, false, true, SPLIT>(rh, rl, gh, gl, m, kmax, F, sub + 1u, lanes);
+        else
+            general_masks<W, L, true, KEPT, SPLIT>(a, p.r, d.words, rh, rl, gh, gl, m, kmax, F,
+                                                   sub + 1u, lanes);
+    }
+    if constexpr (SPLIT) {
+        for (uint32_t o = 1; o < lanes; o <<= 1) {
+#pragma unroll
+            for (int w = 0; w < W; ++w)
+                F[w] &= __shfl_xor(F[w], (int)o, 64);
+        }
+    }
+    est = 0;
+#pragma unroll
+    for (int w = 0; w < W; ++w) {
+        const bool full = !GENERAL && w < W - 1;   // 32(W-1) < m
+        est += __builtin_popcount(full ? F[w] : F[w] & ones_below((int)m - 32 * w));
+    }
     return est <= p.e ? GK_ACCEPT : GK_REJECT;
+}
+
+// Bits 0, step, 2 step, ... of x (step a power of two, the others 0), moved
+// together.
+__device__ __forceinline__ unsigned long long gather_bits(unsigned long long x, uint32_t step)
+{
+    // groups of `width` bits lie at multiples of width * step: join neighbours
+    for (uint32_t width = 1; width * step < 64u; width <<= 1) {
+        const uint32_t dist = width * step;
+        const unsigned long long group = (1ull << width) - 1ull;
+        unsigned long long y = 0;
+        for (uint32_t at = 0; at < 64u; at += 2u * dist)
+            y |= (x >> at & group) << at | (x >> (at + dist) & group) << (at + width);
+        x = y;
+    }
+    return x;
+}
+
+// Accept bits of a wave that holds 64 >> lg pairs, 2^lg lanes (2, 4 or 8) to
+// each; i: the lane's pair, on: its bit, on the first of its lanes only.
+__device__ __forceinline__ void store_split_bits(const FilterArgs &a, uint32_t i, uint32_t lg,
+                                                 bool on)
+{
+    const unsigned long long bits = gather_bits(__ballot(on), 1u << lg);
+    if ((threadIdx.x & 63u) == 0u) {
+        if (lg == 1u)
+            reinterpret_cast<uint32_t *>(a.accept_bits)[i >> 5] = (uint32_t)bits;
+        else if (lg == 2u)
+            reinterpret_cast<uint16_t *>(a.accept_bits)[i >> 4] = (uint16_t)bits;
+        else
+            reinterpret_cast<uint8_t *>(a.accept_bits)[i >> 3] = (uint8_t)bits;
+    }
 }
 
 }  // namespace gkd

@@ -29,9 +29,9 @@ def pairs_of(ref, lengths, n_reads, seed, e_frac=0.12):
                          ids=lambda v: f"max{max(v)}")
 def test_direct_tile_edges(gkctx, ref, lengths):
     gk.gk_load_reference(gkctx, ref)
-    ps = pairs_of(ref, list(lengths), 3000, 61)
+    ps = pairs_of(ref, list(lengths), 12_000, 61)
     want = run_oracle(ref, ps.reads, ps.read_off, ps.pair_read, ps.cand_pos, ps.e)
-    for n in (1, 63, 64, 65, 511, 512, 513, 1024, 1025, 5000):
+    for n in (1, 65, 5000, 24576, 24577, 24833, 25000):
         say(f"case: direct mixed {max(lengths)} n={n}")
         a, s, bits = run_gpu_mixed(gkctx, ps.reads, ps.read_off, ps.pair_read[:n], ps.cand_pos[:n],
                                    ps.e[:n], max_read_len=max(lengths), with_bits=True)
@@ -68,3 +68,46 @@ def test_plain_call_sorted_route(gkctx, ref, layout, identity, flags_known):
     gk.gk_set_option(gkctx, gk.GK_OPT_PAIRS_PER_LANE, 0)
     assert_same(outs[0][0], outs[0][1], outs[1][0], outs[1][1], "sorted vs plain")
     assert np.array_equal(outs[0][2], outs[1][2])
+
+
+@pytest.mark.parametrize("lengths,e", [((100,), None), ((150,), 7), ((250,), 25), ((33, 200, 320), None),
+                                       ((64, 500, 512), None)],
+                         ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else f"e{v}")
+def test_lanes_per_pair(gkctx, ref, lengths, e):
+    """Small batches share a pair's masks among 8, 4 or 2 lanes: batch sizes at
+    and around the rule's limits, and accept bits of partly filled words."""
+    import torch
+    gk.gk_load_reference(gkctx, ref)
+    ps = pairs_of(ref, list(lengths), 25_000, 63, e_frac=0.12)
+    ev = ps.e if e is None else np.full(ps.n_pairs, e, np.uint8)
+    want = run_oracle(ref, ps.reads, ps.read_off, ps.pair_read, ps.cand_pos, ev)
+    dr = device.encode_reads(gkctx, ps.reads, ps.read_off, max_len=max(lengths))
+    text = torch.from_numpy(np.concatenate([ps.reads, np.zeros(64, np.uint8)])).cuda()
+    off = torch.from_numpy(ps.read_off.view(np.int64)).cuda()
+    first = np.unique(ps.pair_read, return_index=True)[1]     # one candidate per read
+    for n in (1, 7, 63, 65, 12288, 12289, 24576, 24577, 49152, 49153):
+        if n <= ps.n_pairs:
+            say(f"case: lanes {lengths} e={e} n={n}")
+            dp = device.upload_pairs(ps.pair_read[:n], ps.cand_pos[:n],
+                                     ev[:n] if e is None else None, with_bits=True)
+            dp.accept_bits.fill_(-1)
+            gk.gk_filter(gkctx, device.batch_for(dr, dp, e_uniform=e or 0), None)
+            torch.cuda.synchronize()
+            check(dp, want[0][:n], want[1][:n], f"plain n={n}")
+        if n <= len(first):
+            sel = first[:n]
+            dp = device.upload_pairs(None, ps.cand_pos[sel], ev[sel] if e is None else None,
+                                     with_bits=True)
+            dp.accept_bits.fill_(-1)
+            gk.gk_filter_ascii(gkctx, device.batch_for(dr, dp, e_uniform=e or 0), text, off, None)
+            torch.cuda.synchronize()
+            check(dp, want[0][sel], want[1][sel], f"ascii n={n}")
+
+
+def check(dp, accept, est, label):
+    a, s = device.results(dp)
+    assert_same(a, s, accept, est, label)
+    got = np.unpackbits(dp.accept_bits.cpu().numpy().view(np.uint8), bitorder="little")
+    n = len(accept)
+    assert np.array_equal(got[:n].astype(bool), (accept == 1) | (accept == 2)), label
+    assert not got[n:].any(), label
