@@ -86,6 +86,15 @@ inline uint32_t split_lanes(uint64_t n_pairs, uint32_t e, uint32_t words)
     return n_pairs <= 49152 && work >= 100u ? 1u : 0u;
 }
 
+// A table of few batches, passed as kernel arguments (at most 4 KiB): the
+// launch then waits for no copy of its table.
+constexpr uint32_t INLINE_BATCHES = 24;
+struct InlineTable {
+    uint32_t n_batches;
+    uint32_t prefix[INLINE_BATCHES + 1];
+    FilterArgs args[INLINE_BATCHES];
+};
+
 // Pairs per tile of the mixed launch for a value of GK_OPT_MIXED_TILE.
 inline uint32_t mixed_tile(uint32_t option) { return option / 4; }
 
@@ -133,12 +142,14 @@ inline bool filter_sorts(bool e_per_pair, uint64_t n_pairs, uint32_t wmax)
 }
 
 struct MixedArgs {
-    const BatchTable *table;     // table form: the device table
+    const BatchTable *table;     // table form: the device table; with n_tiles
+                                 // set, a host table of at most INLINE_BATCHES
     uint32_t *tile_counter;      // table form: zeroed by the launch sequence
     uint32_t tile;               // pairs per tile (multiple of 256, <= 2048)
     uint32_t ppl;                // 1 or 2
     uint32_t sort_e;             // 0 or 1
     uint32_t blocks;             // table form: persistent workgroups
+    uint32_t n_tiles;            // tiles of a host table, else 0
     uint32_t lg;                 // direct form: 2^lg lanes per pair (0, 1 or 2)
 };
 

@@ -21,7 +21,9 @@
 //   direct      one batch, one workgroup per tile, accept bits with the
 //               results: one launch, no scratch;
 //   table       resident workgroups claim tiles of a table of batches from a
-//               device counter, so that one captured graph serves any batches.
+//               device counter, so that one captured graph serves any batches;
+//   inline      one workgroup per tile of a table that comes with the kernel's
+//               arguments.
 #include "gk_pair.h"
 
 namespace gkd {
@@ -138,10 +140,13 @@ __device__ __forceinline__ void run_chunk(const FilterArgs &a, const TilePairs &
 #undef GK_CASE
 }
 
+enum Form { DIRECT, TABLE, INLINE };
+
 // Batch of a tile in a table launch: the last b with prefix[b] <= tile (empty
 // batches share their prefix with the next one, so the last match is the
 // batch that owns the tile).
-__device__ __forceinline__ uint32_t table_batch(const BatchTable *t, uint32_t tile)
+template <typename Table>
+__device__ __forceinline__ uint32_t table_batch(const Table *t, uint32_t tile)
 {
     uint32_t lo = 0, hi = t->n_batches;          // prefix[hi] > tile
     while (hi - lo > 1) {
@@ -171,10 +176,13 @@ __device__ __forceinline__ FilterArgs table_args(const BatchTable *t, uint32_t b
 }
 
 // SPLIT: a small batch, 2^x.lg lanes per pair (split_lanes).
-template <int WMAX, int L, int PPL, bool VAR = false, bool DIRECT = false, bool SPLIT = false>
+struct NoTable {};
+
+template <int WMAX, int L, int PPL, bool VAR = false, Form FORM = TABLE, bool SPLIT = false,
+          typename Batches = NoTable>
 __global__ __launch_bounds__(256)
 __attribute__((amdgpu_waves_per_eu(WMAX <= 10 && PPL == 1 && !VAR && !SPLIT ? 4 : 1)))
-void k_mixed(FilterArgs a0, MixedArgs x)
+void k_mixed(FilterArgs a0, MixedArgs x, Batches batches)
 {
     extern __shared__ uint32_t lds_raw[];
     MixedLds &s = *reinterpret_cast<MixedLds *>(lds_raw);
@@ -190,17 +198,22 @@ void k_mixed(FilterArgs a0, MixedArgs x)
         // (not known to be the same in the next tile's round, so that nothing
         // derived from it is held in registers across the chunks)
         uint32_t tid = threadIdx.x;
-        if (!DIRECT)
+        if (FORM == TABLE)
             asm volatile("" : "+v"(tid));
         const uint32_t lane = tid & 63u;
-        if (!DIRECT && tid == 0)
+        if (FORM == TABLE && tid == 0)
             s.tile = atomicAdd(x.tile_counter, 1u);
         for (uint32_t b = tid; b <= NBINS; b += 256)
             s.hist[b] = 0;
         __syncthreads();
         FilterArgs a = a0;
         uint32_t base = blockIdx.x * x.tile, batch = 0;
-        if constexpr (!DIRECT) {
+        if constexpr (FORM == INLINE) {
+            batch = __builtin_amdgcn_readfirstlane(table_batch(&batches, blockIdx.x));
+            a = batches.args[batch];
+            base = (blockIdx.x - batches.prefix[batch]) * x.tile;
+        }
+        if constexpr (FORM == TABLE) {
             // uniform, so that the batch's arguments come into scalar registers
             const uint32_t tile = __builtin_amdgcn_readfirstlane(s.tile);
             if (tile >= x.table->prefix[x.table->n_batches])
@@ -347,10 +360,12 @@ void k_mixed(FilterArgs a0, MixedArgs x)
             // them (row addresses above all) does not fit the scalar registers
             // when the compiler computes it before the loop.
             FilterArgs a = a0;
-            if constexpr (!DIRECT) {
+            if constexpr (FORM != DIRECT)
                 asm volatile("" : "+s"(batch));
+            if constexpr (FORM == TABLE)
                 a = table_args(x.table, batch);
-            }
+            if constexpr (FORM == INLINE)
+                a = batches.args[batch];
             asm volatile("" : "+s"(a.pitch), "+s"(a.rows), "+s"(a.max_read_len));
             const uint32_t lanes = SPLIT ? 1u << x.lg : 1u, sub = lane & (lanes - 1u);
             const uint32_t at = SPLIT ? lane >> x.lg : lane;
@@ -383,7 +398,7 @@ void k_mixed(FilterArgs a0, MixedArgs x)
                     a.accept_bits[(base + j) >> 6] = bits;
             }
         }
-        if (DIRECT)
+        if (FORM != TABLE)
             break;
         __syncthreads();
     }
@@ -418,14 +433,17 @@ hipError_t launch_mixed_wl(const FilterArgs &a, const MixedArgs &x, hipStream_t 
             two = x.ppl == 2 && a.flags == 0u;
         if (a.flags != 0u) {
             // Variant semantics: their own kernel, one pair per lane.
-            hipLaunchKernelGGL((k_mixed<WMAX, L, 1, true, true>), grid, dim3(256), lds, s, c, x);
+            hipLaunchKernelGGL((k_mixed<WMAX, L, 1, true, DIRECT>), grid, dim3(256), lds, s, c, x,
+                               NoTable{});
         } else if (x.lg != 0u) {
-            hipLaunchKernelGGL((k_mixed<WMAX, L, 1, false, true, true>), grid, dim3(256), lds, s,
-                               c, x);
+            hipLaunchKernelGGL((k_mixed<WMAX, L, 1, false, DIRECT, true>), grid, dim3(256), lds,
+                               s, c, x, NoTable{});
         } else if (!two) {
-            hipLaunchKernelGGL((k_mixed<WMAX, L, 1, false, true>), grid, dim3(256), lds, s, c, x);
+            hipLaunchKernelGGL((k_mixed<WMAX, L, 1, false, DIRECT>), grid, dim3(256), lds, s, c, x,
+                               NoTable{});
         } else if constexpr (WMAX <= 10) {
-            hipLaunchKernelGGL((k_mixed<WMAX, L, 2, false, true>), grid, dim3(256), lds, s, c, x);
+            hipLaunchKernelGGL((k_mixed<WMAX, L, 2, false, DIRECT>), grid, dim3(256), lds, s, c, x,
+                               NoTable{});
         }
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess)
@@ -438,6 +456,21 @@ template <int WMAX, int L>
 hipError_t launch_table_wl(const MixedArgs &x, hipStream_t s)
 {
     FilterArgs none{};
+    if (x.n_tiles != 0u) {
+        const BatchTable *t = x.table;
+        InlineTable in;
+        if (t->n_batches > INLINE_BATCHES || t->prefix[t->n_batches] != x.n_tiles)
+            return hipErrorInvalidValue;
+        in.n_batches = t->n_batches;
+        for (uint32_t b = 0; b < t->n_batches; ++b) {
+            in.prefix[b] = t->prefix[b];
+            in.args[b] = t->args[b];
+        }
+        in.prefix[t->n_batches] = x.n_tiles;
+        hipLaunchKernelGGL((k_mixed<WMAX, L, 1, false, INLINE, false, InlineTable>),
+                           dim3(x.n_tiles), dim3(256), mixed_lds_bytes(x.tile), s, none, x, in);
+        return hipGetLastError();
+    }
     hipLaunchKernelGGL(k_reset, dim3(1), dim3(64), 0, s, x.tile_counter);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess)
@@ -445,12 +478,12 @@ hipError_t launch_table_wl(const MixedArgs &x, hipStream_t s)
     if constexpr (WMAX <= 10) {
         if (x.ppl == 2) {
             hipLaunchKernelGGL((k_mixed<WMAX, L, 2>), dim3(x.blocks), dim3(256),
-                               mixed_lds_bytes(x.tile), s, none, x);
+                               mixed_lds_bytes(x.tile), s, none, x, NoTable{});
             return hipGetLastError();
         }
     }
     hipLaunchKernelGGL((k_mixed<WMAX, L, 1>), dim3(x.blocks), dim3(256), mixed_lds_bytes(x.tile),
-                       s, none, x);
+                       s, none, x, NoTable{});
     return hipGetLastError();
 }
 

@@ -152,7 +152,9 @@ struct gk_server {
     static constexpr uint32_t MAX_COPY_STREAMS = 8;
     hipStream_t s_copy[MAX_COPY_STREAMS] = {};
     uint32_t n_copy = 1;
-    hipStream_t s_compute = nullptr, s_d2h = nullptr;
+    hipStream_t s_compute = nullptr;
+    static constexpr uint32_t N_D2H = 2;
+    hipStream_t s_d2h[N_D2H] = {};       // results out, taken in turn
     uint64_t admitted = 0;                 // requests admitted so far
     std::mutex mu;
     std::condition_variable cv;
@@ -174,6 +176,7 @@ struct gk_server {
     bool buf_busy[2] = {false, false};
     uint32_t *d_counters = nullptr;
     gkd::MixedArgs margs{};
+    bool auto_tile = false;              // no mixed-batch tuning was set
     uint64_t part_pairs = 0, tick_pairs = 0;   // batched mode: part and tick bounds
     uint64_t ticks = 0, tick_req_max = 0, pairs_done = 0;
     std::vector<gk_tick_record> tick_log;  // first TICK_LOG_CAP ticks, in order
@@ -502,13 +505,21 @@ void scheduler_main(gk_server *s)
         gkd::trace_push("gk_server tick");
         gkd::BatchTable *h = s->h_table[t.buf];
         h->n_batches = (uint32_t)t.parts.size();
+        // Few parts go with the launch itself; more take the captured graph,
+        // whose table copy waits its turn behind the requests' copies in (a
+        // burst of 24 requests: the second tick's kernels ended 440 us after
+        // its launch).
+        const bool inline_table = t.parts.size() <= gkd::INLINE_BATCHES && t.pairs > 0;
+        const uint32_t tile = inline_table && s->auto_tile
+                                  ? gkd::mixed_auto_tile(std::max<uint64_t>(t.pairs, 1u << 18), 16)
+                                  : s->margs.tile;
         uint32_t tiles = 0, words = 1;
         for (size_t b = 0; b < t.parts.size(); ++b) {
             const Part &p = t.parts[b];
             words = std::max(words, (p.q->max_len + 31) / 32);
             h->prefix[b] = tiles;
             h->args[b] = args_for(s, p.q, p.first, p.n);
-            tiles += (uint32_t)((p.n + s->margs.tile - 1) / s->margs.tile);
+            tiles += (uint32_t)((p.n + tile - 1) / tile);
         }
         h->prefix[t.parts.size()] = tiles;
         hipError_t e = hipSuccess;
@@ -516,8 +527,15 @@ void scheduler_main(gk_server *s)
             if (e == hipSuccess && p.first == 0)   // a request's loads, once
                 e = hipStreamWaitEvent(s->s_compute, p.q->ready, 0);
         t.t_launch = now_us();
-        if (e == hipSuccess)
+        if (e == hipSuccess && inline_table) {
+            gkd::MixedArgs x = s->margs;
+            x.table = h;
+            x.tile = tile;
+            x.n_tiles = tiles;
+            e = gkd::launch_mixed_table(x, words, GK_READS_SPLIT, s->s_compute);
+        } else if (e == hipSuccess) {
             e = hipGraphLaunch(s->graph[width_class(words)][t.buf], s->s_compute);
+        }
         if (e == hipSuccess)
             e = hipEventRecord(s->tick_done[t.buf], s->s_compute);
         gkd::trace_pop();
@@ -571,12 +589,15 @@ void completer_main(gk_server *s)
             s->cv.notify_all();
             lk.unlock();
         }
+        uint32_t turn = 0;
         for (const Part &p : t.parts)
             if (e == hipSuccess)
-                e = copy_out(p.q, p.first, p.n, s->s_d2h);
-        const hipError_t es = hipStreamSynchronize(s->s_d2h);     // always drained
-        if (e == hipSuccess)
-            e = es;
+                e = copy_out(p.q, p.first, p.n, s->s_d2h[turn++ % gk_server::N_D2H]);
+        for (hipStream_t st : s->s_d2h) {
+            const hipError_t es = hipStreamSynchronize(st);       // always drained
+            if (e == hipSuccess)
+                e = es;
+        }
         if (e == hipSuccess && inject)
             e = hipErrorInvalidValue;
         const int64_t t_copied = now_us();
@@ -607,9 +628,11 @@ void destroy_server(gk_server *s)
     for (hipStream_t st : s->s_copy)
         if (st)
             (void)hipStreamSynchronize(st);
-    for (hipStream_t st : {s->s_compute, s->s_d2h})
+    for (hipStream_t st : s->s_d2h)
         if (st)
             (void)hipStreamSynchronize(st);
+    if (s->s_compute)
+        (void)hipStreamSynchronize(s->s_compute);
     for (int k = 0; k < 2; ++k) {
         for (int c = 0; c < gk_server::WIDTHS; ++c)
             if (s->graph[c][k])
@@ -633,9 +656,11 @@ void destroy_server(gk_server *s)
     for (hipStream_t st : s->s_copy)
         if (st)
             (void)hipStreamDestroy(st);
-    for (hipStream_t st : {s->s_compute, s->s_d2h})
+    for (hipStream_t st : s->s_d2h)
         if (st)
             (void)hipStreamDestroy(st);
+    if (s->s_compute)
+        (void)hipStreamDestroy(s->s_compute);
     delete s;
 }
 
@@ -674,9 +699,11 @@ int gk_server_start(gk_ctx *ctx, uint64_t device_budget_bytes, uint32_t max_slot
     s->n_copy = mode == GK_SERVER_BATCHED ? ctx->server_copy_streams : 1u;
     for (uint32_t k = 0; k < s->n_copy && e == hipSuccess; ++k)
         e = hipStreamCreateWithFlags(&s->s_copy[k], hipStreamNonBlocking);
-    for (hipStream_t *st : {&s->s_compute, &s->s_d2h})
+    if (e == hipSuccess)
+        e = hipStreamCreateWithFlags(&s->s_compute, hipStreamNonBlocking);
+    for (hipStream_t &st : s->s_d2h)
         if (e == hipSuccess)
-            e = hipStreamCreateWithFlags(st, hipStreamNonBlocking);
+            e = hipStreamCreateWithFlags(&st, hipStreamNonBlocking);
     if (e == hipSuccess)
         e = gk_dmalloc(&s->d_counters, sizeof(uint32_t));
     if (e == hipSuccess && mode == GK_SERVER_BATCHED) {
@@ -688,6 +715,7 @@ int gk_server_start(gk_ctx *ctx, uint64_t device_budget_bytes, uint32_t max_slot
         s->margs.tile_counter = s->d_counters;
         s->margs.tile = gkd::mixed_tile(mc.tile);
         s->margs.sort_e = mc.sort_e;
+        s->auto_tile = mc.untouched();
         hipStream_t cap = nullptr;
         if (e == hipSuccess)
             e = hipStreamCreateWithFlags(&cap, hipStreamNonBlocking);
