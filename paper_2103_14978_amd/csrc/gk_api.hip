@@ -40,9 +40,7 @@ void free_reference(gk_ctx *ctx)
         (void)hipFree(ctx->ref_planes);
     if (ctx->ref_unk)
         (void)hipFree(ctx->ref_unk);
-    if (ctx->ref_planes_b)
-        (void)hipFree(ctx->ref_planes_b);
-    ctx->ref_planes_b = nullptr;
+    ctx->ref_b_words = 0;
     if (ctx->ref_unk_lines)
         (void)hipFree(ctx->ref_unk_lines);
     ctx->ref_unk_lines = nullptr;
@@ -59,12 +57,9 @@ hipError_t finish_reference(gk_ctx *ctx, uint64_t words, uint64_t alloc_words,
                             uint64_t unknown)
 {
     const uint64_t k = gkd::REF_SHIFT_WORDS;
-    hipError_t e = gk_dmalloc(&ctx->ref_planes_b, alloc_words * sizeof(uint2));
-    if (e == hipSuccess)
-        e = hipMemset(ctx->ref_planes_b + (alloc_words - k), 0, k * sizeof(uint2));
-    if (e == hipSuccess)
-        e = hipMemcpy(ctx->ref_planes_b, ctx->ref_planes + k, (alloc_words - k) * sizeof(uint2),
-                      hipMemcpyDeviceToDevice);
+    ctx->ref_b_words = (uint32_t)alloc_words;
+    hipError_t e = hipMemcpy(ctx->ref_planes + alloc_words, ctx->ref_planes + k,
+                             (alloc_words - k) * sizeof(uint2), hipMemcpyDeviceToDevice);
     const uint64_t line_words = ((words + gkd::LINE_WORDS - 1) / gkd::LINE_WORDS + 63) / 64 + 1;
     if (e == hipSuccess)
         e = gk_dmalloc(&ctx->ref_unk_lines, line_words * sizeof(unsigned long long));
@@ -330,14 +325,14 @@ int gk_load_reference(gk_ctx *ctx, const char *ascii, uint64_t len)
     free_reference(ctx);
 
     const uint64_t words = (len + 31) / 32;
-    const uint64_t alloc_words = words + gkd::REF_PAD_WORDS;
-    hipError_t e = gk_dmalloc(&ctx->ref_planes, alloc_words * sizeof(uint2));
+    const uint64_t alloc_words = (words + gkd::REF_PAD_WORDS + 15) & ~uint64_t(15);
+    hipError_t e = gk_dmalloc(&ctx->ref_planes, 2 * alloc_words * sizeof(uint2));
     if (e != hipSuccess)
         return free_reference(ctx), hip_fail(ctx, e, "gk_load_reference: hipMalloc planes");
     e = gk_dmalloc(&ctx->ref_unk, alloc_words * sizeof(uint32_t));
     if (e != hipSuccess)
         return free_reference(ctx), hip_fail(ctx, e, "gk_load_reference: hipMalloc unknown");
-    e = hipMemset(ctx->ref_planes, 0, alloc_words * sizeof(uint2));
+    e = hipMemset(ctx->ref_planes, 0, 2 * alloc_words * sizeof(uint2));
     if (e == hipSuccess)
         e = hipMemset(ctx->ref_unk, 0, alloc_words * sizeof(uint32_t));
     if (e == hipSuccess)
@@ -404,14 +399,14 @@ int gk_load_reference_2bit(gk_ctx *ctx, const uint32_t *packed, uint64_t len, ui
     free_reference(ctx);
 
     const uint64_t words = (len + 31) / 32;
-    const uint64_t alloc_words = words + gkd::REF_PAD_WORDS;
-    hipError_t e = gk_dmalloc(&ctx->ref_planes, alloc_words * sizeof(uint2));
+    const uint64_t alloc_words = (words + gkd::REF_PAD_WORDS + 15) & ~uint64_t(15);
+    hipError_t e = gk_dmalloc(&ctx->ref_planes, 2 * alloc_words * sizeof(uint2));
     if (e != hipSuccess)
         return free_reference(ctx), hip_fail(ctx, e, "gk_load_reference_2bit: hipMalloc planes");
     e = gk_dmalloc(&ctx->ref_unk, alloc_words * sizeof(uint32_t));
     if (e != hipSuccess)
         return free_reference(ctx), hip_fail(ctx, e, "gk_load_reference_2bit: hipMalloc unknown");
-    e = hipMemset(ctx->ref_planes, 0, alloc_words * sizeof(uint2));
+    e = hipMemset(ctx->ref_planes, 0, 2 * alloc_words * sizeof(uint2));
     if (e == hipSuccess)
         e = hipMemset(ctx->ref_unk, 0, alloc_words * sizeof(uint32_t));
     if (e == hipSuccess)
@@ -541,7 +536,7 @@ int prepare_batch(gk_ctx *ctx, const gk_batch *b, const char *who, gkd::FilterAr
         return fail(ctx, GK_EINVAL, w + ": NULL read buffer");
     a.flags = b->flags;
     a.ref_planes = ctx->ref_planes;
-    a.ref_planes_b = ctx->ref_planes_b;
+    a.ref_b_words = ctx->ref_b_words;
     a.ref_unk = ctx->ref_unk;
     a.ref_unk_lines = ctx->ref_unk_lines;
     a.ref_len = ctx->ref_len;

@@ -24,21 +24,22 @@ constexpr uint32_t GK_PPL_RESIDENT = 65536;  // pairs-per-lane value meaning
                                              // "one residency of the device"
 
 // Second copy of the planes, shifted by half a 128-byte cache line:
-// ref_planes_b[j] = ref_planes[j + REF_SHIFT_WORDS].  A window gather of up to
-// 9 words that crosses a line of ref_planes lies within one line of
-// ref_planes_b, so every window of up to 256 bases costs one line fetch.
+// word j of the copy is ref_planes[j + REF_SHIFT_WORDS].  A window gather of up
+// to 9 words that crosses a line of ref_planes lies within one line of the
+// copy, so every window of up to 256 bases costs one line fetch.  The copy
+// follows in the same allocation, ref_b_words (a multiple of 16) words on.
 constexpr uint32_t LINE_WORDS = 16;          // uint2 words per 128-byte line
 constexpr uint32_t LINE_BASES = 32 * LINE_WORDS;
 constexpr uint32_t REF_SHIFT_WORDS = 8;
 
 struct FilterArgs {
     const uint2 *ref_planes;
-    const uint2 *ref_planes_b;  // ref_planes shifted by REF_SHIFT_WORDS
     const uint32_t *ref_unk;
     const unsigned long long *ref_unk_lines;  // bit L: bases [512 L, 512 L + 512)
                                               // hold an unknown base
     uint64_t ref_len;
     uint32_t ref_has_unknown;
+    uint32_t ref_b_words;       // where the shifted copy begins
     uint32_t n_reads;
     uint32_t pitch;
     uint32_t e_uniform;

@@ -27,8 +27,8 @@ __global__ __launch_bounds__(256) void k_filter_single(FilterArgs a)
         load_data<W>(a, p, d);
         uint32_t est;
         res = compute_pair<W, L, true, VAR>(a, p, d, est);
-        __builtin_nontemporal_store((uint8_t)res, a.accept + i);
-        __builtin_nontemporal_store((uint16_t)est, a.est + i);
+        put(a.accept, i, (uint8_t)res);
+        put(a.est, i, (uint16_t)est);
     }
     if (a.accept_bits) {
         const unsigned long long bits = __ballot(i < n && (res == GK_ACCEPT || res == GK_UNDEFINED));
@@ -55,8 +55,8 @@ __global__ __launch_bounds__(256) void k_filter_split(FilterArgs a, uint32_t lg)
         uint32_t est;
         res = compute_pair<W, L, true, false, false, true>(a, p, d, est, sub, lanes);
         if (sub == 0u) {
-            a.accept[i] = (uint8_t)res;
-            a.est[i] = (uint16_t)est;
+            put(a.accept, i, (uint8_t)res);
+            put(a.est, i, (uint16_t)est);
         }
     }
     if (a.accept_bits) {
@@ -88,8 +88,8 @@ __global__ __launch_bounds__(256) void k_filter(FilterArgs a)
             const PairIdx in = load_idx(a, min(i + 2 * stride, n - 1));
             uint32_t est;
             const uint32_t res = compute_pair<W, L>(a, ia, da, est);
-            __builtin_nontemporal_store((uint8_t)res, a.accept + i);
-            __builtin_nontemporal_store((uint16_t)est, a.est + i);
+            put(a.accept, i, (uint8_t)res);
+            put(a.est, i, (uint16_t)est);
             if (a.accept_bits) {
                 const unsigned long long bits = __ballot(res == GK_ACCEPT || res == GK_UNDEFINED);
                 if ((threadIdx.x & 63u) == 0u)
@@ -105,8 +105,8 @@ __global__ __launch_bounds__(256) void k_filter(FilterArgs a)
             const PairIdx in = load_idx(a, min(i + 2 * stride, n - 1));
             uint32_t est;
             const uint32_t res = compute_pair<W, L>(a, ib, db, est);
-            __builtin_nontemporal_store((uint8_t)res, a.accept + i);
-            __builtin_nontemporal_store((uint16_t)est, a.est + i);
+            put(a.accept, i, (uint8_t)res);
+            put(a.est, i, (uint16_t)est);
             if (a.accept_bits) {
                 const unsigned long long bits = __ballot(res == GK_ACCEPT || res == GK_UNDEFINED);
                 if ((threadIdx.x & 63u) == 0u)

@@ -94,8 +94,8 @@ void k_filter_ascii(FilterArgs a, const uint8_t *ascii, const uint64_t *read_off
     if (i < n) {
         PairIdx p;
         p.r = i;
-        p.pos = a.cand_pos[i];
-        p.e = a.e_pair ? (uint32_t)a.e_pair[i] : a.e_uniform;
+        p.pos = elem(a.cand_pos, i);
+        p.e = a.e_pair ? (uint32_t)elem(a.e_pair, i) : a.e_uniform;
         PairData<W> d;
         load_window<W>(a, p.pos, d);
         load_unknown_lines<W>(a, p.pos, d);
@@ -143,8 +143,8 @@ void k_filter_ascii(FilterArgs a, const uint8_t *ascii, const uint64_t *read_off
             est = GK_EST_NONE;
         }
         if (sub == 0u) {
-            __builtin_nontemporal_store((uint8_t)res, a.accept + i);
-            __builtin_nontemporal_store((uint16_t)est, a.est + i);
+            put(a.accept, i, (uint8_t)res);
+            put(a.est, i, (uint16_t)est);
         }
     }
     if (SPLIT && a.accept_bits) {

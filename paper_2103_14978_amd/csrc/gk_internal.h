@@ -79,7 +79,8 @@ struct gk_ctx {
     uint64_t ref_words = 0;     // ceil(ref_len / 32)
     uint64_t ref_unknown = 0;   // unknown bases
     uint2 *ref_planes = nullptr;
-    uint2 *ref_planes_b = nullptr;            // planes shifted by half a line
+    uint32_t ref_b_words = 0;                 // where their shifted copy begins in
+                                              // ref_planes (gkd::REF_SHIFT_WORDS)
     uint32_t *ref_unk = nullptr;
     unsigned long long *ref_unk_lines = nullptr;  // one bit per 512 bases
     unsigned long long *d_counter = nullptr;  // scratch for the unknown count

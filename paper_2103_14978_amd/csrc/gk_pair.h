@@ -325,8 +325,8 @@ __device__ __forceinline__ void load_read(const FilterArgs &a, uint32_t r, uint3
     }
 }
 
-// General path: any m <= 32W and any k <= m-1 <= 511, ANDed into acc (bits at or
-// beyond m are left as they come).  Shifts below 32 as near_masks; from 32 bases on whole words move: the read planes are shifted
+// General path: any m <= 32W and any k <= m-1 <= 511, in acc (bits at or beyond m
+// are 0).  Shifts below 32 as near_masks; from 32 bases on whole words move: the read planes are shifted
 // in place by one word each time k passes a multiple of 32, each mask is
 // amended by itself, and the planes are rebuilt between the deletion and the
 // insertion loop: reloaded from the read rows in memory, or, with KEPT (reads
@@ -344,6 +344,8 @@ __device__ __forceinline__ void general_masks(const FilterArgs &a, uint32_t r,
         V[w] = ones_below((int)m - 32 * w);
         rh[w] &= V[w];
         rl[w] &= V[w];
+        gh[w] &= V[w];
+        gl[w] &= V[w];
     }
     near_masks<W, true, REFINE, SPLIT>(rh, rl, gh, gl, m, kmax < 31u ? kmax : 31u, acc, k0, step);
 
@@ -410,6 +412,9 @@ __device__ __forceinline__ void general_masks(const FilterArgs &a, uint32_t r,
             amend_and<W>(M, acc, X);
         }
     }
+#pragma unroll
+    for (int w = 0; w < W; ++w)
+        acc[w] &= V[w];
 }
 
 // Indices of one pair (first-level loads).
@@ -432,12 +437,33 @@ struct PairData {
 
 // Plain loads throughout: marking the read words and pair entries that are used
 // once as non-temporal moved the 100-base launch by 0.7% and no other.
+
+// base[i] for i < 2^30 (reads, and the pairs of a launch) of elements of up to
+// 4 bytes: a 32-bit offset from a scalar base, no 64-bit address per lane.
+// With the window loads by one base for both copies of the planes, that is 2%
+// fewer vector instructions per pair: 3e6 pairs of 150 bases at e = 7 over
+// 775 MB of planes went from 86.6 to 83.7 us, 2^23 of 250 at e = 25 from 746 to
+// 736, a mixed batch of 2^24 (64 to 300 bases) from 807 to 789.
+template <typename T>
+__device__ __forceinline__ T elem(const T *base, uint32_t i)
+{
+    return *reinterpret_cast<const T *>(reinterpret_cast<const char *>(base) +
+                                        (uint32_t)(i * (uint32_t)sizeof(T)));
+}
+
+template <typename T>
+__device__ __forceinline__ void put(T *base, uint32_t i, T v)
+{
+    __builtin_nontemporal_store(v, reinterpret_cast<T *>(reinterpret_cast<char *>(base) +
+                                                         (uint32_t)(i * (uint32_t)sizeof(T))));
+}
+
 __device__ __forceinline__ PairIdx load_idx(const FilterArgs &a, uint32_t i)
 {
     PairIdx p;
-    p.r = a.pair_read ? a.pair_read[i] : i;
-    p.pos = a.cand_pos[i];
-    p.e = a.e_pair ? (uint32_t)a.e_pair[i] : a.e_uniform;
+    p.r = a.pair_read ? elem(a.pair_read, i) : i;
+    p.pos = elem(a.cand_pos, i);
+    p.e = a.e_pair ? (uint32_t)elem(a.e_pair, i) : a.e_uniform;
     return p;
 }
 
@@ -466,15 +492,16 @@ __device__ __forceinline__ void load_window(const FilterArgs &a, uint32_t pos, P
     const uint32_t nw = ((pos & 31u) + longest<W>(a) + 31u) >> 5;
     const bool use_b = (w0 >= REF_SHIFT_WORDS) & ((w0 & (LINE_WORDS - 1u)) + nw > LINE_WORDS);
     // REF_SHIFT_WORDS is even: an even word of one copy is one of the other
-    const uint2 *src = use_b ? a.ref_planes_b : a.ref_planes;
-    const uint4 *q = reinterpret_cast<const uint4 *>(
-        src + ((use_b ? w0 - REF_SHIFT_WORDS : w0) & ~1u));
+    // (words of both copies number less than 2^29: a 32-bit byte offset)
+    const char *planes = reinterpret_cast<const char *>(a.ref_planes);
+    const uint32_t first = ((use_b ? w0 + a.ref_b_words - REF_SHIFT_WORDS : w0) & ~1u) * 8u;
     // A pair of words the window does not reach is replaced by its last one (no
     // branch, no other line); its bases lie beyond every read's end.
     const uint32_t last = ((pos & 63u) + longest<W>(a) - 1u) >> 6;
 #pragma unroll
     for (int j = 0; j < (W + 3) / 2; ++j)
-        d.win[j] = q[(uint32_t)j < last ? (uint32_t)j : last];
+        d.win[j] = *reinterpret_cast<const uint4 *>(
+            planes + (uint32_t)(first + 16u * ((uint32_t)j < last ? (uint32_t)j : last)));
 }
 
 template <int W>
@@ -485,8 +512,8 @@ __device__ __forceinline__ void load_unknown_lines(const FilterArgs &a, uint32_t
     if (a.ref_has_unknown) {
         pos = pos < a.ref_len ? pos : 0u;
         const uint32_t *lines = reinterpret_cast<const uint32_t *>(a.ref_unk_lines);
-        d.unk0 = lines[pos / LINE_BASES >> 5];
-        d.unk1 = lines[(uint32_t)(((uint64_t)pos + longest<W>(a) - 1u) / LINE_BASES >> 5)];
+        d.unk0 = elem(lines, pos / LINE_BASES >> 5);
+        d.unk1 = elem(lines, (uint32_t)(((uint64_t)pos + longest<W>(a) - 1u) / LINE_BASES >> 5));
     }
 }
 
@@ -499,7 +526,7 @@ __device__ __forceinline__ void load_words(const FilterArgs &a, uint32_t r, Pair
 #pragma unroll
     for (int j = 0; j < 2 * W; ++j) {
         const uint32_t row = (uint32_t)j < a.rows ? (uint32_t)j : a.rows - 1u;
-        d.words[j] = a.reads[(size_t)row * a.pitch + r];
+        d.words[j] = elem(a.reads + (size_t)row * a.pitch, r);
     }
 }
 
@@ -510,8 +537,8 @@ __device__ __forceinline__ void load_data(const FilterArgs &a, const PairIdx &p,
     load_words<W>(a, r, d);
     const uint8_t *flag = a.read_has_n ? a.read_has_n
                                        : reinterpret_cast<const uint8_t *>(a.read_len);
-    d.m = (uint32_t)a.read_len[r];
-    d.has_n = (uint32_t)flag[r];
+    d.m = (uint32_t)elem(a.read_len, r);
+    d.has_n = (uint32_t)elem(flag, r);
     load_window<W>(a, p.pos, d);
     load_unknown_lines<W>(a, p.pos, d);
 }
@@ -553,10 +580,10 @@ __device__ __forceinline__ uint32_t pair_gate(const FilterArgs &a, const PairIdx
     return PAIR_OK;
 }
 
-// Read and window bit-planes of a pair that passed pair_gate: the window
-// words are funnel-shifted by pos mod 32 and cleared at or beyond m.
+// Read and window bit-planes of a pair that passed pair_gate, the window words
+// funnel-shifted by pos mod 32.  Bits at or beyond m are left as they come.
 template <int W, int L>
-__device__ __forceinline__ void pair_planes(const PairIdx &p, const PairData<W> &d, uint32_t m,
+__device__ __forceinline__ void pair_planes(const PairIdx &p, const PairData<W> &d,
                                             uint32_t (&gh)[W], uint32_t (&gl)[W],
                                             uint32_t (&rh)[W], uint32_t (&rl)[W])
 {
@@ -572,9 +599,8 @@ __device__ __forceinline__ void pair_planes(const PairIdx &p, const PairData<W> 
     }
 #pragma unroll
     for (int w = 0; w < W; ++w) {
-        const uint32_t v = ones_below((int)m - 32 * w);
-        gh[w] = funnel(win[w + 1].x, win[w].x, s) & v;
-        gl[w] = funnel(win[w + 1].y, win[w].y, s) & v;
+        gh[w] = funnel(win[w + 1].x, win[w].x, s);
+        gl[w] = funnel(win[w + 1].y, win[w].y, s);
         planes_from_words<L>(d.words[2 * w], d.words[2 * w + 1], rh[w], rl[w]);
     }
 }
@@ -601,13 +627,15 @@ __device__ __forceinline__ uint32_t compute_pair(const FilterArgs &a, const Pair
     if (gate != PAIR_OK)
         return gate;
     uint32_t gh[W], gl[W], rh[W], rl[W], F[W];
-    pair_planes<W, L>(p, d, m, gh, gl, rh, rl);
+    pair_planes<W, L>(p, d, gh, gl, rh, rl);
     const uint32_t kmax = p.e < m - 1u ? p.e : m - 1u;
     const bool exact = !GENERAL || (m > 32u * (W - 1) && kmax <= 31u);
+    const uint32_t vtop = ones_below((int)m - 32 * (W - 1));
     if (exact) {
-        const uint32_t vtop = ones_below((int)m - 32 * (W - 1));
         rh[W - 1] &= vtop;
         rl[W - 1] &= vtop;
+        gh[W - 1] &= vtop;
+        gl[W - 1] &= vtop;
     }
     bool refine = true;
     if constexpr (VAR) {                       // variants (uniform per launch)
@@ -645,12 +673,12 @@ __device__ __forceinline__ uint32_t compute_pair(const FilterArgs &a, const Pair
                 F[w] &= __shfl_xor(F[w], (int)o, 64);
         }
     }
+    if (exact)
+        F[W - 1] &= vtop;
     est = 0;
 #pragma unroll
-    for (int w = 0; w < W; ++w) {
-        const bool full = !GENERAL && w < W - 1;   // 32(W-1) < m
-        est += __builtin_popcount(full ? F[w] : F[w] & ones_below((int)m - 32 * w));
-    }
+    for (int w = 0; w < W; ++w)
+        est += __builtin_popcount(F[w]);
     return est <= p.e ? GK_ACCEPT : GK_REJECT;
 }
 

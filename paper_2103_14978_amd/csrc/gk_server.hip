@@ -252,7 +252,7 @@ gkd::FilterArgs args_for(const gk_server *s, const Req *q, uint64_t first, uint6
     const gk_ctx *c = s->ctx;
     gkd::FilterArgs a{};
     a.ref_planes = c->ref_planes;
-    a.ref_planes_b = c->ref_planes_b;
+    a.ref_b_words = c->ref_b_words;
     a.ref_unk = c->ref_unk;
     a.ref_unk_lines = c->ref_unk_lines;
     a.ref_len = c->ref_len;

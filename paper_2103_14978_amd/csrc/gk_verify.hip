@@ -330,7 +330,12 @@ __device__ __forceinline__ bool load_planes(const FilterArgs &a, const PairIdx &
     uint32_t m;
     const bool ok = pair_gate<W>(a, p, d, m) == PAIR_OK;
     uint32_t gh[W], gl[W], rh[W], rl[W];
-    pair_planes<W, L>(p, d, m, gh, gl, rh, rl);
+    pair_planes<W, L>(p, d, gh, gl, rh, rl);
+#pragma unroll
+    for (int w = 0; w < W; ++w) {
+        gh[w] &= ones_below((int)m - 32 * w);
+        gl[w] &= ones_below((int)m - 32 * w);
+    }
 #pragma unroll
     for (int w = 0; w < W; ++w) {
         col.read[w * 64] = make_uint2(rh[w], rl[w]);
@@ -592,7 +597,12 @@ __device__ __forceinline__ uint32_t verify_pair(const PairIdx &p, const PairData
                                                 uint32_t m, uint32_t e)
 {
     uint32_t gh[W], gl[W], rh[W], rl[W];
-    pair_planes<W, L>(p, d, m, gh, gl, rh, rl);
+    pair_planes<W, L>(p, d, gh, gl, rh, rl);
+#pragma unroll
+    for (int w = 0; w < W; ++w) {
+        gh[w] &= ones_below((int)m - 32 * w);
+        gl[w] &= ones_below((int)m - 32 * w);
+    }
     const uint32_t m0 = __builtin_amdgcn_readfirstlane(m);
     if (__ballot(m != m0) == 0ull)
         return e <= 15u ? band_distance<W, uint32_t>(rh, rl, gh, gl, m0, e)
