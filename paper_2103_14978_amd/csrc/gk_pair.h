@@ -309,6 +309,229 @@ __device__ __forceinline__ void near_masks(uint32_t (&rh)[W], uint32_t (&rl)[W],
         F[w] &= G[w];
 }
 
+// ---- masks of up to BLOCK_KMAX shifts in blocks of 64 bits ------------------
+//
+// near_masks spends two of its eight instructions per word on the neighbours
+// M[i-1] and M[i+1], a funnel shift each.  A 64-bit shift by a constant issues
+// at the rate of a 32-bit one (35 T lanes/s both), so on blocks of two words
+// the neighbours cost half, if no bit has to come from another block.  Blocks
+// therefore overlap by two bits: word w starts at position 32w - w_off(w), and
+// centres are collected at the position of their last (deletions) or first
+// (insertions) base, so that the bits a block lacks are the ones its neighbour
+// has.  The words then hold block_cap positions: 64, 126, 188, 250 ... of an
+// even number of words.  2^23 pairs of 250 bases at e = 25 went from 737 to 699 us, a
+// mixed batch of 2^24 pairs (64 to 300 bases) from 785 to 776.  Reads of the last
+// few lengths of a word count (127, 128, 157-160, 251-256, ...) stay with near_masks.
+//
+// Laying out the blocks and going back costs about 11 instructions per word,
+// and a shift (two masks) saves two per word, less two: from 7 shifts on at 8
+// words, 9 at 5.  With every wave on blocks 250 bases at e = 25 gained 4.7% and
+// 150 at e = 7 or 100 at e = 5 lost 1.3%, so a wave takes them from BLOCK_KMIN
+// shifts on, if all its pairs fit (lanes on both ways would run both).  Lanes
+// that share a pair's shifts have too few each.
+constexpr uint32_t BLOCK_KMAX = 30;          // shifts whose edges fit one word
+constexpr uint32_t BLOCK_KMIN = 10;
+constexpr int BLOCK_WMIN = 4;
+
+__host__ __device__ constexpr uint32_t w_off(int w) { return 2u * (uint32_t)(w / 2); }
+
+template <int W>
+__device__ __forceinline__ constexpr uint32_t block_cap()
+{
+    return 32u * W - w_off(W - 1);
+}
+
+// Plane words to block words.
+template <int W>
+__device__ __forceinline__ void to_blocks(uint32_t (&x)[W])
+{
+#pragma unroll
+    for (int w = W - 1; w >= 2; --w)
+        x[w] = funnel(x[w], x[w - 1], 32u - w_off(w));
+}
+
+// The 32 positions below block word w >= 1, and the 32 above it.
+template <int W>
+__device__ __forceinline__ uint32_t below(const uint32_t (&x)[W], int w)
+{
+    return w % 2 ? x[w - 1] : funnel(x[w - 1], x[w - 2], 30);
+}
+
+template <int W>
+__device__ __forceinline__ uint32_t above(const uint32_t (&x)[W], int w)
+{
+    if (w == W - 1)
+        return 0u;
+    return w % 2 ? funnel(w + 2 < W ? x[w + 2] : 0u, x[w + 1], 2) : x[w + 1];
+}
+
+// Block words shifted up by q < 32 positions.
+template <int W>
+__device__ __forceinline__ void blocks_up(uint32_t (&x)[W], uint32_t q)
+{
+    if (q != 0u) {
+#pragma unroll
+        for (int w = W - 1; w >= 1; --w)
+            x[w] = funnel(x[w], below<W>(x, w), 32u - q);
+        x[0] <<= q;
+    }
+}
+
+// M of the next position below (UP) or above in the block, and of the one after.
+template <int W, bool UP>
+__device__ __forceinline__ void block_centres(const uint32_t (&M)[W], uint32_t (&one)[W],
+                                              uint32_t (&two)[W])
+{
+    // (opaque: a right shift by a constant becomes a funnel and a shift)
+    uint32_t by1 = 1u, by2 = 2u;
+    asm("" : "+s"(by1), "+s"(by2));
+#pragma unroll
+    for (int w = 0; w + 1 < W; w += 2) {
+        const uint64_t x = (uint64_t)M[w + 1] << 32 | M[w];
+        const uint64_t y = UP ? x << 1 : x >> by1, z = UP ? x << 2 : x >> by2;
+        one[w] = (uint32_t)y;
+        one[w + 1] = (uint32_t)(y >> 32);
+        two[w] = (uint32_t)z;
+        two[w + 1] = (uint32_t)(z >> 32);
+    }
+    if constexpr (W % 2) {
+        one[W - 1] = UP ? M[W - 1] << 1 : M[W - 1] >> 1;
+        two[W - 1] = UP ? M[W - 1] << 2 : M[W - 1] >> 2;
+    }
+}
+
+// near_masks with refinement, for 32(W-1) < m <= block_cap and
+// kmax <= min(BLOCK_KMAX, m - 1).
+template <int W>
+__device__ __forceinline__ void block_masks(uint32_t (&rh)[W], uint32_t (&rl)[W],
+                                            uint32_t (&gh)[W], uint32_t (&gl)[W], uint32_t m,
+                                            uint32_t kmax, uint32_t (&F)[W])
+{
+    constexpr uint32_t OFF = w_off(W - 1);
+    uint32_t A[W], M[W], one[W], two[W], sh[W], sl[W], nh[W], nl[W];
+    to_blocks<W>(rh);
+    to_blocks<W>(rl);
+    to_blocks<W>(gh);
+    to_blocks<W>(gl);
+
+    // Hamming and deletion masks: read[i-k] against window[i], centre i at bit
+    // i + 1.  Above the top word: centres block_cap - 1 (tail) and block_cap (last).
+    mismatch<W>(rh, rl, gh, gl, M);
+    block_centres<W, true>(M, one, two);
+    uint32_t last = M[W - 1], tail = M[W - 1] | one[W - 1];
+#pragma unroll
+    for (int w = 0; w < W; ++w) {
+        A[w] = M[w] | one[w] | two[w];
+        nh[w] = w > 0 ? below<W>(rh, w) : 0u;
+        nl[w] = w > 0 ? below<W>(rl, w) : 0u;
+    }
+    uint32_t PA = 0xFFFFFFFFu, PB = 0xFFFFFFFFu;
+    const uint32_t vtop = ones_below((int)m - 32 * (W - 1) + (int)OFF);
+    for (uint32_t k = 1; k <= kmax; ++k) {
+#pragma unroll
+        for (int w = 0; w < W; ++w) {
+            sh[w] = w > 0 ? funnel(rh[w], nh[w], 32u - k) : rh[0] << k;
+            sl[w] = w > 0 ? funnel(rl[w], nl[w], 32u - k) : rl[0] << k;
+        }
+        mismatch<W>(sh, sl, gh, gl, M);
+        M[W - 1] &= vtop;                      // bases moved past the read end
+        last &= M[W - 1];
+        block_centres<W, true>(M, one, two);
+        tail &= M[W - 1] | one[W - 1];
+#pragma unroll
+        for (int w = 0; w < W; ++w) {
+            const uint32_t c = M[w] | one[w] | two[w];
+            if (w == 0) {
+                A[0] &= c | ((4u << k) - 1u);
+                PA &= c | ~(2u << k);
+                PB &= c | ~(1u << k);
+            } else {
+                A[w] &= c;
+            }
+        }
+    }
+    {   // back to plane words, then widened: F[i] = A[i] & A[i+1] & A[i+2]
+        const uint32_t over = tail >> 31 | (last >> 31) << 1;
+        uint32_t a[W + 1];
+#pragma unroll
+        for (int w = 0; w < W; ++w) {
+            const uint32_t next = w == W - 1 ? over : w % 2 ? A[w + 1] >> 2 : A[w + 1];
+            a[w] = funnel(next, A[w], w_off(w));
+        }
+        a[W] = OFF == 0u ? over : 0u;
+#pragma unroll
+        for (int w = 0; w < W; ++w)
+            F[w] = a[w] & funnel(a[w + 1], a[w], 1) & funnel(a[w + 1], a[w], 2);
+        F[0] &= PA & (PA >> 1 | 0x80000000u) & PB;
+    }
+
+    // Insertion masks: read[i+k] against window[i], last base at block_cap - 1,
+    // first base in bit q, centre i at bit i - 1.  Below bit 0: centres 0
+    // (head) and -1 (first).
+    const uint32_t q = block_cap<W>() - m;
+    blocks_up<W>(rh, q);
+    blocks_up<W>(rl, q);
+    blocks_up<W>(gh, q);
+    blocks_up<W>(gl, q);
+    uint32_t head = 0xFFFFFFFFu, first = 0xFFFFFFFFu;
+    PA = PB = 0xFFFFFFFFu;
+#pragma unroll
+    for (int w = 0; w < W; ++w) {
+        A[w] = 0xFFFFFFFFu;
+        nh[w] = above<W>(rh, w);
+        nl[w] = above<W>(rl, w);
+    }
+    const uint32_t vlow = 0xFFFFFFFFu << q;
+    for (uint32_t k = 1; k <= kmax; ++k) {
+#pragma unroll
+        for (int w = 0; w < W; ++w) {
+            sh[w] = w < W - 1 ? funnel(nh[w], rh[w], k) : rh[W - 1] >> k;
+            sl[w] = w < W - 1 ? funnel(nl[w], rl[w], k) : rl[W - 1] >> k;
+        }
+        mismatch<W>(sh, sl, gh, gl, M);
+        M[0] &= vlow;                          // bases moved past the read start
+        first &= M[0];
+        block_centres<W, false>(M, one, two);
+        head &= M[0] | one[0];
+#pragma unroll
+        for (int w = 0; w < W; ++w) {
+            const uint32_t c = M[w] | one[w] | two[w];
+            if (w == W - 1) {
+                A[W - 1] &= c | (0xFFFFFFFFu << (30u - k));
+                PA &= c | ~(1u << (30u - k));
+                PB &= c | ~(1u << (31u - k));
+            } else {
+                A[w] &= c;
+            }
+        }
+    }
+    uint32_t G[W];
+    {   // G[i] = A[i] & A[i-1] & A[i-2]
+        uint32_t a[W];
+#pragma unroll
+        for (int w = 0; w < W; ++w) {
+            if (w % 2 && w < W - 1)
+                a[w] = funnel(A[w + 1] >> 2, (A[w] & 0x3FFFFFFFu) | A[w + 1] << 30, w_off(w));
+            else
+                a[w] = funnel(w < W - 1 ? A[w + 1] : 0u, A[w], w_off(w));
+        }
+        const uint32_t under = head << 31 | (first & 1u) << 30;
+#pragma unroll
+        for (int w = 0; w < W; ++w) {
+            const uint32_t prev = w > 0 ? a[w - 1] : under;
+            G[w] = a[w] & funnel(a[w], prev, 31) & funnel(a[w], prev, 30);
+        }
+        const uint32_t R = PA & (PA << 1 | 1u) & PB;
+        G[W - 1] &= OFF == 0u ? R : funnel(0xFFFFFFFFu, R, OFF);
+        if constexpr (OFF != 0u)
+            G[W - 2] &= funnel(R, 0xFFFFFFFFu, OFF);
+    }
+    shift_down<W, false>(G, q);
+#pragma unroll
+    for (int w = 0; w < W; ++w)
+        F[w] &= G[w];
+}
+
 // Read r's plane words 0..W-1 from global memory (words at or beyond the read
 // length are 0), for the general path.
 template <int W, int L>
@@ -325,12 +548,13 @@ __device__ __forceinline__ void load_read(const FilterArgs &a, uint32_t r, uint3
     }
 }
 
-// General path: any m <= 32W and any k <= m-1 <= 511, in acc (bits at or beyond m
-// are 0).  Shifts below 32 as near_masks; from 32 bases on whole words move: the read planes are shifted
-// in place by one word each time k passes a multiple of 32, each mask is
-// amended by itself, and the planes are rebuilt between the deletion and the
-// insertion loop: reloaded from the read rows in memory, or, with KEPT (reads
-// that exist only in registers), taken again from the pair's words.
+// General path: any m <= 32W and any k <= m-1 <= 511, in acc (bits at or
+// beyond m are 0).  Shifts below 32 as near_masks; from 32 bases on whole
+// words move: the read planes are shifted in place by one word each time k
+// passes a multiple of 32, each mask is amended by itself, and the planes are
+// rebuilt between the deletion and the insertion loop: reloaded from the read
+// rows in memory, or, with KEPT (reads that exist only in registers), taken
+// again from the pair's words.
 template <int W, int L, bool REFINE, bool KEPT, bool SPLIT>
 __device__ __forceinline__ void general_masks(const FilterArgs &a, uint32_t r,
                                               const uint32_t (&words)[2 * W], uint32_t (&rh)[W],
@@ -660,7 +884,16 @@ __device__ __forceinline__ uint32_t compute_pair(const FilterArgs &a, const Pair
         }
     }
     if (refine) {
-        if (exact)
+        uint32_t blocks = 0u;
+        if constexpr (W >= BLOCK_WMIN && !SPLIT) {   // (one way for the whole wave)
+            blocks = __ballot(!(exact && m <= block_cap<W>() && kmax <= BLOCK_KMAX)) == 0ull &&
+                     __ballot(kmax >= BLOCK_KMIN) != 0ull;
+            // (opaque: a branch known to be uniform took 25 more registers)
+            asm("" : "+v"(blocks));
+        }
+        if (blocks != 0u)
+            block_masks<W>(rh, rl, gh, gl, m, kmax, F);
+        else if (exact)
             near_masks<W, false, true, SPLIT>(rh, rl, gh, gl, m, kmax, F, sub + 1u, lanes);
         else
             general_masks<W, L, true, KEPT, SPLIT>(a, p.r, d.words, rh, rl, gh, gl, m, kmax, F,
