@@ -35,7 +35,9 @@ HBM_PEAK_GBS = 8000.0
 def ops_per_pair(m: int, e: int) -> int:
     """Algorithmic int32 lane-ops per pair: (2e+1) masks x W32 words x 14 ops
     (2 read-plane funnels, 2 compare, 9 amendment, 1 AND), plus 6 per word
-    and 16 per pair for the window gather, count and stores."""
+    and 16 per pair for the window gather, count and stores.  This is the
+    filter's definition, mask by mask; the kernels collect centres of three
+    zeros instead and issue 8 instructions per mask-word."""
     w = (m + 31) // 32
     return 14 * (2 * e + 1) * w + 6 * w + 16
 
@@ -130,13 +132,13 @@ CALIB_KINDS = {0: "v_bfi_b32", 1: "v_alignbit_b32", 2: "v_xor_b32", 3: "v_and_or
                8: "v_xor_b32_e64", 9: "v_add_u32", 10: "v_perm_b32", 11: "v_bcnt_u32_b32"}
 
 # The VALU instructions of the filter's per-mask loops (the deletion and
-# insertion loops of the fast path, 96 instructions per pass of both), by the
+# insertion loops of near_masks, 75 instructions per pass of both), by the
 # calibrated kind each issues like, from the gfx950 assembly of
-# k_filter_single<4>: funnel shifts, three-input logic, two-input logic,
-# shifts (left and right), and-or / or3, and two compares (taken at the
-# and-or rate).
-FILTER_LOOP_MIX = {"v_alignbit_b32": 37, "v_bitop3_b32": 26, "v_xor_b32": 9, "v_and_b32": 3,
-                   "v_lshlrev_b32": 13, "v_and_or_b32": 7, "v_or3_b32": 1}
+# k_filter_single<4>: funnel shifts, three-input logic, two-input logic (xor,
+# or), shifts (left and right), shift-or, or3, and two compares (taken at the
+# and-or rate, as shift-or).
+FILTER_LOOP_MIX = {"v_alignbit_b32": 24, "v_bitop3_b32": 24, "v_xor_b32": 10, "v_and_b32": 5,
+                   "v_lshlrev_b32": 7, "v_and_or_b32": 3, "v_or3_b32": 2}
 
 
 def mix_peak(rates: dict, mix: dict = FILTER_LOOP_MIX) -> float:
