@@ -60,6 +60,24 @@ size_t verify_lds_bytes(uint32_t words, uint32_t tile)
     return sizeof(VerifyLds) + 4u * wave_planes(words) * sizeof(uint2) + 2u * tile * 2u;
 }
 
+// Tile of a batch: verify_tile's, and from 2^22 pairs on up to 8192 while as many
+// workgroups fit a compute unit.  Longer lists have fewer waves of mixed lengths
+// and thresholds: 2^24 pairs of 64 to 300 bases with a threshold per pair, a
+// third listed, 1,123, 981 and 996 us with 2048, 4096 and 8192 pairs, a seventh
+// listed 730, 622 and 602 (two workgroups each); but 2^24 of 250 bases 1,155,
+// 1,442 and 1,617 (three, two and two).
+uint32_t tile_of(uint64_t n_pairs, uint32_t words)
+{
+    const size_t lds = 160u * 1024u;
+    uint32_t tile = verify_tile(n_pairs);
+    if (n_pairs >= (1u << 22)) {
+        const size_t fit = lds / verify_lds_bytes(words, tile);
+        while (tile < 8192u && lds / verify_lds_bytes(words, 2u * tile) == fit)
+            tile *= 2u;
+    }
+    return tile;
+}
+
 // A lane's column of its wave's planes: the read's words at read[w * 64], the
 // window's at text[w * 64].
 struct Column {
@@ -366,6 +384,12 @@ __device__ __forceinline__ bool load_planes_w(const FilterArgs &a, const PairIdx
     return false;
 }
 
+// Bin of an entry: words of the read, e.
+__device__ __forceinline__ uint32_t entry_key(uint32_t en)
+{
+    return (((en & 0x3FFu) + 31u) / 32u - 1u) * 32u + (en >> 10);
+}
+
 template <int WMAX, int L>
 __global__ __launch_bounds__(256) void k_verify_tile(FilterArgs a, const uint8_t *accept,
                                                      uint16_t *dist, uint32_t tile,
@@ -403,14 +427,12 @@ __global__ __launch_bounds__(256) void k_verify_tile(FilterArgs a, const uint8_t
             const uint32_t j = j0 + 256u * q;
             if (j >= tile)
                 break;
-            uint32_t en = NOT_LISTED, key = NOT_LISTED;
+            uint32_t en = NOT_LISTED;
             if (on[q] && m[q] != 0u && m[q] <= a.max_read_len) {
                 en = m[q] | (e[q] << 10);
-                key = ((m[q] + 31u) / 32u - 1u) * 32u + e[q];
-                atomicAdd(&s.hist[key], 1u);
+                atomicAdd(&s.hist[entry_key(en)], 1u);
             }
             entry[j] = (uint16_t)en;
-            list[j] = (uint16_t)key;               // until step 3
         }
     }
     __syncthreads();
@@ -441,19 +463,14 @@ __global__ __launch_bounds__(256) void k_verify_tile(FilterArgs a, const uint8_t
             run += local[q];
         }
     }
-    uint32_t key8[8];
-#pragma unroll
-    for (int q = 0; q < 8; ++q) {
-        const uint32_t j = tid + 256u * q;
-        key8[q] = j < tile ? list[j] : NOT_LISTED;
-    }
     __syncthreads();
 
     // 3. slots in key order
-#pragma unroll
-    for (int q = 0; q < 8; ++q)
-        if (key8[q] != NOT_LISTED)
-            list[atomicAdd(&s.hist[key8[q]], 1u)] = (uint16_t)(tid + 256u * q);
+    for (uint32_t j = tid; j < tile; j += 256) {
+        const uint32_t en = entry[j];
+        if (en != NOT_LISTED)
+            list[atomicAdd(&s.hist[entry_key(en)], 1u)] = (uint16_t)j;
+    }
     __syncthreads();
 
     // 4. waves take 64 at a time from the end of the list
@@ -973,7 +990,7 @@ hipError_t list_l(const FilterArgs &a, const uint8_t *accept, uint16_t *dist, ui
 hipError_t launch_verify(const FilterArgs &a, const uint8_t *accept, uint16_t *dist,
                          uint32_t words, uint32_t layout, hipStream_t s)
 {
-    const uint32_t tile = verify_tile(a.n_pairs);
+    const uint32_t tile = tile_of(a.n_pairs, words);
     return layout == GK_READS_INTERLEAVED
                ? tile_l<GK_READS_INTERLEAVED>(a, accept, dist, words, tile, s)
                : tile_l<GK_READS_SPLIT>(a, accept, dist, words, tile, s);
