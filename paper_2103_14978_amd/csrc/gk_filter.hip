@@ -60,7 +60,6 @@ __global__ __launch_bounds__(256) void k_filter_split(FilterArgs a, uint32_t lg)
         }
     }
     if (a.accept_bits) {
-        // (the grid covers whole words)
         store_split_bits(a, i, lg, sub == 0u && i < n &&
                                        (res == GK_ACCEPT || res == GK_UNDEFINED));
     }

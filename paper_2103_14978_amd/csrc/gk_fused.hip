@@ -148,7 +148,6 @@ void k_filter_ascii(FilterArgs a, const uint8_t *ascii, const uint64_t *read_off
         }
     }
     if (SPLIT && a.accept_bits) {
-        // (the grid covers whole words)
         store_split_bits(a, i, lg, sub == 0u && i < n &&
                                        (res == GK_ACCEPT || res == GK_UNDEFINED));
     } else if (a.accept_bits) {

@@ -932,12 +932,16 @@ __device__ __forceinline__ unsigned long long gather_bits(unsigned long long x, 
 }
 
 // Accept bits of a wave that holds 64 >> lg pairs, 2^lg lanes (2, 4 or 8) to
-// each; i: the lane's pair, on: its bit, on the first of its lanes only.
+// each; i: the lane's pair, on: its bit, on the first of its lanes only.  The
+// grid holds every bit of the bitmap's words, and whole workgroups of it: with
+// two lanes per pair a workgroup is two words wide, and the second word of the
+// last one may lie past the bitmap.
 __device__ __forceinline__ void store_split_bits(const FilterArgs &a, uint32_t i, uint32_t lg,
                                                  bool on)
 {
     const unsigned long long bits = gather_bits(__ballot(on), 1u << lg);
-    if ((threadIdx.x & 63u) == 0u) {
+    const uint32_t end = ((uint32_t)a.n_pairs + 63u) & ~63u;
+    if ((threadIdx.x & 63u) == 0u && i < end) {
         if (lg == 1u)
             reinterpret_cast<uint32_t *>(a.accept_bits)[i >> 5] = (uint32_t)bits;
         else if (lg == 2u)
