@@ -487,11 +487,13 @@ __global__ __launch_bounds__(256) void k_verify_tile(FilterArgs a, const uint8_t
             break;
         const uint32_t at = c + lane;
         const bool have = at < total;
-        const uint32_t slot = list[have ? total - 1u - at : total - 1u];
-        const uint32_t en = entry[slot];
-        const uint32_t e = have ? en >> 10 : 0u;
+        // Lanes past the list's end load the wave's first pair, whose loads are
+        // in flight anyway, and take no part: its entry may hold a result by now.
+        const uint32_t slot = list[have ? total - 1u - at : total - 1u - c];
+        const uint32_t en = have ? entry[slot] : 0u;
+        const uint32_t e = en >> 10;
         PairIdx p = load_idx(a, base + slot);
-        p.e = en >> 10;
+        p.e = e;
         FilterArgs ac = a;     // (nor the row addresses of every width)
         asm volatile("" : "+s"(ac.pitch), "+s"(ac.rows), "+s"(ac.max_read_len));
         const uint32_t w = wave_max(((en & 0x3FFu) + 31u) / 32u);
