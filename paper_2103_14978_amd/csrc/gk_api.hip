@@ -759,37 +759,57 @@ int gk_verify(gk_ctx *ctx, const gk_batch *b, const uint8_t *accept, uint16_t *d
     if (!g.ok)
         return fail(ctx, GK_EDEVICE, "gk_verify: hipSetDevice failed");
     const uint32_t words = (b->max_read_len + 31) / 32;
-    const bool lists = gkd::verify_lists(b->e != nullptr, b->e_uniform, b->n_pairs);
-    gk_detail_log(ctx, "gk_verify: %llu pairs, %s, %s", (unsigned long long)b->n_pairs,
-                  accept ? "accepted ones" : "every one",
-                  lists ? "one list" : "listed by tile");
     hipError_t e;
     if (!ctx->d_verify_count) {
         e = gk_dmalloc(&ctx->d_verify_count, sizeof(uint32_t));
         if (e != hipSuccess)
             return hip_fail(ctx, e, "gk_verify: hipMalloc count");
     }
+    // A caller's graph would hold the scratch's address, which a later, larger
+    // call replaces: under capture the tile form, which has none.
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    bool lists = gkd::verify_lists(a);
+    if (lists && hipStreamIsCapturing((hipStream_t)stream, &capture) != hipSuccess) {
+        (void)hipGetLastError();
+        lists = false;
+    }
+    lists = lists && capture == hipStreamCaptureStatusNone;
+    gkd::VerifyScratch x{};
     if (lists) {
-        // The pair list (one word per pair of a chunk of up to 2^30) and one
-        // word per 4096 of those pairs for the listing's counts.
-        const uint64_t need = std::min<uint64_t>(b->n_pairs, 1ull << 30);
+        const uint64_t n = std::min<uint64_t>(a.n_pairs, 1ull << 30), groups = (n + 4095) / 4096;
+        const uint64_t bins = (n + groups + 3) & ~uint64_t(3);
+        const uint64_t need =
+            !a.e_pair ? n + groups
+                      : bins + gkd::VERIFY_BIN_WORDS +
+                            (uint64_t)a.n_reads * gkd::verify_read_stride(a.rows);
         if (need > ctx->verify_cap) {
             if (ctx->d_verify_list)
                 (void)hipFree(ctx->d_verify_list);
             ctx->d_verify_list = nullptr;
             ctx->verify_cap = 0;
-            e = gk_dmalloc(&ctx->d_verify_list, (need + (need + 4095) / 4096) * sizeof(uint32_t));
-            if (e != hipSuccess)
+            e = gk_dmalloc(&ctx->d_verify_list, need * sizeof(uint32_t));
+            if (e == hipSuccess) {
+                ctx->verify_cap = need;
+            } else if (e == hipErrorOutOfMemory) {
+                (void)hipGetLastError();     // the tile form needs none
+                lists = false;
+            } else {
                 return hip_fail(ctx, e, "gk_verify: hipMalloc list");
-            ctx->verify_cap = need;
+            }
         }
-        const gkd::VerifyScratch x{ctx->d_verify_list, ctx->d_verify_list + ctx->verify_cap,
-                                   ctx->d_verify_count};
+        if (lists) {
+            uint32_t *const l = ctx->d_verify_list;
+            x = {l, l + n, ctx->d_verify_count, l + bins, l + bins + gkd::VERIFY_BIN_WORDS};
+        }
+    }
+    gk_detail_log(ctx, "gk_verify: %llu pairs, %s, %s", (unsigned long long)b->n_pairs,
+                  accept ? "accepted ones" : "every one",
+                  lists ? "one list" : "listed by tile");
+    if (lists)
         e = gkd::launch_verify_listed(a, accept, dist, words, b->read_layout, x, ctx->cu_count,
                                       (hipStream_t)stream);
-    } else {
+    else
         e = gkd::launch_verify(a, accept, dist, words, b->read_layout, (hipStream_t)stream);
-    }
     if (e != hipSuccess)
         return hip_fail(ctx, e, "gk_verify: launch");
     return GK_OK;

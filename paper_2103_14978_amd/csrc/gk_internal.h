@@ -110,10 +110,10 @@ struct gk_ctx {
     bool table_used[TABLE_RING] = {};
     uint32_t table_next = 0;
     HostPipe host;                            // gk_filter_host
-    uint32_t *d_verify_list = nullptr;        // gk_verify: listed pairs (verify_cap
-                                              // words), per-workgroup counts
+    uint32_t *d_verify_list = nullptr;        // gk_verify: listed pairs and counts, reads
+                                              // row by row (gkd::VerifyScratch)
     uint32_t *d_verify_count = nullptr;       // listed pairs
-    uint64_t verify_cap = 0;
+    uint64_t verify_cap = 0;                  // words of d_verify_list
 };
 
 // gk_tune_mixed's use of its cache (environment GK_AUTOTUNE=use|refresh|off):

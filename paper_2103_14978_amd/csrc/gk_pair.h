@@ -754,11 +754,31 @@ __device__ __forceinline__ void load_words(const FilterArgs &a, uint32_t r, Pair
     }
 }
 
+// The same from reads in rows of a.pitch words (a multiple of 4), one run of
+// 16-byte loads per read.
 template <int W>
+__device__ __forceinline__ void load_words_rowwise(const FilterArgs &a, uint32_t r, PairData<W> &d)
+{
+    const uint4 *q = reinterpret_cast<const uint4 *>(a.reads + (size_t)r * a.pitch);
+#pragma unroll
+    for (int j = 0; j < 2 * W; j += 4) {
+        const uint4 v = q[(uint32_t)j < a.pitch ? (uint32_t)j / 4u : a.pitch / 4u - 1u];
+        const uint32_t w4[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            if (j + k < 2 * W)
+                d.words[j + k] = w4[k];
+    }
+}
+
+template <int W, bool ROWWISE = false>
 __device__ __forceinline__ void load_data(const FilterArgs &a, const PairIdx &p, PairData<W> &d)
 {
     const uint32_t r = p.r < a.n_reads ? p.r : 0u;
-    load_words<W>(a, r, d);
+    if constexpr (ROWWISE)
+        load_words_rowwise<W>(a, r, d);
+    else
+        load_words<W>(a, r, d);
     const uint8_t *flag = a.read_has_n ? a.read_has_n
                                        : reinterpret_cast<const uint8_t *>(a.read_len);
     d.m = (uint32_t)elem(a.read_len, r);

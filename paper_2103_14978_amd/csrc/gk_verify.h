@@ -12,13 +12,18 @@ namespace gkd {
 hipError_t launch_verify(const FilterArgs &a, const uint8_t *accept, uint16_t *dist,
                          uint32_t words, uint32_t layout, hipStream_t s);
 
-// The same through one list of the whole batch's pairs, for a batch with one
-// threshold (a.e_pair NULL, a.e_uniform <= GK_VERIFY_MAX_E).
+// The same through one list of the whole batch's pairs: of a batch with one
+// threshold (a.e_uniform <= GK_VERIFY_MAX_E), or with a threshold per pair, a
+// read index per pair and n_reads > 0.
 struct VerifyScratch {
     uint32_t *list;      // min(n_pairs, 2^30) words
-    uint32_t *groups;    // a word per 4096 of those pairs, rounded up
+    uint32_t *groups;    // one threshold: a word per 4096 of those pairs, rounded up
     uint32_t *count;     // one word
+    uint32_t *bins;      // a threshold per pair: VERIFY_BIN_WORDS words
+    uint32_t *reads;     // the same: n_reads * verify_read_stride(rows) words, 16-byte aligned
 };
+constexpr uint32_t VERIFY_BIN_WORDS = 3u * 512u * 32u;
+inline uint32_t verify_read_stride(uint32_t rows) { return (rows + 3u) & ~3u; }
 hipError_t launch_verify_listed(const FilterArgs &a, const uint8_t *accept, uint16_t *dist,
                                 uint32_t words, uint32_t layout, const VerifyScratch &x, int cus,
                                 hipStream_t s);
@@ -33,16 +38,32 @@ inline uint32_t verify_tile(uint64_t n_pairs)
          : n_pairs < (3u << 18) ? 1024u : 2048u;
 }
 
-// Whether a batch is listed as a whole.  Where the band's column loop is the
-// whole cost, planes in registers and full waves beat the tile form: 2^22 pairs
-// of 150 bases at e = 15 148 against 180 us, of 250 at e = 25 518 against 599,
-// of 100 at e = 10 85 against 98; at e <= 7 (furthest-reaching points) 63
-// against 76 us the other way.  Its four launches take 20 us before any work,
-// so small batches stay with one.
-inline bool verify_lists(bool e_per_pair, uint32_t e, uint64_t n_pairs)
+// Whether a batch is listed as a whole.
+//
+// One threshold of 8 or more: the band's column loop is the whole cost, and
+// planes in registers and full waves beat the tile form: 2^22 pairs of 150 bases
+// at e = 15 148 against 180 us, of 250 at e = 25 518 against 599, of 100 at e = 10
+// 85 against 98.  One threshold up to 7: full waves, however few of the pairs are
+// listed: 2^22 pairs of 100 bases at e = 5 57 against 67 us, 2^26 of 250 at e = 7
+// 1,742 against 2,351 with a third listed and 620 against 1,096 with a fifteenth.
+// The four launches take 20 us before any work, so smaller batches stay with one.
+//
+// A threshold per pair: the list is in order of (words, e) over the batch, which
+// takes each read's candidates apart, so the reads are copied row by row first.
+// From about 12 candidates per read on that pays at any share listed (16 and 24
+// to 28 per read, tile against list: 2^22 pairs 199 and 161 us, 219 and 143; 2^26
+// pairs 2,603 and 2,314, 2,477 and 2,044), with 7 only at some (2^22 pairs 218
+// and 190 us with a fifth listed, 97 and 108 with a twentieth), with 3 at none.
+inline bool verify_lists(const FilterArgs &a)
 {
-    return !e_per_pair && e >= 8 && e <= GK_VERIFY_MAX_E &&
-           n_pairs >= (e >= 16 ? 1u << 17 : e >= 12 ? 1u << 18 : 1u << 19);
+    if (a.e_pair)
+        return a.pair_read && a.n_reads > 0 && a.n_pairs >= (3u << 20) &&
+               a.n_pairs / 12u >= a.n_reads;
+    const uint32_t e = a.e_uniform;
+    return e <= GK_VERIFY_MAX_E && a.n_pairs >= (e >= 16  ? 1u << 17
+                                                 : e >= 12 ? 1u << 18
+                                                 : e >= 8  ? 1u << 19
+                                                           : 1u << 22);
 }
 
 }  // namespace gkd

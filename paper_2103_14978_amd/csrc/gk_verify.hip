@@ -33,6 +33,8 @@
 // first took four to six (2^22 pairs of 100 bases at e = 5: 76 -> 63 us, 1,000
 // pairs 22 -> 9; 2^20 pairs of mixed lengths and thresholds 113 -> 72, 1,000
 // pairs 98 -> 39).
+#include <algorithm>
+
 #include "gk_pair.h"
 #include "gk_verify.h"
 
@@ -340,11 +342,11 @@ __device__ __forceinline__ uint32_t banded(const Column &col, uint32_t m, bool h
 
 // Loads one pair and puts its planes into the lane's column.  Returns whether
 // the pair can be compared.
-template <int W, int L>
+template <int W, int L, bool ROWWISE>
 __device__ __forceinline__ bool load_planes(const FilterArgs &a, const PairIdx &p, const Column &col)
 {
     PairData<W> d;
-    load_data<W>(a, p, d);
+    load_data<W, ROWWISE>(a, p, d);
     uint32_t m;
     const bool ok = pair_gate<W>(a, p, d, m) == PAIR_OK;
     uint32_t gh[W], gl[W], rh[W], rl[W];
@@ -364,14 +366,14 @@ __device__ __forceinline__ bool load_planes(const FilterArgs &a, const PairIdx &
     return ok;
 }
 
-template <int WMAX, int L>
+template <int WMAX, int L, bool ROWWISE>
 __device__ __forceinline__ bool load_planes_w(const FilterArgs &a, const PairIdx &p, uint32_t w,
                                               const Column &col)
 {
 #define GK_CASE(N)                                                                 \
     case N:                                                                        \
         if (N <= WMAX)                                                             \
-            return load_planes<(N <= WMAX ? N : 1), L>(a, p, col);           \
+            return load_planes<(N <= WMAX ? N : 1), L, ROWWISE>(a, p, col);  \
         break;
     switch (w) {
         GK_CASE(1) GK_CASE(2) GK_CASE(3) GK_CASE(4) GK_CASE(5) GK_CASE(6) GK_CASE(7) GK_CASE(8)
@@ -382,6 +384,30 @@ __device__ __forceinline__ bool load_planes_w(const FilterArgs &a, const PairIdx
     }
 #undef GK_CASE
     return false;
+}
+
+// Distances of a wave's pairs, one per lane: len the read's length where the
+// lane has a pair with p.e <= GK_VERIFY_MAX_E, else 0 (p is then any pair whose
+// loads may be issued).
+template <int WMAX, int L, bool ROWWISE = false>
+__device__ __forceinline__ uint32_t wave_distances(const FilterArgs &a, const PairIdx &p,
+                                                   uint32_t len, const Column &col)
+{
+    FilterArgs ac = a;         // (nor the row addresses of every width)
+    asm volatile("" : "+s"(ac.pitch), "+s"(ac.rows), "+s"(ac.max_read_len));
+    const uint32_t e = len != 0u ? p.e : 0u;
+    const uint32_t w = wave_max((len + 31u) / 32u);
+    const uint32_t E = wave_max(e);
+    const bool ok = load_planes_w<WMAX, L, ROWWISE>(ac, p, w, col) && len != 0u;
+    const uint32_t m = ok ? len : 0u;
+    uint32_t d;
+    if (E <= FURTHEST_MAX_E)
+        d = furthest_distance<FURTHEST_MAX_E / 2>(col, (int)m, e, E);
+    else if (E <= 15u)
+        d = banded<uint32_t>(col, m, ok, e, E, w);
+    else
+        d = banded<B64>(col, m, ok, e, E, w);
+    return ok ? d : GK_EST_NONE;
 }
 
 // Bin of an entry: words of the read, e.
@@ -491,24 +517,11 @@ __global__ __launch_bounds__(256) void k_verify_tile(FilterArgs a, const uint8_t
         // in flight anyway, and take no part: its entry may hold a result by now.
         const uint32_t slot = list[have ? total - 1u - at : total - 1u - c];
         const uint32_t en = have ? entry[slot] : 0u;
-        const uint32_t e = en >> 10;
         PairIdx p = load_idx(a, base + slot);
-        p.e = e;
-        FilterArgs ac = a;     // (nor the row addresses of every width)
-        asm volatile("" : "+s"(ac.pitch), "+s"(ac.rows), "+s"(ac.max_read_len));
-        const uint32_t w = wave_max(((en & 0x3FFu) + 31u) / 32u);
-        const uint32_t E = wave_max(e);
-        const bool ok = load_planes_w<WMAX, L>(ac, p, w, col);
-        const int m = ok && have ? (int)(en & 0x3FFu) : 0;
-        uint32_t d;
-        if (E <= FURTHEST_MAX_E)
-            d = furthest_distance<FURTHEST_MAX_E / 2>(col, m, e, E);
-        else if (E <= 15u)
-            d = banded<uint32_t>(col, (uint32_t)m, ok && have, e, E, w);
-        else
-            d = banded<B64>(col, (uint32_t)m, ok && have, e, E, w);
+        p.e = en >> 10;
+        const uint32_t d = wave_distances<WMAX, L>(a, p, en & 0x3FFu, col);
         if (have)
-            entry[slot] = (uint16_t)(ok ? d : GK_EST_NONE);
+            entry[slot] = (uint16_t)d;
     }
     __syncthreads();
 
@@ -557,10 +570,11 @@ hipError_t tile_l(const FilterArgs &a, const uint8_t *accept, uint16_t *dist, ui
 
 // ---- one list over the whole batch ---------------------------------------
 //
-// Large batches under one threshold of 8 and more: the band's column loop is
-// the whole cost, and it runs fastest with the planes in registers (no LDS
-// but the tile form's, whose columns leave 3 waves per SIMD at 8 words) and
-// full waves from one list.
+// Large batches (verify_lists).  Under one threshold of 8 and more the band's
+// column loop is the whole cost, and it runs fastest with the planes in
+// registers (no LDS but the tile form's, whose columns leave 3 waves per SIMD at
+// 8 words) and full waves from one list; smaller thresholds and batches with a
+// threshold per pair take the tile form's algorithms in full waves.
 
 // Read bases are taken from [32 zero bits | plane words 0..W-1 | zeros]: for
 // text column j = 32 blk + c + 1 the band starts at extended bit
@@ -655,14 +669,13 @@ __global__ __launch_bounds__(256) void k_verify_list(FilterArgs a, const uint32_
 // k_select_count stores each workgroup's count, k_select_scan turns the
 // counts into offsets (and the total into *count), k_select_write puts each
 // workgroup's pairs at its offset through LDS: in pair order when they all
-// have one sort key, else ordered by key (read length; with a per-pair e,
-// also whether e > 15), so that the waves of the verify kernel see one
-// length (its fast path needs it).  VEC needs accept
-// and dist aligned to 16 bytes; the host checks.
+// have one read length, else ordered by it, so that the waves of the verify
+// kernel see one length (its fast path needs it).  VEC needs accept and dist
+// aligned to 16 bytes; the host checks.
 constexpr uint32_t SEL_PER_LANE = 16u, SEL_PER_GROUP = 256u * SEL_PER_LANE;
 
 // Bit j of the result: pair i0 + j is listed.  With fill, the 16 dist entries
-// are set to GK_EST_NONE first (k_verify overwrites the listed ones later).
+// are set to GK_EST_NONE first (the listed ones are overwritten later).
 template <bool VEC>
 __device__ __forceinline__ uint32_t select_bits(const uint8_t *accept, uint32_t n, uint32_t i0,
                                                 uint16_t *dist, bool fill)
@@ -893,6 +906,183 @@ __global__ __launch_bounds__(256) void k_select_write(FilterArgs a, const uint8_
     }
 }
 
+// ---- listing by (words of the read, e) over the whole batch ------------------
+//
+// With a threshold per pair a 4096-pair group lists a few hundred pairs over as
+// many (words, e) bins, so sorting within groups leaves nearly every wave mixed.
+// These kernels sort the listed pairs of the whole batch: each group counts its
+// pairs per bin in LDS and adds the counts to one of BIN_COPIES copies of the
+// bins' counts (by group number, so that no count is added to by more than
+// 1 / BIN_COPIES of the groups); a scan turns the counts into starts, bin by bin
+// and copy by copy; each group then reserves its run in its copy of each bin
+// with one atomic and writes its pairs there (the order within a bin does not
+// matter: every result is written at its own pair index).  Pairs that cannot be
+// compared go to bin 0.
+constexpr uint32_t BIN_COPIES = 32u;
+constexpr uint32_t BIN_CELLS = VBINS * BIN_COPIES;   // counts, then cursors, then starts
+static_assert(VERIFY_BIN_WORDS == 3u * BIN_CELLS, "the host allocates them");
+
+__device__ __forceinline__ void bin_keys(const FilterArgs &a, uint32_t i0, uint32_t sel,
+                                         uint32_t (&key)[SEL_PER_LANE])
+{
+    length_keys(a, i0, sel, key);
+#pragma unroll
+    for (uint32_t j = 0; j < SEL_PER_LANE; ++j) {
+        const uint32_t e = (sel & (1u << j)) ? (uint32_t)a.e_pair[i0 + j] : 0u;
+        key[j] = key[j] && e <= GK_VERIFY_MAX_E ? ((key[j] + 31u) / 32u - 1u) * 32u + e : 0u;
+    }
+}
+
+__global__ __launch_bounds__(256) void k_bin_zero(uint32_t *bins)
+{
+    for (uint32_t b = blockIdx.x * 256u + threadIdx.x; b < 2u * BIN_CELLS; b += gridDim.x * 256u)
+        bins[b] = 0u;
+}
+
+template <bool VEC>
+__global__ __launch_bounds__(256) void k_bin_count(FilterArgs a, const uint8_t *accept, uint32_t n,
+                                                   uint32_t *bins, uint16_t *dist)
+{
+    __shared__ uint32_t h[VBINS];
+    for (uint32_t b = threadIdx.x; b < VBINS; b += 256u)
+        h[b] = 0u;
+    __syncthreads();
+    const uint32_t i0 = blockIdx.x * SEL_PER_GROUP + threadIdx.x * SEL_PER_LANE;
+    const uint32_t sel = select_bits<VEC>(accept, n, i0, dist, true);
+    uint32_t key[SEL_PER_LANE];
+    bin_keys(a, i0, sel, key);
+#pragma unroll
+    for (uint32_t j = 0; j < SEL_PER_LANE; ++j)
+        if (sel & (1u << j))
+            atomicAdd(&h[key[j]], 1u);
+    __syncthreads();
+    uint32_t *copy = bins + (blockIdx.x % BIN_COPIES) * VBINS;
+    for (uint32_t b = threadIdx.x; b < VBINS; b += 256u)
+        if (h[b])
+            atomicAdd(&copy[b], h[b]);
+}
+
+// Starts of every (bin, copy) cell, bin-major, at bins[2 BIN_CELLS + copy *
+// VBINS + bin], the total into *count.
+__global__ __launch_bounds__(1024) void k_bin_scan(uint32_t *bins, uint32_t *count)
+{
+    __shared__ uint32_t wave_sum[16];
+    constexpr uint32_t PER = BIN_CELLS / 1024u;       // cells per thread
+    const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
+    uint32_t local[PER], sum = 0;
+#pragma unroll
+    for (uint32_t q = 0; q < PER; ++q) {
+        const uint32_t cell = threadIdx.x * PER + q;  // = bin * BIN_COPIES + copy
+        local[q] = bins[(cell % BIN_COPIES) * VBINS + cell / BIN_COPIES];
+        sum += local[q];
+    }
+    uint32_t incl = sum;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const uint32_t t = __shfl_up(incl, o, 64);
+        if (lane >= (uint32_t)o)
+            incl += t;
+    }
+    if (lane == 63u)
+        wave_sum[wave] = incl;
+    __syncthreads();
+    uint32_t before = 0;
+    for (uint32_t w = 0; w < wave; ++w)
+        before += wave_sum[w];
+    uint32_t run = before + incl - sum;
+#pragma unroll
+    for (uint32_t q = 0; q < PER; ++q) {
+        const uint32_t cell = threadIdx.x * PER + q;
+        bins[2u * BIN_CELLS + (cell % BIN_COPIES) * VBINS + cell / BIN_COPIES] = run;
+        run += local[q];
+    }
+    if (threadIdx.x == 1023u)
+        *count = before + incl;
+}
+
+template <bool VEC>
+__global__ __launch_bounds__(256) void k_bin_write(FilterArgs a, const uint8_t *accept, uint32_t n,
+                                                   uint32_t *bins, uint32_t *list)
+{
+    __shared__ uint32_t h[VBINS];
+    for (uint32_t b = threadIdx.x; b < VBINS; b += 256u)
+        h[b] = 0u;
+    __syncthreads();
+    const uint32_t i0 = blockIdx.x * SEL_PER_GROUP + threadIdx.x * SEL_PER_LANE;
+    const uint32_t sel = select_bits<VEC>(accept, n, i0, nullptr, false);
+    uint32_t key[SEL_PER_LANE], rank[SEL_PER_LANE];
+    bin_keys(a, i0, sel, key);
+#pragma unroll
+    for (uint32_t j = 0; j < SEL_PER_LANE; ++j)
+        rank[j] = (sel & (1u << j)) ? atomicAdd(&h[key[j]], 1u) : 0u;
+    __syncthreads();
+    // this group's run in its copy of each bin: the cell's start plus a
+    // reservation on the cell's cursor
+    const uint32_t c = (blockIdx.x % BIN_COPIES) * VBINS;
+    for (uint32_t b = threadIdx.x; b < VBINS; b += 256u)
+        if (h[b])
+            h[b] = bins[2u * BIN_CELLS + c + b] + atomicAdd(&bins[BIN_CELLS + c + b], h[b]);
+    __syncthreads();
+#pragma unroll
+    for (uint32_t j = 0; j < SEL_PER_LANE; ++j)
+        if (sel & (1u << j))
+            list[h[key[j]] + rank[j]] = i0 + j;
+}
+
+// Transposed read rows (word j of read r at reads[j * pitch + r]) to rows of
+// `stride` words (a multiple of 4): a workgroup stages 256 reads in LDS (each
+// row read with consecutive lanes on consecutive words), and each lane writes
+// its read in 16-byte stores.  The list of a batch by (words, e) scatters each
+// read's candidates, and a line per transposed row for each of them is what
+// would bound their loads.
+__global__ __launch_bounds__(256) void k_reads_rowwise(const uint32_t *reads, uint32_t pitch,
+                                                       uint32_t rows, uint32_t n_reads,
+                                                       uint32_t stride, uint32_t *out)
+{
+    extern __shared__ uint32_t lds_raw[];
+    const uint32_t r = blockIdx.x * 256u + threadIdx.x;
+    uint32_t *row = lds_raw + threadIdx.x * (stride + 1u);   // odd: distinct banks
+    for (uint32_t j = 0; j < stride; ++j)
+        row[j] = r < n_reads && j < rows ? reads[(size_t)j * pitch + r] : 0u;
+    if (r < n_reads) {
+        uint4 *q = reinterpret_cast<uint4 *>(out + (size_t)r * stride);
+        for (uint32_t j = 0; j < stride; j += 4)
+            q[j / 4] = make_uint4(row[j], row[j + 1], row[j + 2], row[j + 3]);
+    }
+}
+
+// The list's pairs, 64 in a row per wave, by the tile form's algorithms on
+// planes in LDS.  ROWWISE: the reads come from k_reads_rowwise.  Bound as the
+// tile form by LDS latency (furthest-reaching points) and column steps (bands),
+// but no wave is partly filled or mixes thresholds, and no LDS goes to the list:
+// a workgroup more per compute unit at 8 to 10 words.  Figures at verify_lists.
+template <int WMAX, int L, bool ROWWISE>
+__global__ __launch_bounds__(256) void k_verify_waves(FilterArgs a, const uint32_t *list,
+                                                      const uint32_t *count, uint16_t *dist,
+                                                      uint32_t words)
+{
+    extern __shared__ uint32_t lds_raw[];
+    const uint32_t lane = threadIdx.x & 63u;
+    Column col;
+    col.read = reinterpret_cast<uint2 *>(lds_raw) + (threadIdx.x >> 6) * wave_planes(words) + lane;
+    col.text = col.read + (words + 1u) * 64u;
+    const uint32_t n = *count;
+    const uint32_t waves = gridDim.x * 4u;
+    // the last bins, whose pairs take longest, first
+    for (uint32_t c = blockIdx.x * 4u + (threadIdx.x >> 6); c * 64u < n; c += waves) {
+        const uint32_t at = c * 64u + lane;
+        const bool have = at < n;
+        const uint32_t i = list[n - 1u - (have ? at : c * 64u)];
+        const PairIdx p = load_idx(a, i);
+        const bool live = have && p.r < a.n_reads && p.e <= GK_VERIFY_MAX_E;
+        uint32_t len = a.read_len[live ? p.r : 0u];
+        len = live && len <= a.max_read_len ? len : 0u;
+        const uint32_t d = wave_distances<WMAX, L, ROWWISE>(a, p, len, col);
+        if (have)
+            dist[i] = (uint16_t)d;
+    }
+}
+
 // Resident 256-lane workgroups per CU of k_verify_list.
 template <int W, int L>
 hipError_t list_blocks_per_cu(int &out)
@@ -910,79 +1100,101 @@ hipError_t list_blocks_per_cu(int &out)
     return hipSuccess;
 }
 
+// The list of n pairs into x.list and its length into x.count; dist of the
+// others set to GK_EST_NONE.
+template <bool VEC>
+void make_list(const FilterArgs &c, const uint8_t *accept, uint32_t n, uint16_t *dist,
+               const VerifyScratch &x, hipStream_t s)
+{
+    const uint32_t groups = (n + SEL_PER_GROUP - 1) / SEL_PER_GROUP;
+    if (c.e_pair) {
+        hipLaunchKernelGGL(k_bin_zero, dim3(32), dim3(256), 0, s, x.bins);
+        hipLaunchKernelGGL(k_bin_count<VEC>, dim3(groups), dim3(256), 0, s, c, accept, n, x.bins,
+                           dist);
+        hipLaunchKernelGGL(k_bin_scan, dim3(1), dim3(1024), 0, s, x.bins, x.count);
+        hipLaunchKernelGGL(k_bin_write<VEC>, dim3(groups), dim3(256), 0, s, c, accept, n, x.bins,
+                           x.list);
+        return;
+    }
+    hipLaunchKernelGGL(k_select_count<VEC>, dim3(groups), dim3(256), 0, s, accept, n, x.groups,
+                       dist);
+    hipLaunchKernelGGL(k_select_scan, dim3(1), dim3(1024), 0, s, x.groups, groups, x.count);
+    hipLaunchKernelGGL(k_select_write<VEC>, dim3(groups), dim3(256), 0, s, c, accept, n, x.groups,
+                       x.list);
+}
+
 template <int W, int L>
-hipError_t list_wl(const FilterArgs &a, const uint8_t *accept, uint16_t *dist,
-                   const VerifyScratch &x, int cus, hipStream_t s)
+hipError_t list_wl(const FilterArgs &c, uint16_t *dist, const VerifyScratch &x, uint32_t most,
+                   int cus, hipStream_t s)
 {
     int per_cu = 1;
     const hipError_t oe = list_blocks_per_cu<W, L>(per_cu);
     if (oe != hipSuccess)
         return oe;
-    const uint64_t CHUNK = 1ull << 30;
-    for (uint64_t first = 0; first < a.n_pairs; first += CHUNK) {
-        FilterArgs c = a;
-        const uint64_t n = a.n_pairs - first < CHUNK ? a.n_pairs - first : CHUNK;
-        c.n_pairs = n;
-        c.pair_read = a.pair_read ? a.pair_read + first : nullptr;
-        if (!a.pair_read && first > 0)
-            c.n_reads = 0;   // pair i uses read i < n_reads < 2^30: none here
-        c.cand_pos = a.cand_pos + first;
-        c.accept = nullptr;
-        c.est = nullptr;
-        c.accept_bits = nullptr;
-        const uint8_t *acc = accept ? accept + first : nullptr;
-        uint16_t *out = dist + first;
-        const uint32_t groups = (uint32_t)((n + SEL_PER_GROUP - 1) / SEL_PER_GROUP);
-        const bool vec = ((uintptr_t)acc & 15u) == 0 && ((uintptr_t)out & 15u) == 0;
-        if (vec)
-            hipLaunchKernelGGL(k_select_count<true>, dim3(groups), dim3(256), 0, s, acc,
-                               (uint32_t)n, x.groups, out);
-        else
-            hipLaunchKernelGGL(k_select_count<false>, dim3(groups), dim3(256), 0, s, acc,
-                               (uint32_t)n, x.groups, out);
-        hipLaunchKernelGGL(k_select_scan, dim3(1), dim3(1024), 0, s, x.groups, groups, x.count);
-        if (vec)
-            hipLaunchKernelGGL(k_select_write<true>, dim3(groups), dim3(256), 0, s, c, acc,
-                               (uint32_t)n, x.groups, x.list);
-        else
-            hipLaunchKernelGGL(k_select_write<false>, dim3(groups), dim3(256), 0, s, c, acc,
-                               (uint32_t)n, x.groups, x.list);
-        // Up to 8 times the resident workgroups: later workgroups start as
-        // earlier ones finish, so the waves' gathers do not all come at once
-        // (measured faster than one resident round at every sweep point; the
-        // list length is only known on the device).
-        const uint64_t want = (n + 255) / 256, most = 8ull * cus * per_cu;
-        hipLaunchKernelGGL((k_verify_list<W, L>), dim3((uint32_t)(want < most ? want : most)),
-                           dim3(256), 0, s, c, (const uint32_t *)x.list,
-                           (const uint32_t *)x.count, out);
-        const hipError_t e = hipGetLastError();
-        if (e != hipSuccess)
-            return e;
-    }
-    return hipSuccess;
+    // Up to 8 times the resident workgroups: later workgroups start as
+    // earlier ones finish, so the waves' gathers do not all come at once
+    // (measured faster than one resident round at every sweep point; the
+    // list length is only known on the device).
+    const uint32_t grid = std::min(most, 8u * (uint32_t)(cus * per_cu));
+    hipLaunchKernelGGL((k_verify_list<W, L>), dim3(grid), dim3(256), 0, s, c,
+                       (const uint32_t *)x.list, (const uint32_t *)x.count, dist);
+    return hipGetLastError();
 }
 
-template <int L>
-hipError_t list_l(const FilterArgs &a, const uint8_t *accept, uint16_t *dist, uint32_t words,
-                  const VerifyScratch &x, int cus, hipStream_t s)
+template <int WMAX, int L, bool ROWWISE>
+hipError_t waves_wl(const FilterArgs &c, uint16_t *dist, const VerifyScratch &x, uint32_t words,
+                    uint32_t most, int cus, hipStream_t s)
 {
+    const uint32_t grid = std::min(most, 32u * (uint32_t)cus);
+    hipLaunchKernelGGL((k_verify_waves<WMAX, L, ROWWISE>), dim3(grid), dim3(256),
+                       4u * wave_planes(words) * sizeof(uint2), s, c, (const uint32_t *)x.list,
+                       (const uint32_t *)x.count, dist, words);
+    return hipGetLastError();
+}
+
+template <int L, bool ROWWISE>
+hipError_t waves_l(const FilterArgs &c, uint16_t *dist, uint32_t words, const VerifyScratch &x,
+                   uint32_t most, int cus, hipStream_t s)
+{
+    if (words <= 4)
+        return waves_wl<4, L, ROWWISE>(c, dist, x, words, most, cus, s);
+    if (words <= 8)
+        return waves_wl<8, L, ROWWISE>(c, dist, x, words, most, cus, s);
+    if (words <= 10)
+        return waves_wl<10, L, ROWWISE>(c, dist, x, words, most, cus, s);
+    return waves_wl<16, L, ROWWISE>(c, dist, x, words, most, cus, s);
+}
+
+// Distances of the list's pairs.
+template <int L>
+hipError_t list_l(const FilterArgs &c, uint16_t *dist, uint32_t words, const VerifyScratch &x,
+                  uint32_t most, int cus, hipStream_t s)
+{
+    if (c.e_pair) {
+        FilterArgs r = c;
+        r.reads = x.reads;
+        r.pitch = verify_read_stride(c.rows);
+        return waves_l<L, true>(r, dist, words, x, most, cus, s);
+    }
+    if (c.e_uniform <= FURTHEST_MAX_E)
+        return waves_l<L, false>(c, dist, words, x, most, cus, s);
     switch (words) {
-    case 1: return list_wl<1, L>(a, accept, dist, x, cus, s);
-    case 2: return list_wl<2, L>(a, accept, dist, x, cus, s);
-    case 3: return list_wl<3, L>(a, accept, dist, x, cus, s);
-    case 4: return list_wl<4, L>(a, accept, dist, x, cus, s);
-    case 5: return list_wl<5, L>(a, accept, dist, x, cus, s);
-    case 6: return list_wl<6, L>(a, accept, dist, x, cus, s);
-    case 7: return list_wl<7, L>(a, accept, dist, x, cus, s);
-    case 8: return list_wl<8, L>(a, accept, dist, x, cus, s);
-    case 9: return list_wl<9, L>(a, accept, dist, x, cus, s);
-    case 10: return list_wl<10, L>(a, accept, dist, x, cus, s);
-    case 11: return list_wl<11, L>(a, accept, dist, x, cus, s);
-    case 12: return list_wl<12, L>(a, accept, dist, x, cus, s);
-    case 13: return list_wl<13, L>(a, accept, dist, x, cus, s);
-    case 14: return list_wl<14, L>(a, accept, dist, x, cus, s);
-    case 15: return list_wl<15, L>(a, accept, dist, x, cus, s);
-    case 16: return list_wl<16, L>(a, accept, dist, x, cus, s);
+    case 1: return list_wl<1, L>(c, dist, x, most, cus, s);
+    case 2: return list_wl<2, L>(c, dist, x, most, cus, s);
+    case 3: return list_wl<3, L>(c, dist, x, most, cus, s);
+    case 4: return list_wl<4, L>(c, dist, x, most, cus, s);
+    case 5: return list_wl<5, L>(c, dist, x, most, cus, s);
+    case 6: return list_wl<6, L>(c, dist, x, most, cus, s);
+    case 7: return list_wl<7, L>(c, dist, x, most, cus, s);
+    case 8: return list_wl<8, L>(c, dist, x, most, cus, s);
+    case 9: return list_wl<9, L>(c, dist, x, most, cus, s);
+    case 10: return list_wl<10, L>(c, dist, x, most, cus, s);
+    case 11: return list_wl<11, L>(c, dist, x, most, cus, s);
+    case 12: return list_wl<12, L>(c, dist, x, most, cus, s);
+    case 13: return list_wl<13, L>(c, dist, x, most, cus, s);
+    case 14: return list_wl<14, L>(c, dist, x, most, cus, s);
+    case 15: return list_wl<15, L>(c, dist, x, most, cus, s);
+    case 16: return list_wl<16, L>(c, dist, x, most, cus, s);
     default: return hipErrorInvalidValue;
     }
 }
@@ -1002,9 +1214,44 @@ hipError_t launch_verify_listed(const FilterArgs &a, const uint8_t *accept, uint
                                 uint32_t words, uint32_t layout, const VerifyScratch &x, int cus,
                                 hipStream_t s)
 {
-    return layout == GK_READS_INTERLEAVED
-               ? list_l<GK_READS_INTERLEAVED>(a, accept, dist, words, x, cus, s)
-               : list_l<GK_READS_SPLIT>(a, accept, dist, words, x, cus, s);
+    if (a.e_pair) {
+        const uint32_t stride = verify_read_stride(a.rows);
+        hipLaunchKernelGGL(k_reads_rowwise, dim3((a.n_reads + 255u) / 256u), dim3(256),
+                           256u * (stride + 1u) * sizeof(uint32_t), s, a.reads, a.pitch, a.rows,
+                           a.n_reads, stride, x.reads);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess)
+            return e;
+    }
+    const uint64_t CHUNK = 1ull << 30;
+    for (uint64_t first = 0; first < a.n_pairs; first += CHUNK) {
+        FilterArgs c = a;
+        const uint64_t n = a.n_pairs - first < CHUNK ? a.n_pairs - first : CHUNK;
+        c.n_pairs = n;
+        c.pair_read = a.pair_read ? a.pair_read + first : nullptr;
+        if (!a.pair_read && first > 0)
+            c.n_reads = 0;   // pair i uses read i < n_reads < 2^30: none here
+        c.cand_pos = a.cand_pos + first;
+        c.e_pair = a.e_pair ? a.e_pair + first : nullptr;
+        c.accept = nullptr;
+        c.est = nullptr;
+        c.accept_bits = nullptr;
+        const uint8_t *acc = accept ? accept + first : nullptr;
+        uint16_t *out = dist + first;
+        if (((uintptr_t)acc & 15u) == 0 && ((uintptr_t)out & 15u) == 0)
+            make_list<true>(c, acc, (uint32_t)n, out, x, s);
+        else
+            make_list<false>(c, acc, (uint32_t)n, out, x, s);
+        hipError_t e = hipGetLastError();
+        const uint32_t most = (uint32_t)((n + 255) / 256);
+        if (e == hipSuccess)
+            e = layout == GK_READS_INTERLEAVED
+                    ? list_l<GK_READS_INTERLEAVED>(c, out, words, x, most, cus, s)
+                    : list_l<GK_READS_SPLIT>(c, out, words, x, most, cus, s);
+        if (e != hipSuccess)
+            return e;
+    }
+    return hipSuccess;
 }
 
 }  // namespace gkd
