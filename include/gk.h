@@ -202,7 +202,8 @@ typedef struct gk_batch {
  * 2^30 pairs), one GPU lane per pair at a time (Sec. 3.2: one thread per
  * filtration), the read and window held as 32-base bit-planes in registers.
  * A large batch with a threshold per pair (2^18 pairs or more, max_read_len
- * above 128) is sorted by threshold within workgroups, as gk_filter_mixed does.
+ * above 128) is sorted by threshold within workgroups, as gk_filter_mixed does,
+ * where neighbouring thresholds differ.
  * Asynchronous on stream.
  * Errors (nothing launched): GK_EINVAL for NULL required pointers, pitch <
  * n_reads, n_reads or pitch >= 2^30, max_read_len outside 1..512, e_uniform

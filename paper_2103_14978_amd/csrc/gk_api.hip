@@ -687,11 +687,7 @@ int gk_filter(gk_ctx *ctx, const gk_batch *b, void *stream)
     hipError_t e;
     if (a.flags == 0u && ctx->pairs_per_lane == 0 &&
         gkd::filter_sorts(b->e != nullptr, b->n_pairs, words)) {
-        gkd::MixedArgs x{};
-        x.tile = 1024;
-        x.ppl = 1;
-        x.sort_e = 1;
-        e = gkd::launch_mixed(a, x, words, b->read_layout, (hipStream_t)stream);
+        e = gkd::launch_ordered(a, words, b->read_layout, (hipStream_t)stream);
     } else {
         e = gkd::launch_filter(a, words, b->read_layout, ctx->pairs_per_lane,
                                (hipStream_t)stream);

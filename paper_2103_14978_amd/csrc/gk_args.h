@@ -130,7 +130,7 @@ inline bool mixed_unsorted(uint64_t n_pairs, uint32_t wmax)
     return n_pairs <= (wmax <= 4 ? 1u << 17 : 24576u);
 }
 
-// Whether the plain call sorts its pairs first (the direct form of the mixed
+// Whether the plain call sorts its pairs first (the ordered form of the mixed
 // launch): a threshold per pair makes a wave of neighbours run the largest of
 // its thresholds.  4 M pairs, e per pair up to a tenth of the length: 250 bases
 // 384 us as they come, 252 sorted; 150 bases 161 and 135; mixed lengths up to
@@ -142,6 +142,11 @@ inline bool filter_sorts(bool e_per_pair, uint64_t n_pairs, uint32_t wmax)
     return e_per_pair && wmax >= 5 && n_pairs >= (1u << 18);
 }
 
+// Pairs per tile of that form.  Enough tiles for every compute unit: 2^18 pairs
+// of 250 bases 32, 25, 31 and 56 us with 256, 512, 1024 and 2048; 2^22 pairs 330,
+// 262, 249 and 261.
+inline uint32_t filter_tile(uint64_t n_pairs) { return n_pairs < (1u << 19) ? 512u : 1024u; }
+
 struct MixedArgs {
     const BatchTable *table;     // table form: the device table; with n_tiles
                                  // set, a host table of at most INLINE_BATCHES
@@ -151,7 +156,7 @@ struct MixedArgs {
     uint32_t sort_e;             // 0 or 1
     uint32_t blocks;             // table form: persistent workgroups
     uint32_t n_tiles;            // tiles of a host table, else 0
-    uint32_t lg;                 // direct form: 2^lg lanes per pair (0, 1 or 2)
+    uint32_t lg;                 // direct form: 2^lg lanes per pair (0 or 1)
 };
 
 }  // namespace gkd

@@ -183,6 +183,9 @@ namespace gkd {
 // Mixed-batch filter of one batch, direct form: one launch per 2^30 pairs.
 hipError_t launch_mixed(const FilterArgs &a, const MixedArgs &x, uint32_t wmax, uint32_t layout,
                         hipStream_t s);
+// Plain filter of a batch with a threshold per pair and reads of more than 4
+// words: the direct form, but a tile that is in order already is left as it is.
+hipError_t launch_ordered(const FilterArgs &a, uint32_t wmax, uint32_t layout, hipStream_t s);
 // Workgroups of the table form that fit one compute unit.
 hipError_t mixed_blocks_per_cu(uint32_t wmax, uint32_t layout, uint32_t tile, uint32_t ppl,
                                int *out);

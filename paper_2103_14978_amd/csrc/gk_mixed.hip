@@ -23,7 +23,14 @@
 //   table       resident workgroups claim tiles of a table of batches from a
 //               device counter, so that one captured graph serves any batches;
 //   inline      one workgroup per tile of a table that comes with the kernel's
-//               arguments.
+//               arguments;
+//   ordered     the direct form for the plain call, which cannot know whether
+//               the thresholds of an array differ: a tile whose pairs lie in
+//               runs of one (W, k_max) goes to the chunks unsorted (a constant
+//               threshold over 2^20 pairs of 150 bases, e = 3: 25 us, 32 sorted,
+//               24 without looking; 2^22 of 250, e = 1: 87, 106 and 102), and
+//               widths of 6 and 12 words keep the waves per SIMD of the plain
+//               kernel (5 and 3, against 4 and 2 in the next wider).
 #include "gk_pair.h"
 
 namespace gkd {
@@ -39,7 +46,8 @@ struct MixedLds {
     uint32_t tile;
     uint32_t n_chunks;
     uint32_t next_chunk;
-    uint32_t pad_[2];
+    uint32_t sorts;                       // 0: every 64 pairs in a row share a bin
+    uint32_t pad_;
 };
 
 // Dynamic LDS after MixedLds: the tile's pair entries pos[T], read[T],
@@ -140,7 +148,7 @@ __device__ __forceinline__ void run_chunk(const FilterArgs &a, const TilePairs &
 #undef GK_CASE
 }
 
-enum Form { DIRECT, TABLE, INLINE };
+enum Form { DIRECT, TABLE, INLINE, ORDERED };
 
 // Batch of a tile in a table launch: the last b with prefix[b] <= tile (empty
 // batches share their prefix with the next one, so the last match is the
@@ -205,6 +213,8 @@ void k_mixed(FilterArgs a0, MixedArgs x, Batches batches)
             s.tile = atomicAdd(x.tile_counter, 1u);
         for (uint32_t b = tid; b <= NBINS; b += 256)
             s.hist[b] = 0;
+        if (FORM == ORDERED && tid == 0)
+            s.sorts = 0u;
         __syncthreads();
         FilterArgs a = a0;
         uint32_t base = blockIdx.x * x.tile, batch = 0;
@@ -260,102 +270,145 @@ void k_mixed(FilterArgs a0, MixedArgs x, Batches batches)
                 t.pos[j] = p[q].pos;
                 t.read[j] = p[q].r;
                 t.entry[j] = en;
-                if (key <= NBINS)
-                    atomicAdd(&s.hist[key], 1u);
                 sorted[j] = (uint16_t)key;         // until step 3
+                if constexpr (FORM != ORDERED) {
+                    if (key <= NBINS)
+                        atomicAdd(&s.hist[key], 1u);
+                    continue;
+                }
+                // one bin for the wave's 64 pairs: counted at once
+                const unsigned long long on = __ballot(key <= NBINS);
+                if (on == 0ull)
+                    continue;
+                const uint32_t first = __builtin_ctzll(on);
+                const uint32_t key0 = __builtin_amdgcn_readlane(key, first);
+                if (__ballot(key <= NBINS && key != key0) == 0ull) {
+                    if (lane == first)
+                        atomicAdd(&s.hist[key], (uint32_t)__builtin_popcountll(on));
+                } else {
+                    if (key <= NBINS)
+                        atomicAdd(&s.hist[key], 1u);
+                    s.sorts = 1u;
+                }
             }
         }
         __syncthreads();
+        const bool sorts = FORM != ORDERED || __builtin_amdgcn_readfirstlane(s.sorts) != 0u;
 
-        // 2. exclusive prefix over the bins (wave 0: 8 bins per lane)
-        if (tid < 64) {
-            uint32_t local[8], sum = 0;
+        if (sorts) {
+            // 2. exclusive prefix over the bins (wave 0: 8 bins per lane)
+            if (tid < 64) {
+                uint32_t local[8], sum = 0;
+#pragma unroll
+                for (int q = 0; q < 8; ++q) {
+                    local[q] = s.hist[tid * 8 + q];
+                    sum += local[q];
+                }
+                uint32_t incl = sum;
+#pragma unroll
+                for (int o = 1; o < 64; o <<= 1) {
+                    const uint32_t v = __shfl_up(incl, o, 64);
+                    if (lane >= (uint32_t)o)
+                        incl += v;
+                }
+                uint32_t run = incl - sum;
+#pragma unroll
+                for (int q = 0; q < 8; ++q) {
+                    const uint32_t b = tid * 8 + q;
+                    if (b % 32u == 0u)
+                        s.wstart[b / 32u] = run;
+                    s.hist[b] = run;
+                    run += local[q];
+                }
+                if (tid == 63) {
+                    s.wstart[FAR] = run;
+                    s.wstart[FAR + 1] = run + s.hist[NBINS];
+                    s.hist[NBINS] = run;
+                }
+            }
+            // keys to registers: the sorted slots take their place
+            uint32_t key8[8];
 #pragma unroll
             for (int q = 0; q < 8; ++q) {
-                local[q] = s.hist[tid * 8 + q];
-                sum += local[q];
+                const uint32_t j = tid + 256u * q;
+                key8[q] = j < x.tile ? sorted[j] : NBINS + 1u;
             }
-            uint32_t incl = sum;
-#pragma unroll
-            for (int o = 1; o < 64; o <<= 1) {
-                const uint32_t v = __shfl_up(incl, o, 64);
-                if (lane >= (uint32_t)o)
-                    incl += v;
-            }
-            uint32_t run = incl - sum;
-#pragma unroll
-            for (int q = 0; q < 8; ++q) {
-                const uint32_t b = tid * 8 + q;
-                if (b % 32u == 0u)
-                    s.wstart[b / 32u] = run;
-                s.hist[b] = run;
-                run += local[q];
-            }
-            if (tid == 63) {
-                s.wstart[FAR] = run;
-                s.wstart[FAR + 1] = run + s.hist[NBINS];
-                s.hist[NBINS] = run;
-            }
-        }
-        // keys to registers: the sorted slots take their place
-        uint32_t key8[8];
-#pragma unroll
-        for (int q = 0; q < 8; ++q) {
-            const uint32_t j = tid + 256u * q;
-            key8[q] = j < x.tile ? sorted[j] : NBINS + 1u;
-        }
-        __syncthreads();
+            __syncthreads();
 
-        // 3. scatter slots into bin order
+            // 3. scatter slots into bin order
 #pragma unroll
-        for (int q = 0; q < 8; ++q)
-            if (key8[q] <= NBINS)
-                sorted[atomicAdd(&s.hist[key8[q]], 1u)] = (uint16_t)(tid + 256u * q);
+            for (int q = 0; q < 8; ++q)
+                if (key8[q] <= NBINS)
+                    sorted[atomicAdd(&s.hist[key8[q]], 1u)] = (uint16_t)(tid + 256u * q);
 
-        // 4. chunks: runs of one W, 64 * ppl pairs at most.  A W's pairs are
-        //    in ascending k_max, so its one partial chunk is put first, on the
-        //    pairs with the fewest shifts: its idle lanes then wait through
-        //    the shortest loop.
-        if (tid < 64) {
-            const uint32_t ch = SPLIT ? 64u >> x.lg : tid == FAR ? 64u : 64u * PPL;
-            const uint32_t w0 = tid <= FAR ? s.wstart[tid] : 0u;
-            const uint32_t cnt = tid <= FAR ? s.wstart[tid + 1] - w0 : 0u;
-            const uint32_t nch = (cnt + ch - 1) / ch;
-            const uint32_t lead = cnt % ch == 0u ? ch : cnt % ch;   // size of chunk 0
-            uint32_t incl = nch;
+            // 4. chunks: runs of one W, 64 * ppl pairs at most.  A W's pairs are
+            //    in ascending k_max, so its one partial chunk is put first, on the
+            //    pairs with the fewest shifts: its idle lanes then wait through
+            //    the shortest loop.
+            if (tid < 64) {
+                const uint32_t ch = SPLIT ? 64u >> x.lg : tid == FAR ? 64u : 64u * PPL;
+                const uint32_t w0 = tid <= FAR ? s.wstart[tid] : 0u;
+                const uint32_t cnt = tid <= FAR ? s.wstart[tid + 1] - w0 : 0u;
+                const uint32_t nch = (cnt + ch - 1) / ch;
+                const uint32_t lead = cnt % ch == 0u ? ch : cnt % ch;   // size of chunk 0
+                uint32_t incl = nch;
 #pragma unroll
-            for (int o = 1; o < 64; o <<= 1) {
-                const uint32_t v = __shfl_up(incl, o, 64);
-                if (lane >= (uint32_t)o)
-                    incl += v;
+                for (int o = 1; o < 64; o <<= 1) {
+                    const uint32_t v = __shfl_up(incl, o, 64);
+                    if (lane >= (uint32_t)o)
+                        incl += v;
+                }
+                const uint32_t first = incl - nch;
+                for (uint32_t c = 0; c < nch; ++c) {
+                    chunk_start[first + c] = w0 + (c == 0u ? 0u : lead + (c - 1u) * ch);
+                    chunk_info[first + c] = (c == 0u ? lead : ch) | ((tid + 1u) << 16);
+                }
+                if (tid == 63) {
+                    s.n_chunks = incl;
+                    s.next_chunk = 0;
+                }
             }
-            const uint32_t first = incl - nch;
-            for (uint32_t c = 0; c < nch; ++c) {
-                chunk_start[first + c] = w0 + (c == 0u ? 0u : lead + (c - 1u) * ch);
-                chunk_info[first + c] = (c == 0u ? lead : ch) | ((tid + 1u) << 16);
-            }
-            if (tid == 63) {
-                s.n_chunks = incl;
-                s.next_chunk = 0;
-            }
+            __syncthreads();
         }
-        __syncthreads();
 
         // 5. waves take chunks, the heaviest (largest W and k_max, at the
-        //    end of the list) first, so the tile ends on short chunks
-        const uint32_t n_chunks = s.n_chunks;
+        //    end of the list) first, so the tile ends on short chunks; of a
+        //    tile left in order each its own 64 pairs
+        const uint32_t lanes = SPLIT ? 1u << x.lg : 1u, sub = lane & (lanes - 1u);
+        const uint32_t n_chunks = sorts ? s.n_chunks : x.tile * lanes / 64u;
+        uint32_t own = __builtin_amdgcn_readfirstlane(tid >> 6);
         while (true) {
-            uint32_t c = 0;
-            if (lane == 0)
-                c = atomicAdd(&s.next_chunk, 1u);
-            c = __builtin_amdgcn_readfirstlane(c);
+            uint32_t c = own;
+            if (sorts) {
+                if (lane == 0)
+                    c = atomicAdd(&s.next_chunk, 1u);
+                c = __builtin_amdgcn_readfirstlane(c);
+            }
+            own += 4u;
             if (c >= n_chunks)
                 break;
-            c = n_chunks - 1u - c;
-            const uint32_t start = __builtin_amdgcn_readfirstlane(chunk_start[c]);
-            const uint32_t info = __builtin_amdgcn_readfirstlane(chunk_info[c]);
-            const uint32_t cnt = info & 0xFFFFu;
-            const uint32_t w = info >> 16;
+            uint32_t at = SPLIT ? lane >> x.lg : lane, cnt, w, s0;
+            bool on;
+            if (sorts) {
+                c = n_chunks - 1u - c;
+                const uint32_t start = __builtin_amdgcn_readfirstlane(chunk_start[c]);
+                const uint32_t info = __builtin_amdgcn_readfirstlane(chunk_info[c]);
+                cnt = info & 0xFFFFu;
+                w = info >> 16;
+                on = at < cnt;
+                at += start;
+                s0 = on ? sorted[at] : 0u;
+            } else {
+                cnt = 0u;
+                s0 = at + c * 64u / lanes;
+                const uint32_t key = sorted[s0];
+                on = key <= NBINS;
+                const unsigned long long any = __ballot(on);
+                if (any == 0ull)
+                    continue;
+                const uint32_t key0 = __builtin_amdgcn_readlane(key, __builtin_ctzll(any));
+                w = key0 == NBINS ? FAR + 1u : key0 / 32u + 1u;
+            }
             // The arguments anew for each chunk: what all 16 widths derive from
             // them (row addresses above all) does not fit the scalar registers
             // when the compiler computes it before the loop.
@@ -367,15 +420,12 @@ void k_mixed(FilterArgs a0, MixedArgs x, Batches batches)
             if constexpr (FORM == INLINE)
                 a = batches.args[batch];
             asm volatile("" : "+s"(a.pitch), "+s"(a.rows), "+s"(a.max_read_len));
-            const uint32_t lanes = SPLIT ? 1u << x.lg : 1u, sub = lane & (lanes - 1u);
-            const uint32_t at = SPLIT ? lane >> x.lg : lane;
-            if (at < cnt) {
-                const uint32_t s0 = sorted[start + at];
+            if (on) {
                 if (w == FAR + 1u) {
                     run_chunk_pair<WMAX, L, true, VAR, SPLIT>(a, t, s0, sub, lanes);
                 } else {
-                    const bool has1 = lane + 64u < cnt;
-                    const uint32_t s1 = has1 ? sorted[start + lane + 64u] : s0;
+                    const bool has1 = PPL == 2 && lane + 64u < cnt;
+                    const uint32_t s1 = has1 ? sorted[at + 64u] : s0;
                     run_chunk<WMAX, L, PPL, VAR, SPLIT>(a, t, w, s0, has1, s1, sub, lanes);
                 }
             }
@@ -410,7 +460,8 @@ __global__ __launch_bounds__(64) void k_reset(uint32_t *tile_counter)
         *tile_counter = 0;
 }
 
-template <int WMAX, int L>
+// ORD: the ordered form.
+template <int WMAX, int L, bool ORD = false>
 hipError_t launch_mixed_wl(const FilterArgs &a, const MixedArgs &x, hipStream_t s)
 {
     const uint64_t CHUNK = 1ull << 30;
@@ -428,23 +479,17 @@ hipError_t launch_mixed_wl(const FilterArgs &a, const MixedArgs &x, hipStream_t 
         c.accept_bits = a.accept_bits ? a.accept_bits + first / 64 : nullptr;
         const dim3 grid((uint32_t)((n + x.tile - 1) / x.tile));
         const size_t lds = mixed_lds_bytes(x.tile, x.lg);
-        bool two = false;
-        if constexpr (WMAX <= 10)
-            two = x.ppl == 2 && a.flags == 0u;
-        if (a.flags != 0u) {
-            // Variant semantics: their own kernel, one pair per lane.
-            hipLaunchKernelGGL((k_mixed<WMAX, L, 1, true, DIRECT>), grid, dim3(256), lds, s, c, x,
-                               NoTable{});
-        } else if (x.lg != 0u) {
-            hipLaunchKernelGGL((k_mixed<WMAX, L, 1, false, DIRECT, true>), grid, dim3(256), lds,
-                               s, c, x, NoTable{});
-        } else if (!two) {
-            hipLaunchKernelGGL((k_mixed<WMAX, L, 1, false, DIRECT>), grid, dim3(256), lds, s, c, x,
-                               NoTable{});
-        } else if constexpr (WMAX <= 10) {
-            hipLaunchKernelGGL((k_mixed<WMAX, L, 2, false, DIRECT>), grid, dim3(256), lds, s, c, x,
-                               NoTable{});
+        auto kernel = k_mixed<WMAX, L, 1, false, ORD ? ORDERED : DIRECT>;
+        if constexpr (!ORD) {
+            if (a.flags != 0u)            // variant semantics: their own kernel
+                kernel = k_mixed<WMAX, L, 1, true, DIRECT>;
+            else if (x.lg != 0u)
+                kernel = k_mixed<WMAX, L, 1, false, DIRECT, true>;
+            if constexpr (WMAX <= 10)
+                if (x.ppl == 2 && x.lg == 0u && a.flags == 0u)
+                    kernel = k_mixed<WMAX, L, 2, false, DIRECT>;
         }
+        hipLaunchKernelGGL(kernel, grid, dim3(256), lds, s, c, x, NoTable{});
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess)
             return e;
@@ -497,6 +542,18 @@ hipError_t launch_mixed_l(const FilterArgs &a, const MixedArgs &x, uint32_t wmax
     return launch_mixed_wl<16, L>(a, x, s);
 }
 
+template <int L>
+hipError_t launch_ordered_l(const FilterArgs &a, const MixedArgs &x, uint32_t wmax, hipStream_t s)
+{
+    if (wmax <= 6)
+        return launch_mixed_wl<6, L, true>(a, x, s);
+    if (wmax <= 10)
+        return launch_mixed_wl<10, L, true>(a, x, s);
+    if (wmax <= 12)
+        return launch_mixed_wl<12, L, true>(a, x, s);
+    return launch_mixed_wl<16, L, true>(a, x, s);
+}
+
 template <int WMAX, int L>
 hipError_t occupancy_wl(uint32_t tile, uint32_t ppl, int *blocks_per_cu)
 {
@@ -544,6 +601,17 @@ hipError_t launch_mixed(const FilterArgs &a, const MixedArgs &x, uint32_t wmax, 
     return layout == GK_READS_INTERLEAVED
                ? launch_mixed_l<GK_READS_INTERLEAVED>(a, x, wmax, s)
                : launch_mixed_l<GK_READS_SPLIT>(a, x, wmax, s);
+}
+
+hipError_t launch_ordered(const FilterArgs &a, uint32_t wmax, uint32_t layout, hipStream_t s)
+{
+    MixedArgs x{};
+    x.tile = filter_tile(a.n_pairs);
+    x.ppl = 1;
+    x.sort_e = 1;
+    return layout == GK_READS_INTERLEAVED
+               ? launch_ordered_l<GK_READS_INTERLEAVED>(a, x, wmax, s)
+               : launch_ordered_l<GK_READS_SPLIT>(a, x, wmax, s);
 }
 
 }  // namespace gkd
