@@ -430,15 +430,18 @@ int gk_filter_mixed_noalloc(gk_ctx *ctx, const gk_batch *batch, void *stream);
 
 /*
  * Autotuner for gk_filter_mixed.  Times every candidate tuning (tile 2048 /
- * 4096 / 8192, 1 or 2 pairs per lane, sort by e or not, full or half
- * persistent grid) on the first sample_pairs pairs of the batch (0 = all),
- * median of 5 runs each after a warm-up, and keeps the fastest in the
- * context.  When it times candidates, the outputs of the sampled pairs are
+ * 4096 / 8192, 1 or 2 pairs per lane, sort by e or not and, for a batch that
+ * takes the captured form, full or half persistent grid) on the first
+ * sample_pairs pairs of the batch (0 = all), each as gk_filter_mixed would run
+ * the whole batch under it, median of 5 calls after a warm-up.  The context
+ * keeps the fastest; the defaults, which leave tile and lanes to the batch size,
+ * are kept unless another is faster by 2%.  When it times candidates, the outputs of the sampled pairs are
  * written (correct results: every tuning gives the same ones).  Synchronous.
  *
  * cache_path (HOST string or NULL): a text file of JSON lines keyed by
  * device architecture, CU count, words per mask, read layout, threshold mode
- * and batch size (power-of-two bucket).  The last matching line is used
+ * and batch size (power-of-two bucket).  (Lines of earlier versions, which
+ * timed another form than the call's, are not matched.)  The last matching line is used
  * without timing anything; otherwise the measured choice is appended.  A
  * context created with GK_AUTOTUNE=refresh in the environment measures and
  * appends whatever the cache holds; with GK_AUTOTUNE=off it keeps its

@@ -622,9 +622,8 @@ hipError_t copy_table(gk_ctx *ctx, int slot, const gkd::FilterArgs &a, uint32_t 
     return hipMemcpyAsync(ctx->d_table, h, bytes, hipMemcpyHostToDevice, s);
 }
 
-gkd::MixedArgs direct_args(const gk_ctx *ctx, uint64_t n_pairs, uint32_t wmax)
+gkd::MixedArgs direct_args(const MixedConfig &c, uint64_t n_pairs, uint32_t wmax)
 {
-    const MixedConfig &c = ctx->mixed;
     gkd::MixedArgs x{};
     x.tile = c.untouched() ? gkd::mixed_auto_tile(n_pairs, wmax) : gkd::mixed_tile(c.tile);
     x.lg = c.untouched() ? gkd::mixed_auto_lanes(n_pairs, wmax) : 0u;
@@ -633,11 +632,12 @@ gkd::MixedArgs direct_args(const gk_ctx *ctx, uint64_t n_pairs, uint32_t wmax)
     return x;
 }
 
-// The direct form, or the plain launch where a batch is too small to sort.
-hipError_t launch_direct(const gk_ctx *ctx, const gkd::FilterArgs &a, const gkd::MixedArgs &x,
-                         uint32_t wmax, uint32_t layout, hipStream_t s)
+// The direct form with x = direct_args(c, n_pairs, wmax), or the plain launch
+// where a batch of n_pairs is too small to sort.
+hipError_t launch_direct(const MixedConfig &c, const gkd::FilterArgs &a, const gkd::MixedArgs &x,
+                         uint64_t n_pairs, uint32_t wmax, uint32_t layout, hipStream_t s)
 {
-    if (ctx->mixed.untouched() && gkd::mixed_unsorted(a.n_pairs, wmax))
+    if (c.untouched() && gkd::mixed_unsorted(n_pairs, wmax))
         return gkd::launch_filter(a, wmax, layout, 0, s);
     return gkd::launch_mixed(a, x, wmax, layout, s);
 }
@@ -660,6 +660,87 @@ int mixed_args(gk_ctx *ctx, const MixedConfig &c, uint32_t wmax, uint32_t layout
     x.ppl = c.ppl;
     x.sort_e = c.sort_e;
     x.blocks = bpc * (uint32_t)ctx->cu_count;
+    return GK_OK;
+}
+
+// Whether a batch of n_pairs takes the direct form under tuning c: unless one
+// was set and the batch leaves compute units without a tile.  It is one launch,
+// without the argument copy, the graph's launch and the counter reset before it
+// (60,001 pairs: 21 against about 55 us; 2^24 pairs: 805 against 850).  Always
+// for variant semantics (their own kernels) and batches of more than one launch
+// chunk (2^30 pairs).
+bool mixed_direct(const gk_ctx *ctx, const MixedConfig &c, const gkd::FilterArgs &a,
+                  uint64_t n_pairs, uint32_t wmax)
+{
+    const uint32_t tile = direct_args(c, n_pairs, wmax).tile;
+    return !ctx->use_graph || a.flags != 0u || n_pairs > (1ull << 30) || c.untouched() ||
+           (n_pairs + tile - 1) / tile >= (uint64_t)ctx->cu_count;
+}
+
+// gk_filter_mixed of a (checked, scratch ensured) under tuning c, in the form
+// that a batch of n_pairs takes (a.n_pairs, or more where a is a sample of it).
+int run_mixed(gk_ctx *ctx, const MixedConfig &c, const gkd::FilterArgs &a, uint64_t n_pairs,
+              uint32_t wmax, uint32_t layout, hipStream_t hs)
+{
+    hipError_t e;
+    if (mixed_direct(ctx, c, a, n_pairs, wmax)) {
+        const gkd::MixedArgs x = direct_args(c, n_pairs, wmax);
+        gk_detail_log(ctx, "gk_filter_mixed: %llu pairs, direct launch (tile %u, %u per lane, "
+                      "sort by e %u)", (unsigned long long)a.n_pairs, x.tile, x.ppl, x.sort_e);
+        e = launch_direct(c, a, x, n_pairs, wmax, layout, hs);
+        if (e != hipSuccess)
+            return hip_fail(ctx, e, "gk_filter_mixed: launch");
+        return GK_OK;
+    }
+    gkd::MixedArgs x{};
+    const int st = mixed_args(ctx, c, wmax, layout, x);
+    if (st != GK_OK)
+        return st;
+    // Graph: the captured sequence (reset, persistent kernel) reads the batch
+    // from the context's device table, which a copy on the stream fills before
+    // each replay; so one graph serves every batch of a given shape (words per
+    // mask, layout) and tuning, captured the first time that pair is seen.
+    const uint32_t shape[8] = {wmax <= 4 ? 4u : (wmax <= 10 ? 10u : 16u), layout, x.tile,
+                               x.ppl, x.sort_e, x.blocks, 0u, 0u};
+    std::vector<uint8_t> key(sizeof shape);
+    std::memcpy(key.data(), shape, sizeof shape);
+    const bool capture = !ctx->graph_exec || key != ctx->graph_key;
+    gk_detail_log(ctx, "gk_filter_mixed: %llu pairs, graph %s (words per mask up to %u, tile %u, "
+                  "%u per lane, sort by e %u, %u workgroups)", (unsigned long long)a.n_pairs,
+                  capture ? "captured" : "replayed", shape[0], x.tile, x.ppl, x.sort_e, x.blocks);
+    if (capture) {
+        drop_graph(ctx);
+        hipGraph_t graph = nullptr;
+        e = hipStreamBeginCapture(ctx->capture_stream, hipStreamCaptureModeRelaxed);
+        if (e != hipSuccess)
+            return hip_fail(ctx, e, "gk_filter_mixed: begin capture");
+        hipError_t le = gkd::launch_mixed_table(x, wmax, layout, ctx->capture_stream);
+        e = hipStreamEndCapture(ctx->capture_stream, &graph);
+        if (le != hipSuccess || e != hipSuccess) {
+            if (graph)
+                (void)hipGraphDestroy(graph);
+            return hip_fail(ctx, le != hipSuccess ? le : e, "gk_filter_mixed: capture");
+        }
+        e = hipGraphInstantiate(&ctx->graph_exec, graph, nullptr, nullptr, 0);
+        (void)hipGraphDestroy(graph);
+        if (e != hipSuccess) {
+            ctx->graph_exec = nullptr;
+            return hip_fail(ctx, e, "gk_filter_mixed: instantiate");
+        }
+        ctx->graph_key = key;
+    }
+    // This call's table: a pinned slot no earlier replay still reads.
+    const int slot = (int)(ctx->table_next++ % gk_ctx::TABLE_RING);
+    if (ctx->table_used[slot] && (e = hipEventSynchronize(ctx->table_ev[slot])) != hipSuccess)
+        return hip_fail(ctx, e, "gk_filter_mixed: table slot");
+    e = copy_table(ctx, slot, a, x.tile, hs);
+    if (e == hipSuccess)
+        e = hipGraphLaunch(ctx->graph_exec, hs);
+    if (e == hipSuccess)
+        e = hipEventRecord(ctx->table_ev[slot], hs);
+    if (e != hipSuccess)
+        return hip_fail(ctx, e, "gk_filter_mixed: graph launch");
+    ctx->table_used[slot] = true;
     return GK_OK;
 }
 
@@ -826,72 +907,7 @@ int gk_filter_mixed(gk_ctx *ctx, const gk_batch *b, void *stream)
     if ((st = ensure_mixed_scratch(ctx)) != GK_OK)
         return st;
     const uint32_t wmax = (b->max_read_len + 31) / 32;
-    gkd::MixedArgs x = direct_args(ctx, b->n_pairs, wmax);
-    hipError_t e;
-    const hipStream_t hs = (hipStream_t)stream;
-    // Direct form unless a tuning was set and the batch leaves compute units
-    // without a tile: one launch without the argument copy, the graph's launch
-    // and the counter reset before it (60,001 pairs: 21 against about 55 us;
-    // 2^24 pairs: 805 against 850).  Always for variant semantics (their own
-    // kernels) and batches of more than one launch chunk (2^30 pairs).
-    const uint64_t n_tiles = (b->n_pairs + x.tile - 1) / x.tile;
-    if (!ctx->use_graph || a.flags != 0u || b->n_pairs > (1ull << 30) ||
-        ctx->mixed.untouched() || n_tiles >= (uint64_t)ctx->cu_count) {
-        gk_detail_log(ctx, "gk_filter_mixed: %llu pairs, direct launch (tile %u, %u per lane, "
-                      "sort by e %u)", (unsigned long long)b->n_pairs, x.tile, x.ppl, x.sort_e);
-        e = launch_direct(ctx, a, x, wmax, b->read_layout, hs);
-        if (e != hipSuccess)
-            return hip_fail(ctx, e, "gk_filter_mixed: launch");
-        return GK_OK;
-    }
-    if ((st = mixed_args(ctx, ctx->mixed, wmax, b->read_layout, x)) != GK_OK)
-        return st;
-    // Graph: the captured sequence (reset, persistent kernel) reads the batch
-    // from the context's device table, which a copy on the stream fills before
-    // each replay; so one graph serves every batch of a given shape (words per
-    // mask, layout) and tuning, captured the first time that pair is seen.
-    const uint32_t shape[8] = {wmax <= 4 ? 4u : (wmax <= 10 ? 10u : 16u), b->read_layout, x.tile,
-                               x.ppl, x.sort_e, x.blocks, 0u, 0u};
-    std::vector<uint8_t> key(sizeof shape);
-    std::memcpy(key.data(), shape, sizeof shape);
-    const bool capture = !ctx->graph_exec || key != ctx->graph_key;
-    gk_detail_log(ctx, "gk_filter_mixed: %llu pairs, graph %s (words per mask up to %u, tile %u, "
-                  "%u per lane, sort by e %u, %u workgroups)", (unsigned long long)b->n_pairs,
-                  capture ? "captured" : "replayed", shape[0], x.tile, x.ppl, x.sort_e, x.blocks);
-    if (capture) {
-        drop_graph(ctx);
-        hipGraph_t graph = nullptr;
-        e = hipStreamBeginCapture(ctx->capture_stream, hipStreamCaptureModeRelaxed);
-        if (e != hipSuccess)
-            return hip_fail(ctx, e, "gk_filter_mixed: begin capture");
-        hipError_t le = gkd::launch_mixed_table(x, wmax, b->read_layout, ctx->capture_stream);
-        e = hipStreamEndCapture(ctx->capture_stream, &graph);
-        if (le != hipSuccess || e != hipSuccess) {
-            if (graph)
-                (void)hipGraphDestroy(graph);
-            return hip_fail(ctx, le != hipSuccess ? le : e, "gk_filter_mixed: capture");
-        }
-        e = hipGraphInstantiate(&ctx->graph_exec, graph, nullptr, nullptr, 0);
-        (void)hipGraphDestroy(graph);
-        if (e != hipSuccess) {
-            ctx->graph_exec = nullptr;
-            return hip_fail(ctx, e, "gk_filter_mixed: instantiate");
-        }
-        ctx->graph_key = key;
-    }
-    // This call's table: a pinned slot no earlier replay still reads.
-    const int slot = (int)(ctx->table_next++ % gk_ctx::TABLE_RING);
-    if (ctx->table_used[slot] && (e = hipEventSynchronize(ctx->table_ev[slot])) != hipSuccess)
-        return hip_fail(ctx, e, "gk_filter_mixed: table slot");
-    e = copy_table(ctx, slot, a, x.tile, hs);
-    if (e == hipSuccess)
-        e = hipGraphLaunch(ctx->graph_exec, hs);
-    if (e == hipSuccess)
-        e = hipEventRecord(ctx->table_ev[slot], hs);
-    if (e != hipSuccess)
-        return hip_fail(ctx, e, "gk_filter_mixed: graph launch");
-    ctx->table_used[slot] = true;
-    return GK_OK;
+    return run_mixed(ctx, ctx->mixed, a, b->n_pairs, wmax, b->read_layout, (hipStream_t)stream);
 }
 
 int gk_filter_mixed_noalloc(gk_ctx *ctx, const gk_batch *b, void *stream)
@@ -910,9 +926,9 @@ int gk_filter_mixed_noalloc(gk_ctx *ctx, const gk_batch *b, void *stream)
     if (!g.ok)
         return fail(ctx, GK_EDEVICE, "gk_filter_mixed_noalloc: hipSetDevice failed");
     const uint32_t wmax = (b->max_read_len + 31) / 32;
-    const gkd::MixedArgs x = direct_args(ctx, b->n_pairs, wmax);
+    const gkd::MixedArgs x = direct_args(ctx->mixed, b->n_pairs, wmax);
     const hipError_t e =
-        launch_direct(ctx, a, x, wmax, b->read_layout, (hipStream_t)stream);
+        launch_direct(ctx->mixed, a, x, b->n_pairs, wmax, b->read_layout, (hipStream_t)stream);
     if (e != hipSuccess)
         return hip_fail(ctx, e, "gk_filter_mixed_noalloc: launch");
     return GK_OK;
@@ -1049,7 +1065,8 @@ int gk_tune_mixed(gk_ctx *ctx, const gk_batch *b, void *stream, uint64_t sample_
     a.accept_bits = nullptr;
 
     // Key: device, CU count, words per mask, layout, threshold mode, batch
-    // size (power-of-two bucket).
+    // size (power-of-two bucket); lines of tunings timed on other kernels than
+    // those the call runs lack the last part.
     hipDeviceProp_t prop;
     if (hipGetDeviceProperties(&prop, ctx->device) != hipSuccess)
         return fail(ctx, GK_EDEVICE, "gk_tune_mixed: device properties");
@@ -1057,7 +1074,7 @@ int gk_tune_mixed(gk_ctx *ctx, const gk_batch *b, void *stream, uint64_t sample_
     k << prop.gcnArchName << "|cu=" << ctx->cu_count << "|w=" << wmax
       << "|layout=" << b->read_layout << "|e="
       << (b->e ? std::string("per-pair") : "uniform:" + std::to_string(b->e_uniform))
-      << "|n=2^" << (int)std::floor(std::log2((double)n_full));
+      << "|n=2^" << (int)std::floor(std::log2((double)n_full)) << "|as-called";
     const std::string key = k.str();
     std::ostringstream rep;
 
@@ -1113,70 +1130,75 @@ int gk_tune_mixed(gk_ctx *ctx, const gk_batch *b, void *stream, uint64_t sample_
     if (hipEventCreate(&e0) != hipSuccess || hipEventCreate(&e1) != hipSuccess)
         return fail(ctx, GK_EDEVICE, "gk_tune_mixed: hipEventCreate");
     const hipStream_t s = (hipStream_t)stream;
-    int full_bpc = 0;
-    MixedConfig best;
-    float best_ms = -1.f;
     rep << "{\"key\": \"" << key << "\", \"source\": \"measured\", \"sample_pairs\": " << a.n_pairs
         << ", \"candidates\": [";
-    bool first = true;
     hipError_t err = hipSuccess;
-    for (uint32_t tile : {2048u, 4096u, 8192u}) {
-        for (uint32_t ppl : {1u, 2u}) {
-            if (ppl == 2 && wmax > 10)
-                continue;                      // two pairs per lane only up to 10 words
-            if ((err = gkd::mixed_blocks_per_cu(wmax, b->read_layout, gkd::mixed_tile(tile), ppl,
-                                                &full_bpc)) !=
-                hipSuccess)
+    // Median time of five calls on the sample, in the form the whole batch takes.
+    auto time_calls = [&](const MixedConfig &c, float &ms) {
+        float times[5] = {};
+        for (int k = -1; k < 5; ++k) {
+            if ((err = hipEventRecord(e0, s)) != hipSuccess)
                 break;
-            for (uint32_t sort_e : {0u, 1u})
-                for (uint32_t bpc : {0u, (uint32_t)std::max(1, full_bpc / 2)}) {
-                    MixedConfig c{tile, ppl, sort_e, bpc};
-                    gkd::MixedArgs x{};
-                    if ((st = mixed_args(ctx, c, wmax, b->read_layout, x)) != GK_OK) {
-                        (void)hipEventDestroy(e0);
-                        (void)hipEventDestroy(e1);
-                        return st;
-                    }
-                    // (slot 0: no earlier replay reads it once this ends)
-                    if ((err = hipDeviceSynchronize()) == hipSuccess)
-                        err = copy_table(ctx, 0, a, x.tile, s);
-                    float times[5];
-                    for (int rep_i = -1; rep_i < 5 && err == hipSuccess; ++rep_i) {
-                        err = hipEventRecord(e0, s);
-                        if (err == hipSuccess)
-                            err = gkd::launch_mixed_table(x, wmax, b->read_layout, s);
-                        if (err == hipSuccess)
-                            err = hipEventRecord(e1, s);
-                        if (err == hipSuccess)
-                            err = hipEventSynchronize(e1);
-                        float ms = 0;
-                        if (err == hipSuccess)
-                            err = hipEventElapsedTime(&ms, e0, e1);
-                        if (rep_i >= 0)
-                            times[rep_i] = ms;
-                    }
-                    if (err != hipSuccess)
-                        break;
-                    std::sort(times, times + 5);
-                    const float med = times[2];
-                    rep << (first ? "" : ", ") << "{\"tile\": " << tile << ", \"ppl\": " << ppl
-                        << ", \"sort_e\": " << sort_e << ", \"blocks_per_cu\": " << bpc
-                        << ", \"ms\": " << med << "}";
-                    first = false;
-                    if (best_ms < 0 || med < best_ms) {
-                        best_ms = med;
-                        best = c;
-                    }
-                }
-            if (err != hipSuccess)
+            if ((st = run_mixed(ctx, c, a, n_full, wmax, b->read_layout, s)) != GK_OK)
+                return false;
+            float t = 0;
+            if ((err = hipEventRecord(e1, s)) != hipSuccess ||
+                (err = hipEventSynchronize(e1)) != hipSuccess ||
+                (err = hipEventElapsedTime(&t, e0, e1)) != hipSuccess)
                 break;
+            if (k >= 0)
+                times[k] = t;
         }
-        if (err != hipSuccess)
+        std::sort(times, times + 5);
+        ms = times[2];
+        return err == hipSuccess;
+    };
+    std::vector<MixedConfig> candidates;
+    for (uint32_t tile : {2048u, 4096u, 8192u})
+        for (uint32_t ppl : {1u, 2u})
+            for (uint32_t sort_e : {0u, 1u})
+                for (uint32_t half : {0u, 1u}) {
+                    if (ppl == 2 && wmax > 10)
+                        continue;              // two pairs per lane only up to 10 words
+                    MixedConfig c{tile, ppl, sort_e, 0u};
+                    if (half) {
+                        int full = 0;
+                        const hipError_t q = gkd::mixed_blocks_per_cu(
+                            wmax, b->read_layout, gkd::mixed_tile(tile), ppl, &full);
+                        err = err != hipSuccess ? err : q;
+                        c.blocks_per_cu = (uint32_t)std::max(1, full / 2);
+                        if (mixed_direct(ctx, c, a, n_full, wmax))
+                            continue;          // resident workgroups in the captured form only
+                    }
+                    candidates.push_back(c);
+                }
+    // The defaults leave tile and lanes to the batch size; they stay unless
+    // another tuning is faster by more than repeats of one differ.
+    MixedConfig best;
+    float default_ms = 0;
+    const bool log = ctx->log;
+    ctx->log = false;                          // (not a line for each of these calls)
+    bool ok = err == hipSuccess && time_calls(best, default_ms);
+    float best_ms = default_ms;
+    const char *sep = "";
+    for (const MixedConfig &c : candidates) {
+        float ms = default_ms;
+        if (!ok || !(ok = c.untouched() || time_calls(c, ms)))
             break;
+        rep << sep << "{\"tile\": " << c.tile << ", \"ppl\": " << c.ppl << ", \"sort_e\": "
+            << c.sort_e << ", \"blocks_per_cu\": " << c.blocks_per_cu << ", \"ms\": " << ms << "}";
+        sep = ", ";
+        if (ms < best_ms && ms < 0.98f * default_ms) {
+            best_ms = ms;
+            best = c;
+        }
     }
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
-    if (err != hipSuccess)
+    ctx->log = log;
+    if (st != GK_OK)
+        return st;
+    if (!ok)
         return hip_fail(ctx, err, "gk_tune_mixed: timing");
     ctx->mixed = best;
     drop_graph(ctx);
