@@ -46,21 +46,24 @@ inline uint32_t verify_tile(uint64_t n_pairs)
 // 85 against 98.  One threshold up to 7: full waves, however few of the pairs are
 // listed: 2^22 pairs of 100 bases at e = 5 57 against 67 us, 2^26 of 250 at e = 7
 // 1,742 against 2,351 with a third listed and 620 against 1,096 with a fifteenth.
-// The four launches take 20 us before any work, so smaller batches stay with one.
+// The four launches take 20 us before any work, so smaller batches stay with one;
+// from 16 on that is up to one tile per compute unit (250 bases, e = 25: 65,536
+// pairs 30 us by tile and 36 by list, 98,304 pairs 42 and 36).
 //
 // A threshold per pair: the list is in order of (words, e) over the batch, which
 // takes each read's candidates apart, so the reads are copied row by row first.
-// From about 12 candidates per read on that pays at any share listed (16 and 24
-// to 28 per read, tile against list: 2^22 pairs 199 and 161 us, 219 and 143; 2^26
-// pairs 2,603 and 2,314, 2,477 and 2,044), with 7 only at some (2^22 pairs 218
-// and 190 us with a fifth listed, 97 and 108 with a twentieth), with 3 at none.
+// From about 12 candidates per read on that pays at any share listed (13 per
+// read, 3 * 2^19 pairs, tile against list: 111 and 91 us with a sixth listed, 90
+// and 71 with a twentieth, but 2^20 pairs 71 and 80, 51 and 67; 24 per read, 2^26
+// pairs: 2,477 and 2,044), with 7 only at some (2^22 pairs 218 and 190 us with a
+// fifth listed, 97 and 108 with a twentieth), with 3 at none.
 inline bool verify_lists(const FilterArgs &a)
 {
     if (a.e_pair)
-        return a.pair_read && a.n_reads > 0 && a.n_pairs >= (3u << 20) &&
+        return a.pair_read && a.n_reads > 0 && a.n_pairs >= (3u << 19) &&
                a.n_pairs / 12u >= a.n_reads;
     const uint32_t e = a.e_uniform;
-    return e <= GK_VERIFY_MAX_E && a.n_pairs >= (e >= 16  ? 1u << 17
+    return e <= GK_VERIFY_MAX_E && a.n_pairs >= (e >= 16  ? (1u << 16) + 1u
                                                  : e >= 12 ? 1u << 18
                                                  : e >= 8  ? 1u << 19
                                                            : 1u << 22);

@@ -82,6 +82,36 @@ def test_one_small_threshold(gkctx, ref, m, e):
             check(dist.cpu().numpy().view(np.uint16), expected(want, pick, accept), f"m={m} e={e}")
 
 
+@pytest.mark.parametrize("n", [65_536, 65_537])
+def test_one_large_threshold(gkctx, ref, n):
+    rng = np.random.default_rng(n)
+    gk.gk_load_reference(gkctx, ref)
+    reads, off, pos, want = small_thresholds(rng, ref, 130, 20)
+    dr = device.encode_reads(gkctx, reads, off, max_len=130)
+    pick = rng.integers(0, len(pos), n).astype(np.uint32)
+    codes = rng.choice(np.array([0, 1], np.uint8), n, p=[0.3, 0.7])
+    for accept in (codes, None):
+        say(f"case: verify listed e=20 n={n} codes={accept is not None}")
+        check(distances(gkctx, dr, pick, pos[pick], 20, accept), expected(want, pick, accept),
+              f"e=20 n={n}")
+
+
+@pytest.mark.parametrize("n,kinds", [((3 << 19) - 1, 3000), (3 << 19, 3000), (3 << 19, 131_072),
+                                     (3 << 19, 131_073)])
+def test_rule_of_candidates_per_read(gkctx, ref, n, kinds):
+    """Both sides of the rule's limits: pairs of the batch, pairs per read."""
+    rng = np.random.default_rng(n + kinds)
+    gk.gk_load_reference(gkctx, ref)
+    reads, off, pos, e, want = some_pairs(rng, ref, 3000, 150)
+    dr = device.encode_reads(gkctx, np.tile(reads, -(-kinds // 3000)), np.concatenate(
+        [off[:-1] + off[-1] * np.uint64(k) for k in range(-(-kinds // 3000))])[:kinds + 1]
+        if kinds > 3000 else off, max_len=150)
+    pick = rng.integers(0, min(kinds, dr.n_reads), n).astype(np.uint32)
+    say(f"case: verify rule n={n} reads={dr.n_reads}")
+    got = distances(gkctx, dr, pick, pos[pick % 3000], e[pick % 3000])
+    check(got, want[pick % 3000], f"n={n} reads={dr.n_reads}")
+
+
 @pytest.mark.parametrize("per_pair", [False, True])
 def test_without_scratch(ref, per_pair):
     """Where the list cannot be allocated, and under stream capture, the same
