@@ -637,7 +637,7 @@ gkd::MixedArgs direct_args(const MixedConfig &c, uint64_t n_pairs, uint32_t wmax
 hipError_t launch_direct(const MixedConfig &c, const gkd::FilterArgs &a, const gkd::MixedArgs &x,
                          uint64_t n_pairs, uint32_t wmax, uint32_t layout, hipStream_t s)
 {
-    if (c.untouched() && gkd::mixed_unsorted(n_pairs, wmax))
+    if (c.untouched() && gkd::mixed_unsorted(a, n_pairs, wmax))
         return gkd::launch_filter(a, wmax, layout, 0, s);
     return gkd::launch_mixed(a, x, wmax, layout, s);
 }

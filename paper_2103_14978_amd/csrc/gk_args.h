@@ -124,10 +124,13 @@ inline uint32_t mixed_auto_lanes(uint64_t n_pairs, uint32_t wmax)
 // Batches too small for the sort's steps to pay: with 8 or 4 lanes per pair
 // the plain kernel takes 8 to 11 us for up to 16,384 mixed pairs, the sorted one
 // 14 and more; at 4 words per mask and fewer it needs no lanes for that (65,536
-// pairs of 64 to 128 bases: 7.2 against 9.7 us; 262,144: 14.9 against 12.9).
-inline bool mixed_unsorted(uint64_t n_pairs, uint32_t wmax)
+// pairs of 64 to 128 bases: 7.2 against 9.7 us; 262,144: 14.9 against 12.9).  One
+// threshold above 31 leaves nothing to sort, and lanes share only the first 31
+// shifts (500 bases, e = 200: 30,000 pairs 217 us plain, 394 sorted; 196,608 pairs
+// 536 and 677, 262,144 pairs 710 and 680).
+inline bool mixed_unsorted(const FilterArgs &a, uint64_t n_pairs, uint32_t wmax)
 {
-    return n_pairs <= (wmax <= 4 ? 1u << 17 : 24576u);
+    return n_pairs <= (!a.e_pair && a.e_uniform > 31u ? 3u << 16 : wmax <= 4 ? 1u << 17 : 24576u);
 }
 
 // Whether the plain call sorts its pairs first (the ordered form of the mixed

@@ -101,3 +101,22 @@ def test_small_batches_sorted(gkctx, ref, lengths):
                                    with_bits=True)
         assert_same(a, s, want[0][:n], want[1][:n], f"small n={n}")
         check_bits(bits, want[0][:n], f"small n={n}")
+
+
+@pytest.mark.parametrize("m", [100, 250, 500])
+def test_one_large_threshold(gkctx, ref, m):
+    """Up to 3 * 2^16 pairs under one threshold above 31 go as they come."""
+    gk.gk_load_reference(gkctx, ref)
+    n_max = (3 << 16) + 1
+    ps = gen.pairs(ref, seed=75, n_reads=n_max // 3, lengths=[m // 2, m], cand_kind=gen.CAND_GEOM,
+                   cand_param=1 / 4, cand_cap=16, true_frac=0.5, edit_kind=gen.EDIT_RATE,
+                   edit_param=1.2, e_frac=0.12)
+    assert ps.n_pairs >= n_max
+    e = 33
+    want = run_oracle(ref, ps.reads, ps.read_off, ps.pair_read, ps.cand_pos, e)
+    for n in (1000, 24_577, 131_073, 3 << 16, n_max):
+        say(f"case: one large threshold m={m} n={n}")
+        a, s, bits = run_gpu_mixed(gkctx, ps.reads, ps.read_off, ps.pair_read[:n],
+                                   ps.cand_pos[:n], e, max_read_len=m, with_bits=True)
+        assert_same(a, s, want[0][:n], want[1][:n], f"large threshold n={n}")
+        check_bits(bits, want[0][:n], f"large threshold n={n}")
