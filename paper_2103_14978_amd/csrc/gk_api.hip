@@ -1193,6 +1193,12 @@ int gk_tune_mixed(gk_ctx *ctx, const gk_batch *b, void *stream, uint64_t sample_
             best = c;
         }
     }
+    // (timed once more: the first call's batch may have been cold)
+    if (ok && !best.untouched() && (ok = time_calls(MixedConfig{}, default_ms)) &&
+        best_ms >= 0.98f * default_ms) {
+        best_ms = default_ms;
+        best = MixedConfig{};
+    }
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
     ctx->log = log;
