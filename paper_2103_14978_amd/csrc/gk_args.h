@@ -87,15 +87,6 @@ inline uint32_t split_lanes(uint64_t n_pairs, uint32_t e, uint32_t words)
     return n_pairs <= 49152 && work >= 100u ? 1u : 0u;
 }
 
-// A table of few batches, passed as kernel arguments (at most 4 KiB): the
-// launch then waits for no copy of its table.
-constexpr uint32_t INLINE_BATCHES = 24;
-struct InlineTable {
-    uint32_t n_batches;
-    uint32_t prefix[INLINE_BATCHES + 1];
-    FilterArgs args[INLINE_BATCHES];
-};
-
 // Pairs per tile of the mixed launch for a value of GK_OPT_MIXED_TILE.
 inline uint32_t mixed_tile(uint32_t option) { return option / 4; }
 
@@ -161,5 +152,19 @@ struct MixedArgs {
     uint32_t n_tiles;            // tiles of a host table, else 0
     uint32_t lg;                 // direct form: 2^lg lanes per pair (0 or 1)
 };
+
+// A table of few batches, passed as kernel arguments: the launch then waits for
+// no copy of its table.  As many as fit beside the kernel's other arguments in
+// the 4 KiB that a launch may pass.
+constexpr uint32_t INLINE_BATCHES =
+    (4096 - sizeof(FilterArgs) - sizeof(MixedArgs) - 2 * sizeof(uint32_t)) /
+    (sizeof(FilterArgs) + sizeof(uint32_t));
+struct InlineTable {
+    uint32_t n_batches;
+    uint32_t prefix[INLINE_BATCHES + 1];
+    FilterArgs args[INLINE_BATCHES];
+};
+static_assert(sizeof(FilterArgs) + sizeof(MixedArgs) + sizeof(InlineTable) <= 4096,
+              "passed to one launch");
 
 }  // namespace gkd
