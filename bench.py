@@ -750,6 +750,15 @@ def main() -> int:
         served = served_section(args, log, args.served_pool,
                                 [float(x) for x in args.served_lambdas.split(",")],
                                 args.served_duration)
+        # The line keeps each rate's outcome; its ticks and slowest requests go
+        # to the log, so that the whole line fits the tail of a captured output.
+        keep_keys = ("lambda", "requests", "unfinished", "p50_ms", "p99_ms", "pairs_per_s",
+                     "checked_submissions", "mismatched_submissions", "ticks", "skipped")
+        for mode_name, rows in served["by_rate"].items():
+            for row in rows:
+                log(f"{mode_name} {json.dumps(row)}")
+            served["by_rate"][mode_name] = [{k: row[k] for k in keep_keys if k in row}
+                                            for row in rows]
     slo = served["served_at_slo"] if served else None
 
     out = {
