@@ -339,7 +339,9 @@ int gk_verify(gk_ctx *ctx, const gk_batch *batch, const uint8_t *accept, uint16_
                                             2048, 4096 (default) or 8192.
                                             While no GK_OPT_MIXED_* differs
                                             from its default, the batch size
-                                            picks 512, 1024 or 2048 pairs.  */
+                                            picks 256 to 2048 pairs, two lanes
+                                            for each of a small batch, or no
+                                            sort for the smallest.           */
 #define GK_OPT_MIXED_PAIRS_PER_LANE 3  /* gk_filter_mixed: 1 (default) or 2
                                             pairs per lane per chunk        */
 #define GK_OPT_MIXED_SORT_E         4  /* gk_filter_mixed: 1 (default) sorts

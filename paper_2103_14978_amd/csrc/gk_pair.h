@@ -665,9 +665,8 @@ struct PairData {
 // base[i] for i < 2^30 (reads, and the pairs of a launch) of elements of up to
 // 4 bytes: a 32-bit offset from a scalar base, no 64-bit address per lane.
 // With the window loads by one base for both copies of the planes, that is 2%
-// fewer vector instructions per pair: 3e6 pairs of 150 bases at e = 7 over
-// 775 MB of planes went from 86.6 to 83.7 us, 2^23 of 250 at e = 25 from 746 to
-// 736, a mixed batch of 2^24 (64 to 300 bases) from 807 to 789.
+// fewer vector instructions per pair: 2^23 pairs of 250 bases at e = 25 went from
+// 746 to 736 us, a mixed batch of 2^24 (64 to 300 bases) from 807 to 789.
 template <typename T>
 __device__ __forceinline__ T elem(const T *base, uint32_t i)
 {

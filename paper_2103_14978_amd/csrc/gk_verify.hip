@@ -30,9 +30,12 @@
 // that a wave's lanes load alike and run alike, and its waves take 64 of the
 // list at a time, the longest first.  Distances replace the pairs' entries in
 // LDS and go to memory in pair order.  One launch; listing the whole batch
-// first took four to six (2^22 pairs of 100 bases at e = 5: 76 -> 63 us, 1,000
-// pairs 22 -> 9; 2^20 pairs of mixed lengths and thresholds 113 -> 72, 1,000
-// pairs 98 -> 39).
+// first takes four to six (1,000 pairs of 100 bases at e = 5: 22 -> 9 us; 2^20
+// pairs of mixed lengths and thresholds 113 -> 72, 1,000 pairs 98 -> 39).
+//
+// List form: large batches whose tiles would leave waves partly filled go through
+// one list of all their pairs (verify_lists; 2^22 pairs of 100 bases at e = 5 62
+// us, 70 by tile).
 #include <algorithm>
 
 #include "gk_pair.h"
