@@ -312,7 +312,8 @@ int gk_filter_host(gk_ctx *ctx, const gk_host_batch *batch);
  * verified, for pairs gk_filter marks GK_UNDEFINED or GK_INVALID, and for
  * e_i > GK_VERIFY_MAX_E.
  * Asynchronous on stream.  Large batches (from 2^16 pairs under one threshold,
- * from 3 * 2^19 with a threshold per pair and 12 or more pairs per read) use
+ * from 3 * 2^19 with a threshold per pair and 12 or more pairs per read, from 2^24
+ * with 7 or more) use
  * context-owned scratch: one pair list of up to 2^30 entries and a word per 4096
  * pairs, with a threshold per pair also 192 KiB and a copy of the encoded reads,
  * allocated on first use and grown as needed.  Where it cannot be allocated, and

@@ -55,13 +55,13 @@ inline uint32_t verify_tile(uint64_t n_pairs)
 // From about 12 candidates per read on that pays at any share listed (13 per
 // read, 3 * 2^19 pairs, tile against list: 111 and 91 us with a sixth listed, 90
 // and 71 with a twentieth, but 2^20 pairs 71 and 80, 51 and 67; 24 per read, 2^26
-// pairs: 2,477 and 2,044), with 7 only at some (2^22 pairs 218 and 190 us with a
-// fifth listed, 97 and 108 with a twentieth), with 3 at none.
+// pairs: 2,477 and 2,044), with 7 from 2^24 pairs on (757 and 670 us, 366 and 347;
+// 2^22 pairs 218 and 190, 97 and 108), with 3 at none.
 inline bool verify_lists(const FilterArgs &a)
 {
     if (a.e_pair)
         return a.pair_read && a.n_reads > 0 && a.n_pairs >= (3u << 19) &&
-               a.n_pairs / 12u >= a.n_reads;
+               a.n_pairs / (a.n_pairs >= (1u << 24) ? 7u : 12u) >= a.n_reads;
     const uint32_t e = a.e_uniform;
     return e <= GK_VERIFY_MAX_E && a.n_pairs >= (e >= 16  ? (1u << 16) + 1u
                                                  : e >= 12 ? 1u << 18

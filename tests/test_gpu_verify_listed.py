@@ -97,7 +97,8 @@ def test_one_large_threshold(gkctx, ref, n):
 
 
 @pytest.mark.parametrize("n,kinds", [((3 << 19) - 1, 3000), (3 << 19, 3000), (3 << 19, 131_072),
-                                     (3 << 19, 131_073)])
+                                     (3 << 19, 131_073), (1 << 24, 2_396_745),
+                                     (1 << 24, 2_396_746)])
 def test_rule_of_candidates_per_read(gkctx, ref, n, kinds):
     """Both sides of the rule's limits: pairs of the batch, pairs per read."""
     rng = np.random.default_rng(n + kinds)
