@@ -530,7 +530,7 @@ def main() -> int:
                   "filter_plus_verify_pairs_per_s": round(n_pairs / (ms_fv / 1e3), 1),
                   "speedup_vs_verify_all": round(ms_all / ms_fv, 3),
                   "sampled_mismatches": vmism,
-                  "what": "banded bit-parallel edit distance (cap e+1) of the GK_ACCEPT pairs"}
+                  "what": "exact edit distance (cap e+1) of the GK_ACCEPT pairs"}
         log(f"verify {ms_after:.3f} ms for {accepted} accepted pairs; filter+verify "
             f"{ms_fv:.3f} ms vs verify-all {ms_all:.3f} ms")
         del dist
@@ -687,8 +687,8 @@ def main() -> int:
                 "line_rate": ({"lines_per_launch": int(traffic // 128),
                                "G_lines_per_s": round(traffic / 128 / k_avg_s / 1e9, 1),
                                "what": "counted traffic / 128 B over the mean kernel time; "
-                                       "the random window gathers (one line per pair) hold "
-                                       "the launch near 50 G lines/s"}
+                                       "the random window gathers (one line per pair) "
+                                       "bound the launch"}
                               if traffic else None),
                 "kernel_source_hash": khash}
 
