@@ -29,8 +29,10 @@
 //               runs of one (W, k_max) goes to the chunks unsorted (a constant
 //               threshold over 2^20 pairs of 150 bases, e = 3: 25 us, 32 sorted,
 //               24 without looking; 2^22 of 250, e = 1: 87, 106 and 102), and
-//               widths of 6 and 12 words keep the waves per SIMD of the plain
-//               kernel (5 and 3, against 4 and 2 in the next wider).
+//               widths of 6, 8 and 12 words keep the waves per SIMD of the plain
+//               kernel (5, 4 and 3, against 4, 4 and 2 in the next wider) and
+//               the general path, where all pairs take it, near the read's width
+//               (2^20 pairs of 200 bases, e = 32 to 59: 358 us, 435 at 10 words).
 #include "gk_pair.h"
 
 namespace gkd {
@@ -238,18 +240,24 @@ void k_mixed(FilterArgs a0, MixedArgs x, Batches batches)
         for (uint32_t j0 = tid; j0 < x.tile; j0 += 1024) {
             PairIdx p[4];
             uint32_t m[4], un[4];
+            // (a tile of 512 has two: no loads for the others)
+            const bool four = FORM != ORDERED || x.tile > 512u;
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-                const uint32_t i = base + j0 + 256u * q;
-                p[q] = load_idx(a, i < n ? i : n - 1u);
+                if (q < 2 || four) {
+                    const uint32_t i = base + j0 + 256u * q;
+                    p[q] = load_idx(a, i < n ? i : n - 1u);
+                }
             }
             const uint8_t *flag = a.read_has_n ? a.read_has_n
                                                : reinterpret_cast<const uint8_t *>(a.read_len);
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-                const uint32_t r = p[q].r < a.n_reads ? p[q].r : 0u;
-                m[q] = a.read_len[r];
-                un[q] = flag[r];
+                if (q < 2 || four) {
+                    const uint32_t r = p[q].r < a.n_reads ? p[q].r : 0u;
+                    m[q] = a.read_len[r];
+                    un[q] = flag[r];
+                }
             }
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
@@ -547,6 +555,8 @@ hipError_t launch_ordered_l(const FilterArgs &a, const MixedArgs &x, uint32_t wm
 {
     if (wmax <= 6)
         return launch_mixed_wl<6, L, true>(a, x, s);
+    if (wmax <= 8)
+        return launch_mixed_wl<8, L, true>(a, x, s);
     if (wmax <= 10)
         return launch_mixed_wl<10, L, true>(a, x, s);
     if (wmax <= 12)

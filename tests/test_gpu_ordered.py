@@ -37,7 +37,7 @@ def thresholds(kind, n, m):
 
 @pytest.mark.parametrize("kind", ["constant", "far", "runs of 64", "one tile differs",
                                   "runs of 96"])
-@pytest.mark.parametrize("lengths", [(150,), (100, 190), (250,), (330, 370), (500,)],
+@pytest.mark.parametrize("lengths", [(150,), (100, 190), (250,), (300,), (330, 370), (500,)],
                          ids=lambda v: "x".join(map(str, v)))
 def test_thresholds_in_runs(gkctx, ref, lengths, kind):
     import torch
